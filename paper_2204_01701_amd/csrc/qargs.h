@@ -88,11 +88,13 @@ struct BwdDataArgs {
     void *dx;
     float *ws;  // split-K partials [split][M][C]
     const void *zero;
-    int N, H, W, C, O, KH, KW, SH, SW, PH, PW, HO, WO;
+    int N, H, W, C, O, KH, KW, SH, SW, PH, PW, HO, WO;  // O: channels of G, T_a, T_b as passed (zero-padded or not)
     int M, K;  // M = N*H*W input pixels, K = KH*KW*O per term
     int row_tiles, col_tiles, splits, stages_per_split, stages_total;
     int neuron;       // NEURON_*: the epilogue adds G (T4 + identity) or multiplies by 2 X (T2)
-    const void *xin;  // X (N x H x W x C) for T2, else unused
+    // N x H x W x C operand of the neuron type's last step: X (T2, T2&4), or G
+    // as the caller passed it (T4 + identity; gy may be a copy padded to O channels)
+    const void *xin;
     // Position-major pixel order (channel-aligned kernels, the proposed neuron
     // only): GEMM column m is input position m / N of image m % N, at NHWC row
     // (m % N) H W + m / N; a tile's K range is the taps whose output pixel lies
@@ -114,7 +116,9 @@ struct BwdWeightArgs {
     int M, KP;  // M = N*HO*WO output pixels (reduction), KP = KH*KW*C
     int row_tiles, col_tiles, splits, stages_per_split, stages_total;
     int want_db;
-    int C_out;  // channels of dW_t as stored (< C when X arrives zero-padded to C channels)
+    // channels of dW_t, db_t as stored: C_out < C when X arrives zero-padded to
+    // C channels, O_out < O when G, T_a, T_b arrive zero-padded to O channels
+    int C_out, O_out;
     // Stride 1 with HO == H, WO == W: the X address of pixel m at a fixed tap is
     // linear in m, and a K step advances each lane's (oh, ow) by lin_dq rows
     // (mod HO) and lin_dr columns, with one carry.

@@ -258,28 +258,29 @@ __global__ __launch_bounds__(kThreads) void qconv_bwd_weight_reduce2d_kernel(con
     }
 }
 
-// Per-term weight transpose O x KH x KW x C -> C x KH x KW x O (LDS-tiled,
-// 32 x 32 tiles, both sides coalesced).  grid: (ceil(C/32), ceil(O/32), 3*KH*KW).
+// Per-term weight transpose O x KH x KW x C -> C x KH x KW x Op (LDS-tiled,
+// 32 x 32 tiles, both sides coalesced), columns O .. Op - 1 zero.
+// grid: (ceil(C/32), ceil(Op/32), 3*KH*KW).
 template <typename T>
 __global__ __launch_bounds__(kThreads) void qconv_weight_transpose_kernel(const T *__restrict__ w0,
                                                                           const T *__restrict__ w1,
                                                                           const T *__restrict__ w2,
-                                                                          T *__restrict__ out, int O, int KHKW,
-                                                                          int C) {
+                                                                          T *__restrict__ out, int O, int Op,
+                                                                          int KHKW, int C) {
     __shared__ T tile[32][33];
     const int t = blockIdx.z / KHKW, tap = blockIdx.z % KHKW;
     const T *w = t == 0 ? w0 : (t == 1 ? w1 : w2);
-    T *dst = out + (size_t)t * O * KHKW * C;
+    T *dst = out + (size_t)t * Op * KHKW * C;
     const int c0 = blockIdx.x * 32, o0 = blockIdx.y * 32;
     const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 32 x 8
     for (int i = ty; i < 32; i += 8) {
         const int o = o0 + i, c = c0 + tx;
-        if (o < O && c < C) tile[i][tx] = w[((size_t)o * KHKW + tap) * C + c];
+        tile[i][tx] = o < O && c < C ? w[((size_t)o * KHKW + tap) * C + c] : T(0);
     }
     __syncthreads();
     for (int i = ty; i < 32; i += 8) {
         const int c = c0 + i, o = o0 + tx;
-        if (o < O && c < C) dst[((size_t)c * KHKW + tap) * O + o] = tile[tx][i];
+        if (o < Op && c < C) dst[((size_t)c * KHKW + tap) * Op + o] = tile[tx][i];
     }
 }
 
@@ -287,10 +288,6 @@ __global__ __launch_bounds__(kThreads) void qconv_weight_transpose_kernel(const 
 
 namespace ql {
 
-// Copy rows of C elements into rows of Cp >= C elements, zero-filling the
-// extra channels (lets 3-channel images use the 16-byte pipelined path).
-// blockIdx.y selects one of the NSEG (src, dst, rows) segments: four for the
-// forward (X and the three weights), one for the weight gradient (X).
 // Elementwise X o X (the operand of the T2 neuron), 16 bytes per thread and
 // step; n: elements, a multiple of the 16-byte vector.
 template <typename T>
@@ -324,36 +321,49 @@ __global__ __launch_bounds__(kThreads) void qconv_relu_mask_kernel(const T *__re
         out[i] = to_f32(y[i]) > 0.0f ? g[i] : from_f32<T>(0.0f);
 }
 
+// Rows of channels copied into rows of whole 16-byte vectors, the extra
+// channels zero (so that channel counts off the vector width take the
+// kernels that move 16 bytes at a time): up to four tensors of one call, one
+// per blockIdx.y (X and the weights of the forward; G, T_a, T_b of the input
+// gradient; X and G, T_a, T_b of the weight gradient).
 struct PadSegments {
     const void *src[4];
     void *dst[4];
-    long long rows[4];
+    uint32_t total[4];  // 16-byte vectors of the padded tensor
+    int c[4];           // channels of a source row
+    FastDiv fd_nv[4];   // 16-byte vectors of a padded row
 };
 
-template <typename T, int NSEG>
-__global__ __launch_bounds__(kThreads) void qconv_pad_channels_kernel(PadSegments sg, int C, int Cp) {
-    static_assert(NSEG >= 1 && NSEG <= 4, "segments");
-    if (blockIdx.y >= NSEG) return;
-    const T *__restrict__ src = static_cast<const T *>(sg.src[blockIdx.y]);
-    T *__restrict__ dst = static_cast<T *>(sg.dst[blockIdx.y]);
-    if (Cp * (int)sizeof(T) == 16) {
-        // one padded row per 16-byte store (the usual case: 3 channels padded to 8 bf16 or 4 fp32)
-        const long long rows = sg.rows[blockIdx.y];
-        for (long long r = (long long)blockIdx.x * blockDim.x + threadIdx.x; r < rows;
-             r += (long long)gridDim.x * blockDim.x) {
-            float v[16 / sizeof(T)];
+// Bound by the copy's bytes: 64 x 56 x 56 rows of 100 bf16 channels to 104 in
+// 15.2 us (5.4 TB/s read and written), of 101 in 25 us.  One 16-byte store per
+// thread and step; the loads are 4 bytes wide where rows start on 4-byte
+// boundaries, else one element.
+template <typename T>
+__global__ __launch_bounds__(kThreads) void qconv_pad_rows_kernel(const PadSegments sg) {
+    constexpr int VEC = Elem<T>::VEC;
+    const int u = blockIdx.y;
+    const T *__restrict__ src = static_cast<const T *>(sg.src[u]);
+    v4u *__restrict__ dst = static_cast<v4u *>(sg.dst[u]);
+    const int C = sg.c[u];
+    const FastDiv fd = sg.fd_nv[u];
+    for (uint32_t i = blockIdx.x * blockDim.x + threadIdx.x; i < sg.total[u]; i += gridDim.x * blockDim.x) {
+        const uint32_t r = fdiv(i, fd);
+        const int c0 = (int)(i - r * fd.d) * VEC;
+        const T *__restrict__ p = src + (size_t)r * C + c0;
+        const int left = C - c0;
+        uint32_t w[4] = {0u, 0u, 0u, 0u};
+        if (sizeof(T) == 4 || (C & 1) == 0) {
+            const uint32_t *__restrict__ pw = reinterpret_cast<const uint32_t *>(p);
+            constexpr int PER = 4 / (int)sizeof(T);  // elements per dword
 #pragma unroll
-            for (int c = 0; c < (int)(16 / sizeof(T)); ++c) v[c] = c < C ? to_f32<T>(src[r * C + c]) : 0.0f;
-            *reinterpret_cast<v4u *>(dst + r * Cp) = vpack<T>(v);
+            for (int k = 0; k < 4; ++k)
+                if (k * PER < left) w[k] = pw[k];
+        } else if constexpr (sizeof(T) == 2) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+                if (k < left) w[k >> 1] |= (uint32_t)p[k] << ((k & 1) * 16);
         }
-        return;
-    }
-    const long long total = sg.rows[blockIdx.y] * Cp;
-    for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < total;
-         i += (long long)gridDim.x * blockDim.x) {
-        const long long r = i / Cp;
-        const int c = (int)(i - r * Cp);
-        dst[i] = c < C ? src[r * C + c] : T(0);
+        dst[i] = v4u{w[0], w[1], w[2], w[3]};
     }
 }
 

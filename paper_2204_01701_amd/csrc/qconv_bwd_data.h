@@ -321,7 +321,7 @@ __global__ __launch_bounds__(kThreads) void qconv_bwd_data_kernel(const BwdDataA
     // neuron only.)
     if constexpr (OM == OM_PAIR || OM == OM_SQIN) {
         if (a.splits == 1 && (OM == OM_SQIN || a.neuron == NEURON_T4I))
-            neuron_dx_epilogue<T, OM, MR, MC>(acc, OM == OM_SQIN ? a.xin : a.gy, a.M, a.C, pcol0, crow0, lane);
+            neuron_dx_epilogue<T, OM, MR, MC>(acc, a.xin, a.M, a.C, pcol0, crow0, lane);
     }
     // T2&4: acc += 2 X o acc2, linear, so every split applies it to its own partial
     if constexpr (OM == OM_QSQ) qsq_dx_epilogue<T, MR, MC>(acc, acc2, a.xin, a.M, a.C, pcol0, crow0, lane);

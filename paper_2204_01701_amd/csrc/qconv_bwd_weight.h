@@ -293,11 +293,11 @@ __device__ __forceinline__ void bwd_weight_body(const BwdWeightArgs &a, char *sm
                 for (int t = t0; t < t0 + PER && t < NTM; ++t) {
                     const char *tile = smem + (t - t0) * MAPB;
                     float *__restrict__ dst =
-                        a.splits == 1 ? a.dw[t] : a.ws_dw + ((size_t)split * 3 + t) * (size_t)a.O * KPO;
+                        a.splits == 1 ? a.dw[t] : a.ws_dw + ((size_t)split * 3 + t) * (size_t)a.O_out * KPO;
                     for (int c = tid; c < BO * CPR; c += NT) {
                         const int row = c / CPR, cc = c % CPR;
                         const int o = ct * BO + row, k = rt * BKP + 4 * cc;
-                        if (o < a.O && k < a.KP)
+                        if (o < a.O_out && k < a.KP)
                             *reinterpret_cast<v4u *>(dst + (size_t)o * a.KP + k) =
                                 lds_read16(tile + row * PITCH + cc * 16);
                     }
@@ -308,13 +308,13 @@ __device__ __forceinline__ void bwd_weight_body(const BwdWeightArgs &a, char *sm
 #pragma unroll
     for (int t = 0; t < NTM; ++t) {
         if (MAPB <= RING && vec_out) break;  // stored above
-        float *__restrict__ dst = a.splits == 1 ? a.dw[t] : a.ws_dw + ((size_t)split * 3 + t) * (size_t)a.O * KPO;
+        float *__restrict__ dst = a.splits == 1 ? a.dw[t] : a.ws_dw + ((size_t)split * 3 + t) * (size_t)a.O_out * KPO;
 #pragma unroll
         for (int mr = 0; mr < MR; ++mr)
 #pragma unroll
             for (int mc = 0; mc < MC; ++mc) {
                 const int o = ocol0 + mc * 32 + lrow;
-                if (o >= a.O) continue;
+                if (o >= a.O_out) continue;
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
                     const int k = krow0 + mr * 32 + 8 * g + 4 * lhi;
@@ -349,11 +349,11 @@ __device__ __forceinline__ void bwd_weight_body(const BwdWeightArgs &a, char *sm
             for (int mc = 0; mc < MC; ++mc) {
                 const float tot = dsum[t][mc] + __shfl_xor(dsum[t][mc], 32);
                 const int o = ocol0 + mc * 32 + lrow;
-                if (lhi == 0 && o < a.O) {
+                if (lhi == 0 && o < a.O_out) {
                     if (a.splits == 1)
                         a.db[t][o] = tot;
                     else
-                        a.ws_db[((size_t)split * 3 + t) * a.O + o] = tot;
+                        a.ws_db[((size_t)split * 3 + t) * a.O_out + o] = tot;
                 }
             }
     }

@@ -402,11 +402,11 @@ __device__ __forceinline__ void bwd_weight16_body(const BwdWeightArgs &a, char *
             for (int t = t0; t < t0 + PER && t < 3; ++t) {
                 const char *tile = smem_all + (t - t0) * MAPB;
                 float *__restrict__ dst =
-                    a.splits == 1 ? a.dw[t] : a.ws_dw + ((size_t)split * 3 + t) * (size_t)a.O * KPO;
+                    a.splits == 1 ? a.dw[t] : a.ws_dw + ((size_t)split * 3 + t) * (size_t)a.O_out * KPO;
                 for (int c = tid; c < BO * CPR; c += NTW) {
                     const int row = c / CPR, cc = c % CPR;
                     const int o = ct * BO + row, k = rt * BKP + 4 * cc;
-                    if (o < a.O && k < a.KP)
+                    if (o < a.O_out && k < a.KP)
                         *reinterpret_cast<v4u *>(dst + (size_t)o * a.KP + k) = lds_read16(tile + row * PITCH + cc * 16);
                 }
             }
@@ -414,9 +414,9 @@ __device__ __forceinline__ void bwd_weight16_body(const BwdWeightArgs &a, char *
     } else if (grp == 0) {
 #pragma unroll
         for (int t = 0; t < 3; ++t) {
-            float *__restrict__ dst = a.splits == 1 ? a.dw[t] : a.ws_dw + ((size_t)split * 3 + t) * (size_t)a.O * KPO;
+            float *__restrict__ dst = a.splits == 1 ? a.dw[t] : a.ws_dw + ((size_t)split * 3 + t) * (size_t)a.O_out * KPO;
             const int o = ct * BO + ocol + lo;
-            if (o >= a.O) continue;
+            if (o >= a.O_out) continue;
 #pragma unroll
             for (int mr = 0; mr < MR; ++mr) {
 #pragma unroll
@@ -442,11 +442,11 @@ __device__ __forceinline__ void bwd_weight16_body(const BwdWeightArgs &a, char *
             float tot = dsum[t] + __shfl_xor(dsum[t], 16);
             tot += __shfl_xor(tot, 32);
             const int o = ct * BO + ocol + lo;
-            if (lg == 0 && o < a.O) {
+            if (lg == 0 && o < a.O_out) {
                 if (a.splits == 1)
                     a.db[t][o] = tot;
                 else
-                    a.ws_db[((size_t)split * 3 + t) * a.O + o] = tot;
+                    a.ws_db[((size_t)split * 3 + t) * a.O_out + o] = tot;
             }
         }
     }

@@ -246,8 +246,8 @@ __device__ __forceinline__ void bwd_weight_narrow_body(const BwdWeightArgs &a, c
     const int KPO = a.KH * a.KW * a.C_out;
 #pragma unroll
     for (int t = 0; t < 3; ++t) {
-        float *__restrict__ dst = a.splits == 1 ? a.dw[t] : a.ws_dw + ((size_t)split * 3 + t) * (size_t)a.O * KPO;
-        if (o < a.O) {
+        float *__restrict__ dst = a.splits == 1 ? a.dw[t] : a.ws_dw + ((size_t)split * 3 + t) * (size_t)a.O_out * KPO;
+        if (o < a.O_out) {
 #pragma unroll
             for (int i = 0; i < NF; ++i) {
                 const int k = 16 * i + 4 * lg;
@@ -266,11 +266,11 @@ __device__ __forceinline__ void bwd_weight_narrow_body(const BwdWeightArgs &a, c
             }
         }
         if constexpr (SUM) {
-            if (lg == 0 && o < a.O) {
+            if (lg == 0 && o < a.O_out) {
                 const float tot = dred[(0 * 3 + t) * 16 + ol] + dred[(1 * 3 + t) * 16 + ol] +
                                   dred[(2 * 3 + t) * 16 + ol] + dred[(3 * 3 + t) * 16 + ol];
                 if (a.splits == 1) a.db[t][o] = tot;
-                else a.ws_db[((size_t)split * 3 + t) * a.O + o] = tot;
+                else a.ws_db[((size_t)split * 3 + t) * a.O_out + o] = tot;
             }
         }
     }

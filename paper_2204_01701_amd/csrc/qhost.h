@@ -39,6 +39,13 @@ constexpr double kSharedRound = 1.25;
 constexpr double kSharedRoundFwd = 1.6;
 constexpr double kBytesPerStep = 3.2e6;
 constexpr double kReduceSteps = 6.0;  // the reduction kernel's launch and ramp
+// An fp32 K step takes about three times a bf16 one (the fp32 MFMA rate), so
+// the partial sums' traffic and the reduction cost a third as many steps.
+// Measured on 18 fp32 shapes with the factor at 1, 1.5, 2, 3, 4, 6: from 1 to 3
+// the forward of 64 -> 64 channels, 256 x 8 x 8 maps, 3 x 3, goes from 64 to 40
+// us, 32 -> 64 at stride 2 from 37 to 26, the input gradient of 128 -> 128,
+// 16 x 14 x 14 maps, 1 x 1, from 32 to 24; above 3 the weight gradients slow down.
+constexpr double kF32Step = 3.0;
 // A workgroup of two pipelines (one per CU) on the two halves of its K range:
 // the cost of a K step of each pipeline, in the units above.  The two
 // pipelines share the workgroup's barriers, which costs them some of the
@@ -71,10 +78,32 @@ struct Geom {
     int terms() const { return om_terms(om()); }
     size_t esize() const { return dt == QL_BF16 ? 2 : 4; }
     int vec() const { return dt == QL_BF16 ? 8 : 4; }
-    // Few input channels that are not a multiple of the 16-byte vector (e.g.
-    // 3-channel images): X and W_t are copied zero-padded to cpad() channels.
-    bool pad_small_c() const { return C % vec() != 0 && C < 2 * vec(); }
+    // Channel counts that are not a multiple of the 16-byte vector: the tensors
+    // that the pipelined kernels read in 16-byte vectors along those channels
+    // are copied zero-padded to whole vectors (cpad() input, opad() output
+    // channels), where the copies stay within the 32-bit element offsets.  The
+    // register-staged kernels that take such rows as they are load one element
+    // at a time.  us per pass (fwd, input gradient, weight gradient), as they
+    // are against padded, the copies included: 50 x 27 x 27 maps, 60 -> 100
+    // channels, 3 x 3, bf16 197, 368, 318 against 40, 66, 54; a dense layer of
+    // 128 rows, 512 -> 10, bf16 10, 12, 30 against 10, 8, 10; 32 x 28 x 28
+    // maps, 51 -> 51 channels, 3 x 3, fp32 89, 113, 104 against 72, 74, 80.
+    // Not for layers of a few million flops and less, where a pass is about the
+    // launches and the copy is one more (a dense layer of 4 rows, 16 -> 73,
+    // called from Python: 38 us for the three passes as it is, 45 padded); few
+    // input channels (below two vectors) are always padded, as one copied vector
+    // per pixel and tap is what the pipelined kernels need there.
     int cpad() const { return (C + vec() - 1) / vec() * vec(); }
+    int opad() const { return (O + vec() - 1) / vec() * vec(); }
+    bool pad_pays() const { return 6.0 * N * HO * WO * KH * KW * (double)C * O >= 2e6; }
+    bool pad_c() const {
+        return C % vec() != 0 && (C < 2 * vec() || pad_pays()) && (long long)N * H * W * cpad() <= kMaxElems &&
+               3LL * O * KH * KW * cpad() <= kMaxElems;
+    }
+    bool pad_o() const {
+        return O % vec() != 0 && pad_pays() && (long long)N * HO * WO * opad() <= kMaxElems &&
+               3LL * C * KH * KW * opad() <= kMaxElems;
+    }
 };
 
 inline ql_status make_geom(const ql_conv_desc *d, Geom &g) {
@@ -123,16 +152,19 @@ inline ql_status linear_geom(const ql_linear_desc *d, Geom &g) {
 // avoids.  At least min_stages K steps per split, at most kMaxSplitBytes of
 // partial sums (bytes_per_split each).
 inline double plan_splits(int tiles, int stages_total, int min_stages, size_t bytes_per_split, int slots, int &splits,
-                          int &sps, size_t max_bytes = kMaxSplitBytes, int pipes = 1,
+                          int &sps, bool f32, size_t max_bytes = kMaxSplitBytes, int pipes = 1,
                           double shared_round = kSharedRound, double step_cost = 1.0) {
+    const double f32_scale = f32 ? kF32Step : 1.0;
     const int cap_bytes = (int)std::max<size_t>(1, max_bytes / std::max<size_t>(bytes_per_split, 1));
     const int s_max = std::max(1, std::min(stages_total / std::max(min_stages, 1), cap_bytes));
     double best = 0.0;
     splits = 1;
-    for (int s = 1; s <= s_max; ++s) {
-        const int per = cdiv(stages_total, s);
-        const int eff = cdiv(stages_total, per);
-        if (eff != s) continue;  // the same partition as a smaller count
+    // Each partition once, by its K steps per split: cdiv(stages_total, per - 1) is
+    // the next count whose splits are shorter (at most 2 sqrt(stages_total) of
+    // them; the callers plan on every call).
+    for (int s = 1, per = stages_total; s <= s_max; s = cdiv(stages_total, per - 1)) {
+        per = cdiv(stages_total, s);
+        const int eff = s;
         const long long wgs = (long long)tiles * eff;
         const long long round = (long long)kNumCUs * std::max(slots, 1);
         const long long full = wgs / round, rest = wgs % round;
@@ -140,11 +172,12 @@ inline double plan_splits(int tiles, int stages_total, int min_stages, size_t by
         if (rest > 0) rounds += rest > kNumCUs ? shared_round : 1.0;
         double t = per * rounds * step_cost;
         if (pipes > 1) t = (double)cdiv(per, pipes) * (double)(full + (rest > 0)) * kPipeRound;
-        if (eff > 1) t += (double)eff * bytes_per_split * 2.0 / kBytesPerStep + kReduceSteps;
+        if (eff > 1) t += ((double)eff * bytes_per_split * 2.0 / kBytesPerStep + kReduceSteps) / f32_scale;
         if (s == 1 || t < best) {
             best = t;
             splits = eff;
         }
+        if (per == 1) break;
     }
     sps = cdiv(stages_total, splits);
     splits = cdiv(stages_total, sps);
@@ -263,7 +296,7 @@ inline FwdPlan plan_fwd(const Geom &g) {
         p.splits = 1;
         return p;
     }
-    p.pad = g.pad_small_c();
+    p.pad = g.pad_c();
     p.Cp = p.pad ? g.cpad() : g.C;
     const int M = g.N * g.HO * g.WO, K = g.KH * g.KW * p.Cp;
     p.veck = p.Cp % g.vec() == 0;
@@ -322,7 +355,7 @@ inline FwdPlan plan_fwd(const Geom &g) {
     int kst = p.stages_total;
     if (p.pm) kst = pm_max_taps(g, p.BCOL, M) * (p.Cp / p.KE);
     plan_splits(p.row_tiles * p.col_tiles, kst, env_override("QLAYER_FWD_MINSTAGES", 4), (size_t)3 * M * g.O * 4,
-                p.slots, p.splits, p.sps, kMaxSplitBytes, 1, kSharedRoundFwd);
+                p.slots, p.splits, p.sps, g.dt == QL_F32, kMaxSplitBytes, 1, kSharedRoundFwd);
     // Where these tiles would split K over workgroups (small outputs: the 4 x 4
     // and 2 x 2 maps of a CIFAR VGG-16), the in-workgroup K split of
     // qconv_fwd_ksplit.h instead: tiles small enough to fill the GPU, no
@@ -388,7 +421,9 @@ struct BwdDataPlan {
     size_t fused_smem;
     int njb;      // ... 32-column blocks of (r, q, c)
     size_t smem;  // ... LDS of the weight fragments
-    size_t wt_bytes, part_bytes, ws_bytes;
+    bool pad;     // G, T_a, T_b (and the transposed weights) zero-padded to Op output channels first
+    int Op;
+    size_t wt_bytes, gpad_bytes, part_bytes, ws_bytes;  // workspace: [weights][G, T_a, T_b padded][split partials]
 };
 
 inline BwdDataPlan plan_bwd_data(const Geom &g) {
@@ -417,8 +452,12 @@ inline BwdDataPlan plan_bwd_data(const Geom &g) {
             return p;
         }
     }
-    const int M = g.N * g.H * g.W, K = g.KH * g.KW * g.O;
-    p.veck = g.O % g.vec() == 0;
+    p.pad = g.pad_o();
+    p.Op = p.pad ? g.opad() : g.O;
+    if (p.pad) p.gpad_bytes = align_up((size_t)g.N * g.HO * g.WO * p.Op * g.esize());
+    const size_t gpads = om_gmaps(g.om()) * p.gpad_bytes;
+    const int M = g.N * g.H * g.W, K = g.KH * g.KW * p.Op;
+    p.veck = p.Op % g.vec() == 0;
     p.s1 = g.SH == 1 && g.SW == 1;
     // Narrow layers: the transposed weight runs of all three terms stay in registers.
     p.cb = cdiv(g.C, 16);
@@ -427,11 +466,11 @@ inline BwdDataPlan plan_bwd_data(const Geom &g) {
         env_override("QLAYER_BWD_DATA_NARROW", 1) != 0) {
         p.narrow = true;
         p.splits = 1;
-        p.wt_bytes = align_up(3 * (size_t)g.O * g.KH * g.KW * g.C * g.esize());
-        p.ws_bytes = p.wt_bytes;
+        p.wt_bytes = align_up(3 * (size_t)p.Op * g.KH * g.KW * g.C * g.esize());
+        p.ws_bytes = p.wt_bytes + gpads;
         return p;
     }
-    p.natw = p.veck && g.dt == QL_BF16 && g.C % 8 == 0;
+    p.natw = p.veck && !p.pad && g.dt == QL_BF16 && g.C % 8 == 0;
     // the wide kernel: bf16, natural weight tiles, stride 1, 16-channel K steps within one tap
     const bool wide_ok = p.natw && p.s1 && g.O % 16 == 0 && g.KH * g.KW <= 32;
     if (p.veck) {
@@ -467,7 +506,7 @@ inline BwdDataPlan plan_bwd_data(const Geom &g) {
     int kst = p.stages_total;
     if (p.pm) kst = bd_pm_max_taps(g, p.BCOL, M) * (g.O / p.KE);
     plan_splits(p.row_tiles * p.col_tiles, kst, env_override("QLAYER_BWD_DATA_MINSTAGES", 4),
-                (size_t)M * g.C * 4, p.slots, p.splits, p.sps);
+                (size_t)M * g.C * 4, p.slots, p.splits, p.sps, g.dt == QL_F32);
     // Block order of the split grid: tile-major (each XCD's blocks share pixel
     // tiles: their rows of G, T_a, T_b once, all of the weights) where G, T_a,
     // T_b are at least the weight bytes (M >= C KH KW), split-major otherwise
@@ -482,9 +521,9 @@ inline BwdDataPlan plan_bwd_data(const Geom &g) {
         p.order = p.splits > 1 ? env_override("QLAYER_BWD_DATA_ORDER", dflt) : 0;
         if (p.order < 0 || p.order > 2) p.order = 0;
     }
-    p.wt_bytes = p.natw ? 0 : align_up(3 * (size_t)g.O * g.KH * g.KW * g.C * g.esize());
+    p.wt_bytes = p.natw ? 0 : align_up(3 * (size_t)p.Op * g.KH * g.KW * g.C * g.esize());
     p.part_bytes = p.splits > 1 ? align_up((size_t)p.splits * M * g.C * sizeof(float)) : 0;
-    p.ws_bytes = p.wt_bytes + p.part_bytes;
+    p.ws_bytes = p.wt_bytes + gpads + p.part_bytes;
     return p;
 }
 
@@ -511,49 +550,66 @@ struct BwdWeightPlan {
     int BKP, BO, KE, slots;
     int row_tiles, col_tiles, splits, sps, stages_total;
     bool veck;
-    bool pad;  // X zero-padded to Cp channels first (pipelined path only)
-    int Cp;
-    size_t xpad_bytes, dw_bytes, db_bytes, ws_bytes;  // workspace: [X padded][dW partials][db partials]
+    bool padc, pado;  // X zero-padded to Cp, G, T_a, T_b to Op channels first (pipelined paths only)
+    int Cp, Op;
+    // workspace: [X padded][G, T_a, T_b padded][dW partials][db partials]
+    size_t xpad_bytes, gpad_bytes, dw_bytes, db_bytes, ws_bytes;
 };
 
 // max_split_bytes: cap on the dW partial sums (the no-allocation entry point
-// plans for its fixed scratch array).
-inline BwdWeightPlan plan_bwd_weight(const Geom &g, size_t max_split_bytes = kMaxSplitBytes) {
+// plans for its fixed scratch array).  may_pad: whether channel counts off the
+// 16-byte vector may take padded copies (else the register-staged kernel).
+inline BwdWeightPlan plan_bwd_weight(const Geom &g, size_t max_split_bytes = kMaxSplitBytes, bool may_pad = true) {
     BwdWeightPlan p{};
     // the narrow kernel: rows k' of at most 144 (after the channel padding)
-    const int cp_small = g.pad_small_c() ? g.cpad() : g.C;
+    const bool f32_pipe = g.ne == NEURON_QUADRA && env_override("QLAYER_BWD_WEIGHT_F32_PIPE", 1) != 0;
+    may_pad = may_pad && (g.dt == QL_BF16 || f32_pipe);
+    p.padc = may_pad && g.pad_c();
+    p.pado = may_pad && g.pad_o();
+    p.Cp = p.padc ? g.cpad() : g.C;
+    p.Op = p.pado ? g.opad() : g.O;
+    p.veck = p.Cp % g.vec() == 0 && p.Op % g.vec() == 0;
+    if (!p.veck) {  // (one of the two cannot be padded: neither)
+        p.padc = p.pado = false;
+        p.Cp = g.C;
+        p.Op = g.O;
+    }
     // (wider layers, up to 64 channels, in 16-channel slices, one per workgroup row of the
     // grid: by default in fp32, where the 16 -> 32-channel stride-2 CIFAR ResNet layer
     // measured 37 against 66 us per call; in bf16 it and the VGG-16 stem were no faster)
     const int narrow_max_o = env_override("QLAYER_BWD_WEIGHT_NARROW_MAXO", g.dt == QL_F32 ? 64 : 16);
-    const bool narrow_shape = g.ne == NEURON_QUADRA && (g.O <= 16 || (g.O % 16 == 0 && g.O <= narrow_max_o)) &&
-                              g.O % g.vec() == 0 && cp_small % g.vec() == 0 &&
-                              cdiv(g.KH * g.KW * cp_small, 16) <= 9 &&
+    const bool narrow_shape = g.ne == NEURON_QUADRA && (p.Op <= 16 || (p.Op % 16 == 0 && p.Op <= narrow_max_o)) &&
+                              p.veck && cdiv(g.KH * g.KW * p.Cp, 16) <= 9 &&
                               env_override("QLAYER_BWD_WEIGHT_NARROW", 1) != 0;
-    // (fp32 pads only for the narrow kernel)
-    p.pad = g.pad_small_c() && g.O % g.vec() == 0 && (g.dt == QL_BF16 || narrow_shape);
-    p.Cp = p.pad ? g.cpad() : g.C;
     const int M = g.N * g.HO * g.WO, KP = g.KH * g.KW * p.Cp, KPO = g.KH * g.KW * g.C;
-    p.veck = p.Cp % g.vec() == 0 && g.O % g.vec() == 0;
     // pipelined kernels: bf16 every neuron type; fp32 the proposed neuron (the 16 x 16 kernel's fp32 form)
-    p.pipe = p.veck && (g.dt == QL_BF16 ||
-                        (g.ne == NEURON_QUADRA && env_override("QLAYER_BWD_WEIGHT_F32_PIPE", 1) != 0));
-    if (p.pad) p.xpad_bytes = align_up((size_t)g.N * g.H * g.W * p.Cp * g.esize());
+    p.pipe = p.veck && (g.dt == QL_BF16 || f32_pipe);
+    if (p.padc) p.xpad_bytes = align_up((size_t)g.N * g.H * g.W * p.Cp * g.esize());
+    if (p.pado) p.gpad_bytes = align_up((size_t)M * p.Op * g.esize());
+    const size_t pads = p.xpad_bytes + om_gmaps(g.om()) * p.gpad_bytes;
     p.KE = 64 / (int)g.esize();
     p.stages_total = cdiv(M, p.KE);
-    // (the generic kernel's K steps are latency-bound: splits down to one step
-    // each, e.g. the 64 -> 10 head of a CIFAR ResNet at batch 256, 53 -> 17 us)
-    const int min_stages = env_override("QLAYER_BWD_WEIGHT_MINSTAGES", p.pipe ? 16 : 1);
+    // At least two K steps per split (small outputs with few pixels leave most
+    // CUs idle otherwise: 64 -> 64 channels, 8 x 8 x 8 maps, 3 x 3, in fp32 35 us
+    // at a floor of 16, 18 at 4, 16 at 2; no change on the VGG-16 layers).  The
+    // generic kernel's steps are latency-bound: down to one step each (the
+    // 64 -> 10 head of a CIFAR ResNet at batch 256, 53 -> 17 us).
+    const int min_stages = env_override("QLAYER_BWD_WEIGHT_MINSTAGES", p.pipe ? 2 : 1);
     const size_t bytes_per_split = (size_t)3 * g.O * KPO * 4;
     // Narrow layers: the whole gradient of a 16-channel slice is one tile; about
-    // two workgroups per CU in all, at least four K steps per wave, the partial
-    // sums within max_split_bytes.
+    // one workgroup per CU in all down to one K step per wave, two per CU from
+    // four steps per wave, the partial sums within max_split_bytes.  (16 -> 16
+    // channels, 3 x 3, us at four steps per wave everywhere and now: 64 x 16 x 16
+    // maps fp32 22.6 -> 17.8, bf16 18.6 -> 15.1; 16 x 8 x 8 maps fp32 22.4 -> 14.)
     p.nf = cdiv(KP, 16);
-    if (narrow_shape && p.Cp == cp_small) {
+    if (narrow_shape) {
         p.narrow = true;
-        p.nob = cdiv(g.O, 16);
+        p.nob = cdiv(p.Op, 16);
         p.stages_total = cdiv(M, g.dt == QL_BF16 ? 32 : 16);
-        int splits = std::min(std::max(1, 2 * kNumCUs / p.nob), std::max(1, cdiv(p.stages_total, 16)));
+        // (one workgroup up to two steps per wave: a reduction would cost what it saves)
+        int splits = p.stages_total <= 8 ? 1 : std::max(cdiv(p.stages_total, 16),
+                                                        std::min(cdiv(kNumCUs, p.nob), cdiv(p.stages_total, 4)));
+        splits = std::min(std::max(1, 2 * kNumCUs / p.nob), splits);
         splits = env_override("QLAYER_BWD_WEIGHT_NARROW_SPLITS", splits);
         splits = std::max(1, std::min(splits, (int)std::max<size_t>(1, max_split_bytes / bytes_per_split)));
         p.sps = cdiv(p.stages_total, splits);
@@ -562,7 +618,7 @@ inline BwdWeightPlan plan_bwd_weight(const Geom &g, size_t max_split_bytes = kMa
             p.dw_bytes = align_up((size_t)p.splits * 3 * g.O * KPO * sizeof(float));
             p.db_bytes = align_up((size_t)p.splits * 3 * g.O * sizeof(float));
         }
-        p.ws_bytes = p.xpad_bytes + p.dw_bytes + p.db_bytes;
+        p.ws_bytes = pads + p.dw_bytes + p.db_bytes;
         return p;
     }
     auto fill = [&](int cfg) {
@@ -573,7 +629,7 @@ inline BwdWeightPlan plan_bwd_weight(const Geom &g, size_t max_split_bytes = kMa
         p.row_tiles = cdiv(KP, p.BKP);
         p.col_tiles = cdiv(g.O, p.BO);
         return plan_splits(p.row_tiles * p.col_tiles, p.stages_total, min_stages, bytes_per_split, p.slots, p.splits,
-                           p.sps, max_split_bytes, kBwPipes[cfg], kSharedRound, cfg == 5 ? kFatStep : 1.0);
+                           p.sps, g.dt == QL_F32, max_split_bytes, kBwPipes[cfg], kSharedRound, cfg == 5 ? kFatStep : 1.0);
     };
     if (p.pipe && g.ne == NEURON_QUADRA) {
         // the 16 x 16 x 32 kernel: four waves on a 64-channel tile, two such pipelines per
@@ -595,7 +651,7 @@ inline BwdWeightPlan plan_bwd_weight(const Geom &g, size_t max_split_bytes = kMa
         p.dw_bytes = align_up((size_t)p.splits * 3 * g.O * KPO * sizeof(float));
         p.db_bytes = align_up((size_t)p.splits * 3 * g.O * sizeof(float));
     }
-    p.ws_bytes = p.xpad_bytes + p.dw_bytes + p.db_bytes;
+    p.ws_bytes = pads + p.dw_bytes + p.db_bytes;
     return p;
 }
 
@@ -607,6 +663,26 @@ inline ql_status hip_status() {
 inline int grid_1d(long long total) {
     long long b = (total + kThreads - 1) / kThreads;
     return (int)std::max(1LL, std::min(b, 8LL * kNumCUs));
+}
+
+// One tensor of a zero-padding pass (qconv_pad_rows_kernel): `rows` rows of c
+// channels of T into dst, padded to whole 16-byte vectors.
+template <typename T>
+inline void pad_segment(PadSegments &sg, int &n, const void *src, void *dst, long long rows, int c) {
+    const int nv = cdiv(c, Elem<T>::VEC);
+    sg.src[n] = src;
+    sg.dst[n] = dst;
+    sg.total[n] = (uint32_t)(rows * nv);
+    sg.c[n] = c;
+    sg.fd_nv[n] = make_fastdiv(nv);
+    ++n;
+}
+template <typename T>
+inline ql_status launch_pad(const PadSegments &sg, int n, hipStream_t st) {
+    uint32_t most = 0;
+    for (int i = 0; i < n; ++i) most = std::max(most, sg.total[i]);
+    hipLaunchKernelGGL((qconv_pad_rows_kernel<T>), dim3(grid_1d(most), n), dim3(kThreads), 0, st, sg);
+    return hip_status();
 }
 
 // ---------------------------------------------------------------------------

@@ -59,35 +59,49 @@ ql_status launch_bwd_data(const Geom &g, const BwdDataPlan &p, const void *gy, c
         a.wt[0] = wa; a.wt[1] = wb; a.wt[2] = wc;
     } else {
         T *wt = static_cast<T *>(ws);
-        hipLaunchKernelGGL((qconv_weight_transpose_kernel<T>), dim3(cdiv(g.C, 32), cdiv(g.O, 32), g.terms() * khkw),
+        hipLaunchKernelGGL((qconv_weight_transpose_kernel<T>), dim3(cdiv(g.C, 32), cdiv(p.Op, 32), g.terms() * khkw),
                            dim3(kThreads), 0, st, static_cast<const T *>(wa), static_cast<const T *>(wb),
-                           static_cast<const T *>(wc), wt, g.O, khkw, g.C);
+                           static_cast<const T *>(wc), wt, g.O, p.Op, khkw, g.C);
         s = hip_status();
         if (s != QL_OK) return s;
-        const size_t wsz = (size_t)g.O * khkw * g.C;
+        const size_t wsz = (size_t)p.Op * khkw * g.C;
         a.wt[0] = wt; a.wt[1] = wt + wsz; a.wt[2] = wt + 2 * wsz;
     }
-    a.gy = gy; a.ta = ta; a.tb = tb;
+    const void *maps[3] = {gy, ta, tb};
+    const int ngm = om_gmaps(g.om());
+    char *gpad = static_cast<char *>(ws) + p.wt_bytes;
+    if (p.pad) {
+        // Zero-pad the output-side maps the type's operands need to Op channels in the workspace.
+        PadSegments sg{};
+        int n = 0;
+        for (int u = 0; u < ngm; ++u) {
+            pad_segment<T>(sg, n, maps[u], gpad + u * p.gpad_bytes, (long long)g.N * g.HO * g.WO, g.O);
+            maps[u] = gpad + u * p.gpad_bytes;
+        }
+        s = launch_pad<T>(sg, n, st);
+        if (s != QL_OK) return s;
+    }
+    a.gy = maps[0]; a.ta = maps[1]; a.tb = maps[2];
     a.dx = dx;
-    a.ws = reinterpret_cast<float *>(static_cast<char *>(ws) + p.wt_bytes);
+    a.ws = reinterpret_cast<float *>(gpad + ngm * p.gpad_bytes);
     a.zero = zero_page();
     if (!a.zero) return QL_EHIP;
-    a.N = g.N; a.H = g.H; a.W = g.W; a.C = g.C; a.O = g.O; a.KH = g.KH; a.KW = g.KW;
+    a.N = g.N; a.H = g.H; a.W = g.W; a.C = g.C; a.O = p.Op; a.KH = g.KH; a.KW = g.KW;
     a.SH = g.SH; a.SW = g.SW; a.PH = g.PH; a.PW = g.PW; a.HO = g.HO; a.WO = g.WO;
     a.M = g.N * g.H * g.W;
-    a.K = khkw * g.O;
+    a.K = khkw * p.Op;
     a.row_tiles = p.row_tiles; a.col_tiles = p.col_tiles;
     a.splits = p.splits; a.stages_per_split = p.sps; a.stages_total = p.stages_total;
     a.fd_hw = make_fastdiv(g.H * g.W);
     a.fd_w = make_fastdiv(g.W);
-    a.fd_o = make_fastdiv(g.O);
+    a.fd_o = make_fastdiv(p.Op);
     a.fd_kw = make_fastdiv(g.KW);
     a.fd_sh = make_fastdiv(g.SH);
     a.fd_sw = make_fastdiv(g.SW);
     a.neuron = g.ne;
-    a.xin = xin;
+    a.xin = g.ne == NEURON_T4I ? gy : xin;
     a.pm = p.pm ? 1 : 0;
-    a.ops = p.KE > 0 ? std::max(1, g.O / p.KE) : 1;  // (the narrow and few-channel plans set no K step)
+    a.ops = p.KE > 0 ? std::max(1, p.Op / p.KE) : 1;  // (the narrow and few-channel plans set no K step)
     a.fd_n = make_fastdiv(g.N);
     a.fd_ops = make_fastdiv(a.ops);
     a.order = p.order;

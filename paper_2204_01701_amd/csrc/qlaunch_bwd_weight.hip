@@ -43,31 +43,40 @@ ql_status launch_bwd_weight(const Geom &g, const BwdWeightPlan &p, const void *x
     BwdWeightArgs a{};
     a.x = x; a.gy = gy; a.ta = ta; a.tb = tb;
     char *wsb = static_cast<char *>(ws);
-    if (p.pad) {
-        // Zero-pad X to Cp channels in the workspace; dW_t is stored with the true C.
+    const int ngm = om_gmaps(g.om());
+    char *gpad = wsb + p.xpad_bytes, *parts = gpad + ngm * p.gpad_bytes;
+    if (p.padc || p.pado) {
+        // Zero-pad X to Cp and the output-side maps the type's operands need to Op
+        // channels in the workspace; dW_t and db_t are stored with the true C and O.
         PadSegments sg{};
-        sg.src[0] = x;
-        sg.dst[0] = wsb;
-        sg.rows[0] = (long long)g.N * g.H * g.W;
-        const long long pad_items = sg.rows[0] * (p.Cp * (int)sizeof(T) == 16 ? 1 : p.Cp);
-        hipLaunchKernelGGL((qconv_pad_channels_kernel<T, 1>), dim3(grid_1d(pad_items), 1), dim3(kThreads), 0, st,
-                           sg, g.C, p.Cp);
-        const ql_status s0 = hip_status();
+        int n = 0;
+        if (p.padc) {
+            pad_segment<T>(sg, n, x, wsb, (long long)g.N * g.H * g.W, g.C);
+            a.x = wsb;
+        }
+        if (p.pado) {
+            const void **maps[3] = {&a.gy, &a.ta, &a.tb};
+            for (int u = 0; u < ngm; ++u) {
+                pad_segment<T>(sg, n, *maps[u], gpad + u * p.gpad_bytes, (long long)g.N * g.HO * g.WO, g.O);
+                *maps[u] = gpad + u * p.gpad_bytes;
+            }
+        }
+        const ql_status s0 = launch_pad<T>(sg, n, st);
         if (s0 != QL_OK) return s0;
-        a.x = wsb;
     }
     const int C = p.Cp;  // channels the GEMM sees
     a.dw[0] = dwa; a.dw[1] = dwb; a.dw[2] = dwc;
     a.db[0] = dba; a.db[1] = dbb; a.db[2] = dbc;
-    a.ws_dw = reinterpret_cast<float *>(wsb + p.xpad_bytes);
-    a.ws_db = reinterpret_cast<float *>(wsb + p.xpad_bytes + p.dw_bytes);
+    a.ws_dw = reinterpret_cast<float *>(parts);
+    a.ws_db = reinterpret_cast<float *>(parts + p.dw_bytes);
     a.zero = zero_page();
     if (!a.zero) return QL_EHIP;
-    a.N = g.N; a.H = g.H; a.W = g.W; a.C = C; a.O = g.O; a.KH = g.KH; a.KW = g.KW;
+    a.N = g.N; a.H = g.H; a.W = g.W; a.C = C; a.O = p.Op; a.KH = g.KH; a.KW = g.KW;
     a.SH = g.SH; a.SW = g.SW; a.PH = g.PH; a.PW = g.PW; a.HO = g.HO; a.WO = g.WO;
     a.M = g.N * g.HO * g.WO;
     a.KP = g.KH * g.KW * C;
     a.C_out = g.C;
+    a.O_out = g.O;
     a.row_tiles = p.row_tiles; a.col_tiles = p.col_tiles;
     a.splits = p.splits; a.stages_per_split = p.sps; a.stages_total = p.stages_total;
     a.want_db = dba != nullptr;

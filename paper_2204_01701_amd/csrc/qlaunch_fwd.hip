@@ -53,20 +53,12 @@ ql_status launch_fwd(const Geom &g, const FwdPlan &p, const void *x, const void 
     if (p.pad) {
         // Zero-pad X and the three weights to Cp channels in the workspace.
         PadSegments sg{};
-        const void *srcs[4] = {x, wa, wb, wc};
-        const long long wrows = (long long)g.O * g.KH * g.KW;
-        const long long rows[4] = {(long long)g.N * g.H * g.W, wrows, g.terms() >= 2 ? wrows : 0,
-                                   g.terms() >= 3 ? wrows : 0};  // (terms the type lacks: nothing to pad)
-        for (int i = 0; i < 4; ++i) {
-            sg.src[i] = srcs[i];
-            sg.dst[i] = wsb + (i == 0 ? 0 : p.xpad_bytes + (size_t)(i - 1) * p.wpad_bytes);
-            sg.rows[i] = rows[i];
-        }
-        // (one thread per row when a padded row is one 16-byte vector, else per element)
-        const long long pad_items = rows[0] * (p.Cp * (int)sizeof(T) == 16 ? 1 : p.Cp);
-        hipLaunchKernelGGL((qconv_pad_channels_kernel<T, 4>), dim3(grid_1d(pad_items), 4), dim3(kThreads), 0, st,
-                           sg, g.C, p.Cp);
-        const ql_status s0 = hip_status();
+        int n = 0;
+        const void *ws3[3] = {wa, wb, wc};
+        pad_segment<T>(sg, n, x, wsb, (long long)g.N * g.H * g.W, g.C);
+        for (int t = 0; t < g.terms(); ++t)  // (terms the type lacks: nothing to pad)
+            pad_segment<T>(sg, n, ws3[t], wsb + p.xpad_bytes + t * p.wpad_bytes, (long long)g.O * g.KH * g.KW, g.C);
+        const ql_status s0 = launch_pad<T>(sg, n, st);
         if (s0 != QL_OK) return s0;
         a.x = sg.dst[0];
         a.w[0] = sg.dst[1]; a.w[1] = sg.dst[2]; a.w[2] = sg.dst[3];

@@ -221,9 +221,16 @@ ql_status bwd_weight_common(const Geom &g, const void *x, const void *gy, const 
         // the regular entry point), else fewer splits: dW and db partials of
         // 3 O (KP + 1) floats per split, two 256-byte alignments
         if (p.ws_bytes > kScratchBytes) {
-            const size_t room = kScratchBytes - std::min(kScratchBytes, p.xpad_bytes + 2 * kAlign);
+            const size_t pads = p.xpad_bytes + om_gmaps(g.om()) * p.gpad_bytes;
             const size_t kpo = (size_t)g.KH * g.KW * g.C;
+            const size_t room = kScratchBytes - std::min(kScratchBytes, pads + 2 * kAlign);
             p = plan_bwd_weight(g, room / (kpo + 1) * kpo);
+            // Padded copies that do not fit: the register-staged kernel, which needs none.
+            // (Not on the few-channel layers, C below two vectors and O whole vectors:
+            // they are refused here, as the header says.)
+            const bool few = g.C < 2 * g.vec() && !p.pado && (g.dt == QL_BF16 || p.narrow);
+            if (p.ws_bytes > kScratchBytes && (p.padc || p.pado) && !few)
+                p = plan_bwd_weight(g, (kScratchBytes - 2 * kAlign) / (kpo + 1) * kpo, false);
         }
         if (p.ws_bytes > kScratchBytes) return QL_EWORKSPACE;
         ws = scratch_ptr();
