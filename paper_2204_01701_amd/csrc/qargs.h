@@ -80,6 +80,9 @@ struct FwdArgs {
     FastDiv fd_howo, fd_wo, fd_c, fd_kw, fd_n, fd_cps;
 };
 
+// Stride offsets (phases) the input gradient's kernels tell apart at most.
+constexpr int kMaxPhases = 64;
+
 // Input gradient: rows = input channels, columns = input pixels,
 // K = (t, r, q, o) with the per-term weights pre-transposed to C x KH x KW x O.
 struct BwdDataArgs {
@@ -101,6 +104,10 @@ struct BwdDataArgs {
     // in the map for some position of the tile, ops = O / KE steps each.
     int pm, ops;
     int order;  // block order of the split-K grid (tile_coord)
+    // Narrow kernel at stride > 1: the waves are shared out in rounds of `units`,
+    // one per tap of each phase (BwdPhase; at least one); unit_end: their prefix sums.
+    int units;
+    uint16_t unit_end[kMaxPhases];
     FastDiv fd_hw, fd_w, fd_o, fd_kw, fd_sh, fd_sw, fd_n, fd_ops;
 };
 

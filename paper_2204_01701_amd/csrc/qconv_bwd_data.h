@@ -16,8 +16,14 @@
 // Per K step the three weight tiles and the G, T_a and T_b tiles are copied
 // into the LDS ring (qpipe.h).  The products G o T_b and G o T_a are formed
 // in fp32 on the MFMA operand fragments right after they are read from LDS,
-// so they never exist in memory.  Taps that fall between output pixels
-// (stride > 1) or outside the output map load zeros.
+// so they never exist in memory.  Taps that fall outside the output map load
+// zeros.  At stride > 1 a pixel tile holds pixels of one phase (BwdPhase),
+// whose taps alone are its K range: without the phases the tiles multiplied
+// the taps that fall between output pixels as zeros, 27 of 36 tap products of a 3 x 3
+// filter at stride 2 (32 -> 64 channels, 256 x 16 x 16 maps, fp32: 142 us per
+// call, 69 us with them).  Consecutive column tiles cycle through the phases, so
+// the blocks of one XCD hold long and short K ranges alike and the tiles of
+// the same output pixels share its L2.
 #pragma once
 
 #include "qargs.h"
@@ -34,7 +40,7 @@ namespace ql {
 template <typename T, int BR, int BCOL, int WGR, int WGC, int NS, bool S1, bool NATW, bool CA, int OM = OM_QUADRA>
 __global__ __launch_bounds__(kThreads) void qconv_bwd_data_kernel(const BwdDataArgs a) {
     static_assert(!NATW || sizeof(T) == 2, "natural weight tiles need 16-bit elements");
-    static_assert(!CA || (S1 && NATW), "channel-aligned steps are implemented for stride 1, natural weight tiles");
+    static_assert(!CA || NATW, "channel-aligned steps are implemented for natural weight tiles");
     constexpr int VEC = Elem<T>::VEC;
     constexpr int KE = 64 / (int)sizeof(T);
     constexpr int ROWS = 3 * BR + 3 * BCOL;
@@ -53,13 +59,47 @@ __global__ __launch_bounds__(kThreads) void qconv_bwd_data_kernel(const BwdDataA
     const int tid = threadIdx.x, lane = tid & 63, wave = wave_id();
     const int wr = wave / WGC, wc = wave % WGC;
     const TileCoord tc = tile_coord(xcd_remap(blockIdx.x, gridDim.x), a.order, a.row_tiles, a.col_tiles, a.splits);
-    const int split = tc.split, rt = tc.rt, ct = tc.ct;
+    const int split = tc.split, rt = tc.rt;
+    // Stride 1: the whole map is one phase (GEMM column m = NHWC row m, or
+    // position-major); else this tile's phase and its column tile in it.
+    const int nph = S1 ? 1 : a.SH * a.SW;
+    const int ct = S1 ? tc.ct : tc.ct / nph;
+    const BwdPhase ph(S1 ? 0 : tc.ct - ct * nph, a.H, a.W, a.KH, a.KW, S1 ? 1 : a.SH, S1 ? 1 : a.SW, a.PH, a.PW);
+    const int mp = S1 ? a.M : a.N * ph.hp * ph.wp;  // GEMM columns of the phase
+    if (!S1 && ct * BCOL >= mp) return;
+    const int KP = S1 ? a.K : ph.rp * ph.qp * a.O;
+    // ri = tap / qp of a tap of the phase (tap < 2^32 / qp: exact)
+    const uint32_t qinv = S1 || ph.qp <= 1 ? 0u : 0xffffffffu / (uint32_t)ph.qp + 1u;
+    auto tap_row = [&](int tap) -> int {
+        if constexpr (S1) return (int)fdiv((uint32_t)tap, a.fd_kw);
+        else return ph.qp <= 1 ? tap : (int)__umulhi((uint32_t)tap, qinv);
+    };
+    const int QP = S1 ? a.KW : ph.qp;
+    // the filter tap of the phase's tap (ri, qi)
+    auto wtap = [&](int ri, int qi) -> int {
+        if constexpr (S1) return ri * a.KW + qi;
+        else return (ph.r0 + a.SH * ri) * a.KW + ph.q0 + a.SW * qi;
+    };
+    // image and position of GEMM column m
+    auto pixel = [&](int m, int &n, int &hh, int &ww) {
+        if constexpr (S1) {
+            n = (int)fdiv((uint32_t)m, a.fd_hw);
+            const int rem = m - n * a.H * a.W;
+            hh = (int)fdiv((uint32_t)rem, a.fd_w);
+            ww = rem - hh * a.W;
+        } else {
+            const uint32_t hw = ph.hp * ph.wp, rem = (uint32_t)m % hw;
+            n = (uint32_t)m / hw;
+            hh = rem / (uint32_t)ph.wp;
+            ww = rem - hh * ph.wp;
+        }
+    };
     // Position-major order (CA): the taps whose output pixel lies in the map
     // for some position of this pixel tile (a wave-uniform mask); the tile's K
     // range is those taps only.
     uint32_t tmask = 0;
-    int kst = a.stages_total;
-    if (CA && a.pm) {
+    int kst = S1 ? a.stages_total : (KP + KE - 1) / KE;
+    if (S1 && CA && a.pm) {
         const int m_hi = min(ct * BCOL + BCOL, a.M) - 1;
         for (int pos = (int)fdiv((uint32_t)(ct * BCOL), a.fd_n); pos <= (int)fdiv((uint32_t)m_hi, a.fd_n); ++pos) {
             const int h = (int)fdiv((uint32_t)pos, a.fd_w);
@@ -75,6 +115,11 @@ __global__ __launch_bounds__(kThreads) void qconv_bwd_data_kernel(const BwdDataA
     const int nst = max(0, min(a.stages_per_split, kst - s_begin));
     // NHWC row of GEMM column m
     auto prow = [&](int m) -> int {
+        if constexpr (!S1) {
+            int n, hh, ww;
+            pixel(m, n, hh, ww);
+            return (n * a.H + ph.h0 + a.SH * hh) * a.W + ph.w0 + a.SW * ww;
+        }
         if (!CA || !a.pm) return m;
         const int pos = (int)fdiv((uint32_t)m, a.fd_n);
         return (m - pos * a.N) * a.H * a.W + pos;
@@ -105,14 +150,12 @@ __global__ __launch_bounds__(kThreads) void qconv_bwd_data_kernel(const BwdDataA
 #pragma unroll
     for (int j = 0; j < NIP; ++j) {
         const int m = ct * BCOL + 16 * (4 * j + wave) + (lane >> 2);
-        if (m < a.M) {
-            const int n = (int)fdiv((uint32_t)m, a.fd_hw);
-            const int rem = m - n * a.H * a.W;
-            const int h = (int)fdiv((uint32_t)rem, a.fd_w);
-            const int w = rem - h * a.W;
+        if (m < mp) {
+            int n, h, w;
+            pixel(m, n, h, w);
             goff[j] = n * a.HO * a.WO * a.O;
-            hh[j] = h + a.PH;
-            ww[j] = w + a.PW;
+            hh[j] = h + ph.oh0;
+            ww[j] = w + ph.ow0;
         } else {
             goff[j] = -1;
             hh[j] = 0;
@@ -120,7 +163,7 @@ __global__ __launch_bounds__(kThreads) void qconv_bwd_data_kernel(const BwdDataA
         }
     }
 
-    // Channel-aligned K steps (CA: O a multiple of KE, stride 1): a K step lies
+    // Channel-aligned K steps (CA: O a multiple of KE): a K step lies
     // within one tap, so tap and output-channel offset are wave-uniform and
     // each DMA address is a per-lane base plus a scalar offset.  Weight
     // columns past C load the zero page (a fixed per-lane predicate: on layers
@@ -141,24 +184,23 @@ __global__ __launch_bounds__(kThreads) void qconv_bwd_data_kernel(const BwdDataA
         }
 #pragma unroll
         for (int j = 0; j < NIP; ++j) {
-            const int m = min(ct * BCOL + 16 * (4 * j + wave) + (lane >> 2), a.M - 1);
-            int n, rem;
-            if (a.pm) {
-                rem = (int)fdiv((uint32_t)m, a.fd_n);
+            const int m = min(ct * BCOL + 16 * (4 * j + wave) + (lane >> 2), mp - 1);
+            int n, h, w;
+            if (S1 && a.pm) {
+                const int rem = (int)fdiv((uint32_t)m, a.fd_n);
                 n = m - rem * a.N;
+                h = (int)fdiv((uint32_t)rem, a.fd_w);
+                w = rem - h * a.W;
             } else {
-                n = (int)fdiv((uint32_t)m, a.fd_hw);
-                rem = m - n * a.H * a.W;
+                pixel(m, n, h, w);
             }
-            const int h = (int)fdiv((uint32_t)rem, a.fd_w);
-            const int w = rem - h * a.W;
-            const int i0 = h + a.PH, j0 = w + a.PW;  // output pixel of tap (0, 0)
+            const int i0 = h + ph.oh0, j0 = w + ph.ow0;  // output pixel of the phase's tap (0, 0)
             go[j] = ((long long)n * a.HO * a.WO + (long long)i0 * a.WO + j0) * a.O + kcol * VEC;
             uint32_t msk = 0;
-            for (int r = 0; r < a.KH; ++r)
-                for (int q = 0; q < a.KW; ++q)
+            for (int r = 0; r < ph.rp; ++r)
+                for (int q = 0; q < ph.qp; ++q)
                     if ((unsigned)(i0 - r) < (unsigned)a.HO && (unsigned)(j0 - q) < (unsigned)a.WO)
-                        msk |= 1u << (r * a.KW + q);
+                        msk |= 1u << (r * QP + q);
             gmask[j] = msk;
         }
     }
@@ -168,7 +210,7 @@ __global__ __launch_bounds__(kThreads) void qconv_bwd_data_kernel(const BwdDataA
         DmaPart part(lo, hi);
         if constexpr (CA) {
             int tap, o0;
-            if (a.pm) {
+            if (S1 && a.pm) {
                 // step s: output channels ((s mod ops) KE ..) of the tile's (s / ops)-th tap
                 const int sc = max(0, min(s, kst - 1));  // (dead steps past the range re-read a valid one)
                 const int ti = (int)fdiv((uint32_t)sc, a.fd_ops);
@@ -177,13 +219,13 @@ __global__ __launch_bounds__(kThreads) void qconv_bwd_data_kernel(const BwdDataA
                 for (int i = 0; i < ti; ++i) rest &= rest - 1;
                 tap = rest ? __builtin_ctz(rest) : 0;
             } else {
-                const int k0 = min(s, a.stages_total - 1) * KE;
+                const int k0 = min(s, kst - 1) * KE;
                 tap = (int)fdiv((uint32_t)k0, a.fd_o);
                 o0 = k0 - tap * a.O;
             }
-            const int r = (int)fdiv((uint32_t)tap, a.fd_kw);
-            const int q = tap - r * a.KW;
-            const long long sw = ((long long)o0 * khkw + tap) * a.C;
+            const int r = tap_row(tap);
+            const int q = tap - r * QP;
+            const long long sw = ((long long)o0 * khkw + wtap(r, q)) * a.C;
 #pragma unroll
             for (int i = 0; i < NIW; ++i)
                 if (part.take()) dma16(dma_src(wc_ok, wrow[i] + sw, a.zero), base + i * 4096);
@@ -199,45 +241,40 @@ __global__ __launch_bounds__(kThreads) void qconv_bwd_data_kernel(const BwdDataA
             return;
         }
         const int k = s * KE + kcol * VEC;
-        const bool kin = live && k < a.K;
+        const bool kin = live && k < KP;
         const int tap = (int)fdiv((uint32_t)k, a.fd_o);
         const int o = k - tap * a.O;
-        const int r = (int)fdiv((uint32_t)tap, a.fd_kw);
-        const int q = tap - r * a.KW;
+        const int r = tap_row(tap);
+        const int q = tap - r * QP;
         if constexpr (NATW) {
 #pragma unroll
             for (int i = 0; i < NIW; ++i) {
                 const int t = (i * 4096) / WT;
                 const int row = ((i * 4096) % WT + wave * 1024) / (SW * 16) + lane / SW;
                 const int kr = s * KE + row;
-                const int tapr = (int)fdiv((uint32_t)kr, a.fd_o);
+                int tapr = (int)fdiv((uint32_t)kr, a.fd_o);
                 const int orow = kr - tapr * a.O;
-                const bool ok = live && wc_ok && kr < a.K;
+                const bool ok = live && wc_ok && kr < KP;
+                if constexpr (!S1) {
+                    const int ri = tap_row(tapr);
+                    tapr = wtap(ri, tapr - ri * QP);
+                }
                 if (part.take())
                     dma16(dma_src(ok, wt[t] + ((size_t)(orow * khkw + tapr) * a.C + wc0), a.zero), base + i * 4096);
             }
         } else {
+            const int kw = S1 ? k : wtap(r, q) * a.O + o;  // k in the whole filter
 #pragma unroll
             for (int i = 0; i < NIW; ++i) {
                 const bool ok = kin && woff[i] >= 0;
-                if (part.take()) dma16(dma_src(ok, wt[(64 * i) / BR] + woff[i] + k, a.zero), base + i * 4096);
+                if (part.take()) dma16(dma_src(ok, wt[(64 * i) / BR] + woff[i] + kw, a.zero), base + i * 4096);
             }
         }
 #pragma unroll
         for (int j = 0; j < NIP; ++j) {
             const int hi = hh[j] - r, wi = ww[j] - q;
-            bool ok;
-            int p;
-            if constexpr (S1) {
-                ok = (unsigned)hi < (unsigned)a.HO && (unsigned)wi < (unsigned)a.WO;
-                p = goff[j] + (hi * a.WO + wi) * a.O + o;
-            } else {
-                const int i2 = (int)fdiv((uint32_t)max(hi, 0), a.fd_sh);
-                const int j2 = (int)fdiv((uint32_t)max(wi, 0), a.fd_sw);
-                ok = hi >= 0 && wi >= 0 && i2 * a.SH == hi && j2 * a.SW == wi && i2 < a.HO && j2 < a.WO;
-                p = goff[j] + (i2 * a.WO + j2) * a.O + o;
-            }
-            ok = ok && kin && goff[j] >= 0;
+            const bool ok = (unsigned)hi < (unsigned)a.HO && (unsigned)wi < (unsigned)a.WO && kin && goff[j] >= 0;
+            const int p = goff[j] + (hi * a.WO + wi) * a.O + o;
 #pragma unroll
             for (int u = 0; u < NGM; ++u)
                 if (part.take()) dma16(dma_src(ok, gsrc[u] + p, a.zero), base + (NIW3 + u * NIP + j) * 4096);
@@ -321,10 +358,10 @@ __global__ __launch_bounds__(kThreads) void qconv_bwd_data_kernel(const BwdDataA
     // neuron only.)
     if constexpr (OM == OM_PAIR || OM == OM_SQIN) {
         if (a.splits == 1 && (OM == OM_SQIN || a.neuron == NEURON_T4I))
-            neuron_dx_epilogue<T, OM, MR, MC>(acc, a.xin, a.M, a.C, pcol0, crow0, lane);
+            neuron_dx_epilogue<T, OM, MR, MC>(acc, a.xin, mp, a.C, pcol0, crow0, lane, prow);
     }
     // T2&4: acc += 2 X o acc2, linear, so every split applies it to its own partial
-    if constexpr (OM == OM_QSQ) qsq_dx_epilogue<T, MR, MC>(acc, acc2, a.xin, a.M, a.C, pcol0, crow0, lane);
+    if constexpr (OM == OM_QSQ) qsq_dx_epilogue<T, MR, MC>(acc, acc2, a.xin, mp, a.C, pcol0, crow0, lane, prow);
     const bool vec_out = (a.C & 3) == 0;
     T *__restrict__ dx = static_cast<T *>(a.dx);
 
@@ -356,7 +393,7 @@ __global__ __launch_bounds__(kThreads) void qconv_bwd_data_kernel(const BwdDataA
         for (int c = tid; c < BCOL * CPR; c += kThreads) {
             const int row = c / CPR, cc = c % CPR;
             const int m = ct * BCOL + row, ch = rt * BR + cc * (16 / E);
-            if (m < a.M && ch < a.C)
+            if (m < mp && ch < a.C)
                 *reinterpret_cast<v4u *>(out + (size_t)prow(m) * a.C + ch) = lds_read16(smem + row * PITCH + cc * 16);
         }
         return true;
@@ -367,7 +404,7 @@ __global__ __launch_bounds__(kThreads) void qconv_bwd_data_kernel(const BwdDataA
 #pragma unroll
         for (int mc = 0; mc < MC; ++mc) {
             const int m = pcol0 + mc * 32 + lrow;
-            if (m >= a.M) continue;
+            if (m >= mp) continue;
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
                 const int c = crow0 + mr * 32 + 8 * g + 4 * lhi;

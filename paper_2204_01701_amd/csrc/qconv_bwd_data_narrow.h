@@ -20,12 +20,18 @@
 //   - the 16 x 16 accumulator puts input pixel l % 16 and channels
 //     4 (l / 16) .. +4 in lane l: dX of a block is one contiguous run of 16
 //     NHWC rows.
-// Each wave takes every (waves)-th block of 16 input pixels.
+// Each wave takes every (waves)-th block of 16 input pixels.  At stride > 1 it
+// takes blocks of one phase (BwdPhase), whose taps alone are its reduction
+// and its weight runs, and the waves are shared out among the phases by
+// their taps (16 -> 32 channels, 256 x 32 x 32 maps, 3 x 3 at stride 2, whose
+// phases of 1, 2, 2 and 4 taps fit where the 9 taps did not: fp32 290 us in the
+// tiled kernel, 41 us here; bf16 43 and 20).
 #pragma once
 
 #include "qargs.h"
 #include "qdevice.h"
 #include "qconv_fwd_narrow.h"
+#include "qpipe.h"
 
 namespace ql {
 
@@ -41,17 +47,35 @@ __global__ __launch_bounds__(kThreads, 2) void qconv_bwd_data_narrow_kernel(cons
     const T *__restrict__ ta = static_cast<const T *>(a.ta);
     const T *__restrict__ tb = static_cast<const T *>(a.tb);
 
-    // This lane's reduction runs: k = CK ch + VEC lg .. + VEC, tap (r, q), first channel o.
-    int kr[NCH], kq[NCH], ko[NCH];
+    // This wave's phase, its rank among the phase's waves and their number: wave
+    // u of every a.units belongs to the phase with unit_end[phase - 1] <= u < unit_end[phase].
+    const int nw = gridDim.x * (kThreads / 64);
+    const int wid = blockIdx.x * (kThreads / 64) + wave_id();
+    int phase = 0, rank = wid, ranks = nw;
+    if constexpr (!S1) {
+        const int round = wid / a.units, u = wid - round * a.units;
+        while (u >= a.unit_end[phase]) ++phase;  // (u < units = the last phase's end)
+        const int at = phase ? a.unit_end[phase - 1] : 0, n = a.unit_end[phase] - at;
+        rank = round * n + u - at;
+        ranks = (nw / a.units) * n + min(max(nw % a.units - at, 0), n);
+    }
+    const BwdPhase ph(phase, a.H, a.W, a.KH, a.KW, S1 ? 1 : a.SH, S1 ? 1 : a.SW, a.PH, a.PW);
+    const int K = S1 ? a.K : ph.rp * ph.qp * a.O;
+    const int mp = S1 ? a.M : a.N * ph.hp * ph.wp;
+
+    // This lane's reduction runs: k = CK ch + VEC lg .. + VEC, the phase's tap
+    // (ri, qi), first channel o; kw: the run in the whole filter's row.
+    int kr[NCH], kq[NCH], ko[NCH], kw[NCH];
     bool kin[NCH];
 #pragma unroll
     for (int ch = 0; ch < NCH; ++ch) {
         const int k = CK * ch + VEC * lg;
-        kin[ch] = k < a.K;
-        const int tap = (int)fdiv((uint32_t)min(k, a.K - 1), a.fd_o);
+        kin[ch] = k < K;
+        const int tap = kin[ch] ? (int)fdiv((uint32_t)k, a.fd_o) : 0;
         ko[ch] = k - tap * a.O;
-        kr[ch] = (int)fdiv((uint32_t)tap, a.fd_kw);
-        kq[ch] = tap - kr[ch] * a.KW;
+        kr[ch] = S1 ? (int)fdiv((uint32_t)tap, a.fd_kw) : tap / max(ph.qp, 1);
+        kq[ch] = tap - kr[ch] * (S1 ? a.KW : ph.qp);
+        kw[ch] = S1 ? k : ((ph.r0 + a.SH * kr[ch]) * a.KW + ph.q0 + a.SW * kq[ch]) * a.O + ko[ch];
     }
     // The three terms' transposed weight runs: row c = 16 cb + li (zero past C or K).
     v4u wf[3][CB][NCH];
@@ -63,41 +87,44 @@ __global__ __launch_bounds__(kThreads, 2) void qconv_bwd_data_narrow_kernel(cons
             const int c = 16 * cb + li;
 #pragma unroll
             for (int ch = 0; ch < NCH; ++ch) {
-                const int k = CK * ch + VEC * lg;
-                wf[t][cb][ch] = (c < a.C && kin[ch]) ? *reinterpret_cast<const v4u *>(wt + (size_t)c * a.K + k)
+                wf[t][cb][ch] = (c < a.C && kin[ch]) ? *reinterpret_cast<const v4u *>(wt + (size_t)c * a.K + kw[ch])
                                                      : v4u{0u, 0u, 0u, 0u};
             }
         }
     }
 
     T *__restrict__ dx = static_cast<T *>(a.dx);
-    const int nblk = (a.M + 15) / 16;
-    const int nw = gridDim.x * (kThreads / 64);
-    for (int b = blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6); b < nblk; b += nw) {
-        // this lane's input pixel (B column)
-        const int p = 16 * b + li;
-        const bool pok = p < a.M;
-        const int pp = pok ? p : a.M - 1;
-        const int n = (int)fdiv((uint32_t)pp, a.fd_hw);
-        const int rem = pp - n * a.H * a.W;
-        const int h = (int)fdiv((uint32_t)rem, a.fd_w);
-        const int w = rem - h * a.W;
+    const int nblk = (mp + 15) / 16;
+    for (int b = rank; b < nblk; b += ranks) {
+        // this lane's input pixel (B column): image n, position (h, w) of the phase
+        const int m = 16 * b + li;
+        const bool pok = m < mp;
+        const int pp = pok ? m : mp - 1;
+        int n, h, w, p;
+        if constexpr (S1) {
+            n = (int)fdiv((uint32_t)pp, a.fd_hw);
+            const int rem = pp - n * a.H * a.W;
+            h = (int)fdiv((uint32_t)rem, a.fd_w);
+            w = rem - h * a.W;
+            p = m;
+        } else {
+            const uint32_t hw = ph.hp * ph.wp;
+            n = (uint32_t)pp / hw;
+            const uint32_t rem = pp - n * hw;
+            h = rem / (uint32_t)ph.wp;
+            w = rem - h * ph.wp;
+            p = (n * a.H + ph.h0 + a.SH * h) * a.W + ph.w0 + a.SW * w;
+        }
         const size_t nbase = (size_t)n * a.HO * a.WO;
         f32x4n_t acc[CB];
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb) acc[cb] = f32x4n_t{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
         for (int ch = 0; ch < NCH; ++ch) {
+            if (!S1 && CK * ch >= K) continue;  // (wave-uniform: past the phase's taps)
             // the output pixel tap (r, q) of this input pixel reads, if any
-            int oh = h + a.PH - kr[ch], ow = w + a.PW - kq[ch];
-            bool ok = pok && kin[ch] && oh >= 0 && ow >= 0;
-            if constexpr (!S1) {
-                const int qh = (int)fdiv((uint32_t)max(oh, 0), a.fd_sh), qw = (int)fdiv((uint32_t)max(ow, 0), a.fd_sw);
-                ok = ok && qh * a.SH == oh && qw * a.SW == ow;
-                oh = qh;
-                ow = qw;
-            }
-            ok = ok && oh < a.HO && ow < a.WO;
+            const int oh = h + ph.oh0 - kr[ch], ow = w + ph.ow0 - kq[ch];
+            const bool ok = pok && kin[ch] && (unsigned)oh < (unsigned)a.HO && (unsigned)ow < (unsigned)a.WO;
             const size_t off = (nbase + (size_t)oh * a.WO + ow) * a.O + ko[ch];
             const v4u zero = {0u, 0u, 0u, 0u};
             const v4u g = ok ? *reinterpret_cast<const v4u *>(gy + off) : zero;

@@ -538,9 +538,9 @@ __global__ __launch_bounds__(kThreads) void qconv_bwd_data_generic_kernel(const 
     const int pcol0 = ct * BCOL + wc * (BCOL / WGC);
     if constexpr (OM == OM_PAIR || OM == OM_SQIN) {
         if (a.splits == 1 && (OM == OM_SQIN || a.neuron == NEURON_T4I))
-            neuron_dx_epilogue<T, OM, MR, MC>(acc, a.xin, a.M, a.C, pcol0, crow0, lane);
+            neuron_dx_epilogue<T, OM, MR, MC>(acc, a.xin, a.M, a.C, pcol0, crow0, lane, [](int m) { return m; });
     }
-    if constexpr (OM == OM_QSQ) qsq_dx_epilogue<T, MR, MC>(acc, acc2, a.xin, a.M, a.C, pcol0, crow0, lane);
+    if constexpr (OM == OM_QSQ) qsq_dx_epilogue<T, MR, MC>(acc, acc2, a.xin, a.M, a.C, pcol0, crow0, lane, [](int m) { return m; });
     const bool vec_out = (a.C & 3) == 0;
     T *__restrict__ dx = static_cast<T *>(a.dx);
     float *__restrict__ ws = a.ws + (size_t)split * a.M * a.C;

@@ -197,10 +197,11 @@ template <typename T> __device__ __forceinline__ void load4(const T *p, float *f
 // Input-gradient epilogue of the T4 + identity and T2 neurons on a wave's
 // accumulator tile (rows: input channels c, columns: input pixels m, the MFMA
 // layout of mfma_chunk): acc += src[m, c] (src = G, the shortcut's gradient)
-// or acc *= 2 src[m, c] (src = X, the derivative of X o X).  src is M x C.
-template <typename T, int OM, int MR, int MC>
+// or acc *= 2 src[m, c] (src = X, the derivative of X o X).  src is N H W x C,
+// prow(m) the row of GEMM column m < M.
+template <typename T, int OM, int MR, int MC, class Row>
 __device__ __forceinline__ void neuron_dx_epilogue(f32x16_t (&acc)[MR][MC], const void *srcv, int M, int C,
-                                                   int pcol0, int crow0, int lane) {
+                                                   int pcol0, int crow0, int lane, Row &&prow) {
     const T *__restrict__ src = static_cast<const T *>(srcv);
     const int lrow = lane & 31, lhi = lane >> 5;
 #pragma unroll
@@ -209,16 +210,17 @@ __device__ __forceinline__ void neuron_dx_epilogue(f32x16_t (&acc)[MR][MC], cons
         for (int mc = 0; mc < MC; ++mc) {
             const int m = pcol0 + mc * 32 + lrow;
             if (m >= M) continue;
+            const T *__restrict__ sm = src + (size_t)prow(m) * C;
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
                 const int c = crow0 + mr * 32 + 8 * g + 4 * lhi;
                 float v[4] = {0.0f, 0.0f, 0.0f, 0.0f};
                 if ((C & 3) == 0 && c < C) {
-                    load4<T>(src + (size_t)m * C + c, v);  // four channels in one load
+                    load4<T>(sm + c, v);  // four channels in one load
                 } else {
 #pragma unroll
                     for (int i = 0; i < 4; ++i)
-                        if (c + i < C) v[i] = to_f32<T>(src[(size_t)m * C + c + i]);
+                        if (c + i < C) v[i] = to_f32<T>(sm[c + i]);
                 }
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
@@ -231,11 +233,12 @@ __device__ __forceinline__ void neuron_dx_epilogue(f32x16_t (&acc)[MR][MC], cons
 
 // Input-gradient epilogue of the T2&4 neuron: the terms a, b accumulated in
 // acc, the c term (whose operand is X o X) in acc2; acc += 2 X[m, c] acc2
-// (the chain rule through the square).  X is M x C.  Linear in the
+// (the chain rule through the square).  X is N H W x C, prow as above.  Linear in the
 // accumulators, so each split-K partial may take it before the sum.
-template <typename T, int MR, int MC>
+template <typename T, int MR, int MC, class Row>
 __device__ __forceinline__ void qsq_dx_epilogue(f32x16_t (&acc)[MR][MC], const f32x16_t (&acc2)[MR][MC],
-                                                const void *xv, int M, int C, int pcol0, int crow0, int lane) {
+                                                const void *xv, int M, int C, int pcol0, int crow0, int lane,
+                                                Row &&prow) {
     const T *__restrict__ x = static_cast<const T *>(xv);
     const int lrow = lane & 31, lhi = lane >> 5;
 #pragma unroll
@@ -243,17 +246,18 @@ __device__ __forceinline__ void qsq_dx_epilogue(f32x16_t (&acc)[MR][MC], const f
 #pragma unroll
         for (int mc = 0; mc < MC; ++mc) {
             const int m = pcol0 + mc * 32 + lrow;
+            const T *__restrict__ xm = x + (m < M ? (size_t)prow(m) * C : 0);
 #pragma unroll
             for (int g = 0; g < 4; ++g) {
                 const int c = crow0 + mr * 32 + 8 * g + 4 * lhi;
                 float v[4] = {0.0f, 0.0f, 0.0f, 0.0f};
                 if (m < M) {
                     if ((C & 3) == 0 && c < C) {
-                        load4<T>(x + (size_t)m * C + c, v);
+                        load4<T>(xm + c, v);
                     } else {
 #pragma unroll
                         for (int i = 0; i < 4; ++i)
-                            if (c + i < C) v[i] = to_f32<T>(x[(size_t)m * C + c + i]);
+                            if (c + i < C) v[i] = to_f32<T>(xm[c + i]);
                     }
                 }
 #pragma unroll
@@ -313,5 +317,35 @@ __device__ __forceinline__ TileCoord tile_coord(int bid, int order, int row_tile
     }
     return c;
 }
+
+// Input gradient at stride S: input pixel (h, w) meets only the taps (r, q)
+// with r = (h + PH) mod SH and q = (w + PW) mod SW, the pixel's phase.  The
+// pixels of one phase and its taps form a stride-1 problem of their own:
+// pixel (h0 + SH hh, w0 + SW ww), hh < hp, ww < wp, and tap (r0 + SH ri,
+// q0 + SW qi), ri < rp, qi < qp, meet at output pixel (oh0 + hh - ri,
+// ow0 + ww - qi).  Phases without pixels or taps have hp, wp, rp or qp 0.
+// (hp and wp serve the host's plan too.)
+struct BwdPhase {
+    int h0, w0, hp, wp, r0, q0, rp, qp, oh0, ow0;
+    __host__ __device__ static int first(int phase, int pad, int stride) {  // the first pixel of the phase
+        const int d = (phase - pad) % stride;
+        return d < 0 ? d + stride : d;
+    }
+    __host__ __device__ static int count(int x0, int size, int stride) {
+        return x0 < size ? (size - 1 - x0) / stride + 1 : 0;
+    }
+    __host__ __device__ BwdPhase(int phase, int H, int W, int KH, int KW, int SH, int SW, int PH, int PW) {
+        r0 = phase / SW;
+        q0 = phase - r0 * SW;
+        h0 = first(r0, PH, SH);
+        w0 = first(q0, PW, SW);
+        hp = count(h0, H, SH);
+        wp = count(w0, W, SW);
+        rp = count(r0, KH, SH);
+        qp = count(q0, KW, SW);
+        oh0 = (h0 + PH - r0) / SH;
+        ow0 = (w0 + PW - q0) / SW;
+    }
+};
 
 }  // namespace ql

@@ -426,6 +426,17 @@ struct BwdDataPlan {
     size_t wt_bytes, gpad_bytes, part_bytes, ws_bytes;  // workspace: [weights][G, T_a, T_b padded][split partials]
 };
 
+// At stride > 1 the kernels split the input pixels into phases (BwdPhase): the
+// most taps and the most pixels of any phase.
+inline void bwd_phase_extents(const Geom &g, int &taps, int &pixels) {
+    taps = pixels = 0;
+    for (int i = 0; i < g.SH * g.SW; ++i) {
+        const BwdPhase ph(i, g.H, g.W, g.KH, g.KW, g.SH, g.SW, g.PH, g.PW);
+        taps = std::max(taps, ph.rp * ph.qp);
+        pixels = std::max(pixels, g.N * ph.hp * ph.wp);
+    }
+}
+
 inline BwdDataPlan plan_bwd_data(const Geom &g) {
     BwdDataPlan p{};
     {
@@ -456,9 +467,15 @@ inline BwdDataPlan plan_bwd_data(const Geom &g) {
     p.Op = p.pad ? g.opad() : g.O;
     if (p.pad) p.gpad_bytes = align_up((size_t)g.N * g.HO * g.WO * p.Op * g.esize());
     const size_t gpads = om_gmaps(g.om()) * p.gpad_bytes;
-    const int M = g.N * g.H * g.W, K = g.KH * g.KW * p.Op;
-    p.veck = p.Op % g.vec() == 0;
     p.s1 = g.SH == 1 && g.SW == 1;
+    const int M = g.N * g.H * g.W;
+    int taps = g.KH * g.KW, phase_pixels = M;  // of one phase (stride 1: the whole map)
+    // (a phase per stride offset: past kMaxPhases the register-staged kernel,
+    // which gathers each tap's pixel)
+    const bool phases = !p.s1 && (long long)g.SH * g.SW <= kMaxPhases;
+    if (phases) bwd_phase_extents(g, taps, phase_pixels);
+    const int K = taps * p.Op;
+    p.veck = p.Op % g.vec() == 0 && (p.s1 || phases);
     // Narrow layers: the transposed weight runs of all three terms stay in registers.
     p.cb = cdiv(g.C, 16);
     p.nch = cdiv(K, 4 * g.vec());
@@ -494,15 +511,17 @@ inline BwdDataPlan plan_bwd_data(const Geom &g) {
     p.KE = p.cfg == 4 && p.veck ? 16 : 64 / (int)g.esize();
     p.slots = 1;
     p.row_tiles = cdiv(g.C, p.BR);
-    p.col_tiles = cdiv(M, p.BCOL);
-    p.stages_total = cdiv(K, p.KE);
+    // (register-staged kernel at stride > 1: every pixel meets every tap)
+    const bool phased = p.veck && phases;
+    p.col_tiles = phased ? g.SH * g.SW * cdiv(phase_pixels, p.BCOL) : cdiv(M, p.BCOL);
+    p.stages_total = cdiv(p.veck ? K : g.KH * g.KW * p.Op, p.KE);
     // Channel-aligned K steps (each within one tap) in the 4-wave kernels, and
     // with them, on small padded maps, the position-major order that skips
     // the taps whose output pixel lies outside the map for every position of
     // a pixel tile (the proposed neuron: 5 of 9 taps on a 2 x 2 map).
-    p.ca = p.s1 && p.natw && p.cfg != 4 && g.O % p.KE == 0 && g.KH * g.KW <= 32 &&
+    p.ca = p.natw && p.cfg != 4 && g.O % p.KE == 0 && g.KH * g.KW <= 32 &&
            env_override("QLAYER_BWD_DATA_CA", 1) != 0;
-    p.pm = p.ca && g.ne == NEURON_QUADRA && pm_default(g, env_override("QLAYER_BWD_DATA_POSMAJ", -1));
+    p.pm = p.ca && p.s1 && g.ne == NEURON_QUADRA && pm_default(g, env_override("QLAYER_BWD_DATA_POSMAJ", -1));
     int kst = p.stages_total;
     if (p.pm) kst = bd_pm_max_taps(g, p.BCOL, M) * (g.O / p.KE);
     plan_splits(p.row_tiles * p.col_tiles, kst, env_override("QLAYER_BWD_DATA_MINSTAGES", 4),

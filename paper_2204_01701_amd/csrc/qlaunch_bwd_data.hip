@@ -106,7 +106,14 @@ ql_status launch_bwd_data(const Geom &g, const BwdDataPlan &p, const void *gy, c
     a.fd_ops = make_fastdiv(a.ops);
     a.order = p.order;
     if (p.narrow) {
-        const dim3 grid((unsigned)(narrow_waves(a.M) / (kThreads / 64)));
+        if (!p.s1)
+            for (int i = 0; i < g.SH * g.SW; ++i) {
+                const BwdPhase ph(i, g.H, g.W, g.KH, g.KW, g.SH, g.SW, g.PH, g.PW);
+                a.units += std::max(ph.rp * ph.qp, 1);
+                a.unit_end[i] = (uint16_t)a.units;
+            }
+        // (a whole round of units, so that every phase of a strided layer has a wave)
+        const dim3 grid((unsigned)(cdiv(std::max(narrow_waves(a.M), a.units), kThreads / 64)));
 #define QL_BD_NARROW(CB, NCH)                                                                                        \
     do {                                                                                                             \
         if (p.s1)                                                                                                    \
@@ -130,7 +137,7 @@ ql_status launch_bwd_data(const Geom &g, const BwdDataPlan &p, const void *gy, c
         return hip_status();
     }
     const dim3 grid(p.row_tiles * p.col_tiles * p.splits), block(kThreads);
-    // channel-aligned K steps (each within one tap): stride 1, natural weight tiles, O a multiple of KE
+    // channel-aligned K steps (each within one tap): natural weight tiles, O a multiple of KE
     const bool bd_ca = p.ca;
     const int om = g.om();
 #define QL_BD_PIPE_N(BR, BCOL, WR, WC, NS, NW, OM)                                                                     \
@@ -146,8 +153,12 @@ ql_status launch_bwd_data(const Geom &g, const BwdDataPlan &p, const void *gy, c
     do {                                                                                                               \
         if constexpr (sizeof(T) == 2) {                                                                                \
             if (bd_ca) {                                                                                               \
-                hipLaunchKernelGGL((qconv_bwd_data_kernel<T, BR, BCOL, WR, WC, NS, true, true, true, OM>), grid, block, \
-                                   0, st, a);                                                                          \
+                if (p.s1)                                                                                              \
+                    hipLaunchKernelGGL((qconv_bwd_data_kernel<T, BR, BCOL, WR, WC, NS, true, true, true, OM>), grid,   \
+                                       block, 0, st, a);                                                               \
+                else                                                                                                   \
+                    hipLaunchKernelGGL((qconv_bwd_data_kernel<T, BR, BCOL, WR, WC, NS, false, true, true, OM>), grid,  \
+                                       block, 0, st, a);                                                               \
                 break;                                                                                                 \
             }                                                                                                          \
             if (p.natw) {                                                                                              \
