@@ -43,16 +43,16 @@ __global__ __launch_bounds__(kThreads) void qconv_bwd_data_kernel(const BwdDataA
     static_assert(!CA || NATW, "channel-aligned steps are implemented for natural weight tiles");
     constexpr int VEC = Elem<T>::VEC;
     constexpr int KE = 64 / (int)sizeof(T);
-    constexpr int ROWS = 3 * BR + 3 * BCOL;
-    constexpr int STAGE = ROWS * 64;
     constexpr int NTM = om_terms(OM), NGM = om_gmaps(OM);
-    constexpr int NIW3 = 3 * BR / 64;   // DMA instructions of the three weight tiles (layout)
-    constexpr int NIW = NTM * BR / 64;  // ... issued per thread per K step: the type's weight rows
+    constexpr int NIW3 = (3 * BR + 63) / 64;               // DMA instructions of the three weight tiles (layout)
+    constexpr int NIW = NTM == 3 ? NIW3 : NTM * BR / 64;   // ... issued per thread per K step: the type's weight rows
+    constexpr int WROWS = NIW3 * 64;  // 64-byte tile rows of the weight tiles (32-channel tiles: a fourth, of zeros)
+    constexpr int STAGE = (WROWS + 3 * BCOL) * 64;
     constexpr int NIP = BCOL / 64;      // ... rows of each of G, T_a, T_b
     constexpr int NI = NIW + NGM * NIP;
     constexpr int MR = BR / WGR / 32, MC = BCOL / WGC / 32;
     static_assert(WGR * WGC == kThreads / 64, "one wave per wave-tile");
-    static_assert(BR % 64 == 0 && BCOL % 64 == 0 && MR >= 1 && MC >= 1, "tile shape");
+    static_assert((BR % 64 == 0 || (BR == 32 && NTM == 3)) && BCOL % 64 == 0 && MR >= 1 && MC >= 1, "tile shape");
 
     __shared__ __attribute__((aligned(1024))) char smem[NS * STAGE];
 
@@ -68,11 +68,12 @@ __global__ __launch_bounds__(kThreads) void qconv_bwd_data_kernel(const BwdDataA
     const int mp = S1 ? a.M : a.N * ph.hp * ph.wp;  // GEMM columns of the phase
     if (!S1 && ct * BCOL >= mp) return;
     const int KP = S1 ? a.K : ph.rp * ph.qp * a.O;
-    // ri = tap / qp of a tap of the phase (tap < 2^32 / qp: exact)
+    // ri = tap / qp of a tap of the phase (tap < 2^32 / qp: exact), branch-free in the K loop
     const uint32_t qinv = S1 || ph.qp <= 1 ? 0u : 0xffffffffu / (uint32_t)ph.qp + 1u;
+    const uint32_t qone = ph.qp <= 1 ? ~0u : 0u;
     auto tap_row = [&](int tap) -> int {
         if constexpr (S1) return (int)fdiv((uint32_t)tap, a.fd_kw);
-        else return ph.qp <= 1 ? tap : (int)__umulhi((uint32_t)tap, qinv);
+        else return (int)(__umulhi((uint32_t)tap, qinv) | ((uint32_t)tap & qone));
     };
     const int QP = S1 ? a.KW : ph.qp;
     // the filter tap of the phase's tap (ri, qi)
@@ -136,12 +137,21 @@ __global__ __launch_bounds__(kThreads) void qconv_bwd_data_kernel(const BwdDataA
 #pragma unroll
     for (int i = 0; i < NIW; ++i) {
         const int row = 16 * (4 * i + wave) + (lane >> 2);
-        const int c = rt * BR + (row - ((64 * i) / BR) * BR);
-        woff[i] = c < a.C ? c * a.K : -1;
+        const int c = rt * BR + row % BR;
+        woff[i] = c < a.C && row < 3 * BR ? c * a.K : -1;
     }
     // Natural weight tiles: KE rows (K indices) of BR channels per term.
     constexpr int SW = BR / 8;          // 16-byte slots per weight row
     constexpr int WT = KE * BR * 2;     // bytes of one term's weight tile
+    // term and row of the weights that DMA instruction i of this wave copies
+    auto wtile_term = [&](int i) -> int {
+        if constexpr (WT % 4096 == 0) return (i * 4096) / WT;
+        else return (i * 4096 + wave * 1024) / WT;
+    };
+    auto wtile_row = [&](int i) -> int {
+        if constexpr (WT % 4096 == 0) return ((i * 4096) % WT + wave * 1024) / (SW * 16) + lane / SW;
+        else return ((i * 4096 + wave * 1024) % WT) / (SW * 16) + lane / SW;
+    };
     const int wslot = (lane % SW) ^ nat_swz<SW>(lane / SW);
     const int wc0 = rt * BR + 8 * wslot;
     const bool wc_ok = wc0 < a.C;
@@ -178,9 +188,8 @@ __global__ __launch_bounds__(kThreads) void qconv_bwd_data_kernel(const BwdDataA
         const int wcc = min(wc0, a.C - 8);
 #pragma unroll
         for (int i = 0; i < NIW; ++i) {
-            const int t = (i * 4096) / WT;
-            const int row = ((i * 4096) % WT + wave * 1024) / (SW * 16) + lane / SW;
-            wrow[i] = wt[t] + (size_t)row * khkw * a.C + wcc;
+            const int row = wtile_row(i);
+            wrow[i] = wt[min(wtile_term(i), 2)] + (size_t)row * khkw * a.C + wcc;
         }
 #pragma unroll
         for (int j = 0; j < NIP; ++j) {
@@ -225,10 +234,12 @@ __global__ __launch_bounds__(kThreads) void qconv_bwd_data_kernel(const BwdDataA
             }
             const int r = tap_row(tap);
             const int q = tap - r * QP;
-            const long long sw = ((long long)o0 * khkw + wtap(r, q)) * a.C;
+            const long long sw = ((long long)o0 * khkw + (S1 ? tap : wtap(r, q))) * a.C;
 #pragma unroll
             for (int i = 0; i < NIW; ++i)
-                if (part.take()) dma16(dma_src(wc_ok, wrow[i] + sw, a.zero), base + i * 4096);
+                if (part.take())
+                    dma16(dma_src(wc_ok && (WT % 4096 == 0 || wtile_term(i) < 3), wrow[i] + sw, a.zero),
+                          base + i * 4096);
             const long long sg = o0 - ((long long)r * a.WO + q) * a.O;
 #pragma unroll
             for (int j = 0; j < NIP; ++j) {
@@ -241,7 +252,7 @@ __global__ __launch_bounds__(kThreads) void qconv_bwd_data_kernel(const BwdDataA
             return;
         }
         const int k = s * KE + kcol * VEC;
-        const bool kin = live && k < KP;
+        const bool kin = live & (k < KP);
         const int tap = (int)fdiv((uint32_t)k, a.fd_o);
         const int o = k - tap * a.O;
         const int r = tap_row(tap);
@@ -249,31 +260,34 @@ __global__ __launch_bounds__(kThreads) void qconv_bwd_data_kernel(const BwdDataA
         if constexpr (NATW) {
 #pragma unroll
             for (int i = 0; i < NIW; ++i) {
-                const int t = (i * 4096) / WT;
-                const int row = ((i * 4096) % WT + wave * 1024) / (SW * 16) + lane / SW;
+                const int t = wtile_term(i);
+                const int row = wtile_row(i);
                 const int kr = s * KE + row;
                 int tapr = (int)fdiv((uint32_t)kr, a.fd_o);
                 const int orow = kr - tapr * a.O;
-                const bool ok = live && wc_ok && kr < KP;
+                const bool ok = live & wc_ok & (kr < KP) & (t < 3);
                 if constexpr (!S1) {
                     const int ri = tap_row(tapr);
                     tapr = wtap(ri, tapr - ri * QP);
                 }
                 if (part.take())
-                    dma16(dma_src(ok, wt[t] + ((size_t)(orow * khkw + tapr) * a.C + wc0), a.zero), base + i * 4096);
+                    dma16(dma_src(ok, wt[min(t, 2)] + ((size_t)(orow * khkw + tapr) * a.C + wc0), a.zero), base + i * 4096);
             }
         } else {
             const int kw = S1 ? k : wtap(r, q) * a.O + o;  // k in the whole filter
 #pragma unroll
             for (int i = 0; i < NIW; ++i) {
-                const bool ok = kin && woff[i] >= 0;
-                if (part.take()) dma16(dma_src(ok, wt[(64 * i) / BR] + woff[i] + kw, a.zero), base + i * 4096);
+                const bool ok = kin & (woff[i] >= 0);
+                if (part.take()) dma16(dma_src(ok, wt[BR >= 64 ? (64 * i) / BR : min((64 * i + 16 * wave) / BR, 2)] + woff[i] + kw, a.zero), base + i * 4096);
             }
         }
 #pragma unroll
         for (int j = 0; j < NIP; ++j) {
             const int hi = hh[j] - r, wi = ww[j] - q;
-            const bool ok = (unsigned)hi < (unsigned)a.HO && (unsigned)wi < (unsigned)a.WO && kin && goff[j] >= 0;
+            // (bitwise: as && the compiler branched around it, which split the K loop's
+            // block and kept its MFMAs from interleaving, 72 -> 81 us in fp32 on 32 -> 32
+            // channels, 256 x 16 x 16 maps)
+            const bool ok = ((unsigned)hi < (unsigned)a.HO) & ((unsigned)wi < (unsigned)a.WO) & kin & (goff[j] >= 0);
             const int p = goff[j] + (hi * a.WO + wi) * a.O + o;
 #pragma unroll
             for (int u = 0; u < NGM; ++u)
@@ -308,7 +322,7 @@ __global__ __launch_bounds__(kThreads) void qconv_bwd_data_kernel(const BwdDataA
         for (int mc = 0; mc < MC; ++mc) {
             const int prow = wc * (BCOL / WGC) + mc * 32;
 #pragma unroll
-            for (int u = 0; u < NGM; ++u) gr[set][u][mc] = lds_read16(base + (3 * BR + u * BCOL + prow) * 64);
+            for (int u = 0; u < NGM; ++u) gr[set][u][mc] = lds_read16(base + (WROWS + u * BCOL + prow) * 64);
         }
         if constexpr (NATW) {
             const char *wtile = smem + slot * STAGE;

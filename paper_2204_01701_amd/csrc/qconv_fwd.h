@@ -31,17 +31,17 @@ template <typename T, int BR, int BCOL, int WGR, int WGC, int NS, bool CA, int N
 __global__ __launch_bounds__(NT) void qconv_fwd_kernel(const FwdArgs a) {
     constexpr int VEC = Elem<T>::VEC;
     constexpr int KE = 64 / (int)sizeof(T);  // reduction elements per K step
-    constexpr int ROWS = 3 * BR + BCOL;
-    constexpr int STAGE = ROWS * 64;
     constexpr int RPI = NT / 4;         // 64-byte tile rows one DMA instruction of the workgroup fills
     constexpr int NTM = om_terms(OM);   // first-order terms
-    constexpr int NIW3 = 3 * BR / RPI;  // DMA instructions of the three weight blocks (tile layout)
-    constexpr int NIW = NTM * BR / RPI; // ... of the blocks this type has (issued per thread per K step)
+    constexpr int NIW3 = (3 * BR + RPI - 1) / RPI;  // DMA instructions of the three weight blocks (tile layout)
+    constexpr int NIW = NTM == 3 ? NIW3 : NTM * BR / RPI; // ... of the blocks this type has (issued per thread per K step)
+    constexpr int WROWS = NIW3 * RPI;   // tile rows of the weight blocks (32-channel blocks: a fourth, of zeros)
+    constexpr int STAGE = (WROWS + BCOL) * 64;
     constexpr int NIX = BCOL / RPI;     // ... pixel rows
     constexpr int NI = NIW + NIX;
     constexpr int MR = BR / WGR / 32, MC = BCOL / WGC / 32;
     static_assert(WGR * WGC == NT / 64, "one wave per wave-tile");
-    static_assert((3 * BR) % RPI == 0 && BCOL % RPI == 0 && MR >= 1 && MC >= 1, "tile shape");
+    static_assert(BR % 32 == 0 && BCOL % RPI == 0 && MR >= 1 && MC >= 1, "tile shape");
     static_assert(NTM == 3 || BR % RPI == 0, "each weight DMA instruction within one term block");
 
     __shared__ __attribute__((aligned(1024))) char smem[NS * STAGE];
@@ -93,13 +93,13 @@ __global__ __launch_bounds__(NT) void qconv_fwd_kernel(const FwdArgs a) {
         const int row = RPI * i + 16 * wave + (lane >> 2);
         const int t = row / BR;
         const int o = rt * BR + (row - t * BR);
-        wterm[i] = t;
-        woff[i] = o < a.O ? o * a.K : -1;
+        wterm[i] = min(t, 2);
+        woff[i] = o < a.O && t < 3 ? o * a.K : -1;
     }
     int xoff[NIX], ih0[NIX], iw0[NIX];
 #pragma unroll
     for (int j = 0; j < NIX; ++j) {
-        const int p = RPI * (NIW3 + j) + 16 * wave + (lane >> 2) - 3 * BR;
+        const int p = RPI * j + 16 * wave + (lane >> 2);
         const int m = ct * BCOL + p;
         if (m < a.M) {
             const int n = (int)fdiv((uint32_t)m, a.fd_howo);
@@ -134,12 +134,12 @@ __global__ __launch_bounds__(NT) void qconv_fwd_kernel(const FwdArgs a) {
             const int row = RPI * i + 16 * wave + (lane >> 2);
             const int t = row / BR;
             const int o = rt * BR + (row - t * BR);
-            wok[i] = o < a.O;
-            wrow[i] = wp[t] + (size_t)min(o, a.O - 1) * a.K + kcol * VEC;
+            wok[i] = o < a.O && t < 3;
+            wrow[i] = wp[min(t, 2)] + (size_t)min(o, a.O - 1) * a.K + kcol * VEC;
         }
 #pragma unroll
         for (int j = 0; j < NIX; ++j) {
-            const int p = RPI * (NIW3 + j) + 16 * wave + (lane >> 2) - 3 * BR;
+            const int p = RPI * j + 16 * wave + (lane >> 2);
             const int m = min(ct * BCOL + p, a.M - 1);
             int n, rem;
             if (a.pm) {
@@ -243,7 +243,7 @@ __global__ __launch_bounds__(NT) void qconv_fwd_kernel(const FwdArgs a) {
         const char *base = smem + slot * STAGE + lrow * 64 + (ch == 0 ? colx0 : colx1);
 #pragma unroll
         for (int mc = 0; mc < MC; ++mc)
-            bf[set][mc] = lds_read16(base + (3 * BR + wc * (BCOL / WGC) + mc * 32) * 64);
+            bf[set][mc] = lds_read16(base + (WROWS + wc * (BCOL / WGC) + mc * 32) * 64);
 #pragma unroll
         for (int t = 0; t < NTM; ++t)
 #pragma unroll

@@ -250,20 +250,32 @@ inline int bd_pm_max_taps(const Geom &g, int bcol, long long M) {
 // Pipelined forward tile configurations (rows = output channels per term,
 // columns = output pixels; per-wave tile in parentheses; 4 waves unless noted):
 //   0: 128 x 128 (32 x 128), 1: 64 x 256 (32 x 128), 2: 128 x 128 (64 x 64), 3: 64 x 128 (32 x 64),
-//   4: 128 x 256 (32 x 128, 8 waves), 5: 128 x 256 (64 x 64, 8 waves), 6: as 4 with four LDS stages.
+//   4: 128 x 256 (32 x 128, 8 waves), 5: 128 x 256 (64 x 64, 8 waves), 6: as 4 with four LDS stages,
+//   7: 32 x 128 (32 x 32).
 // Larger workgroup tiles move fewer bytes through the vector-memory address
 // path per MFMA: 32768 (1/BCOL + 1/(3 BR)) bytes.
-constexpr int kFwdCfgs = 7;
-constexpr int kFwdBR[kFwdCfgs] = {128, 64, 128, 64, 128, 128, 128};
-constexpr int kFwdBCOL[kFwdCfgs] = {128, 256, 128, 128, 256, 256, 256};
+constexpr int kFwdCfgs = 8;
+constexpr int kFwdBR[kFwdCfgs] = {128, 64, 128, 64, 128, 128, 128, 32};
+constexpr int kFwdBCOL[kFwdCfgs] = {128, 256, 128, 128, 256, 256, 256, 128};
 // Workgroups one CU holds at once (limited by LDS stages and registers).
-constexpr int kFwdSlots[kFwdCfgs] = {1, 1, 1, 2, 1, 1, 1};
+constexpr int kFwdSlots[kFwdCfgs] = {1, 1, 1, 2, 1, 1, 1, 2};
 
 // Waves of the narrow kernels (a multiple of the four per workgroup): one per
 // 16-pixel block up to three per SIMD, then more blocks per wave.
 inline int narrow_waves(long long pixels) {
     const long long waves = std::min<long long>(std::max<long long>(1, cdiv(pixels, 16)), 3LL * 4 * kNumCUs);
     return (int)(cdiv(waves, 4) * 4);
+}
+
+// Whether the 32-row tiles serve `rows` GEMM rows (channels) better than the
+// 64-row ones: in fp32, whose MFMAs bound the kernels, wherever they leave
+// fewer empty rows; in bf16, whose copies of the pixel operand do, only up to 32
+// rows.  us per call (64-row against 32-row; forward, input gradient): 32 -> 32
+// channels, 256 x 16 x 16 maps, 3 x 3, fp32 67, 81 against 39, 52, bf16 14.9, 22.6
+// against 12.3, 20.2; 96 -> 96, 128 x 14 x 14, fp32 165, 188 against 121, 172, bf16
+// 25.5, 46.4 against 29.4, 61.2.
+inline bool rows32(int rows, ql_dtype dt) {
+    return dt == QL_F32 ? cdiv(rows, 32) * 32 < cdiv(rows, 64) * 64 : rows <= 32;
 }
 
 struct FwdPlan {
@@ -324,7 +336,7 @@ inline FwdPlan plan_fwd(const Geom &g) {
         const bool big = g.O >= 128 && (long long)cdiv(g.O, 128) * cdiv(M, 256) >= 4 * kNumCUs;
         // (the 8-wave tile with four stages where the filter has several taps: measured 3 % faster on
         // the N=64, 256-channel 56 x 56 layer, and no faster on the dense layer)
-        p.cfg = env_override("QLAYER_FWD_CFG", big ? (g.KH * g.KW > 1 ? 6 : 4) : 3);
+        p.cfg = env_override("QLAYER_FWD_CFG", big ? (g.KH * g.KW > 1 ? 6 : 4) : rows32(g.O, g.dt) ? 7 : 3);
         if (p.cfg < 0 || p.cfg >= kFwdCfgs || g.ne != NEURON_QUADRA) p.cfg = 3;  // (the other types: tile 3 only)
         p.BR = kFwdBR[p.cfg];
         p.BCOL = kFwdBCOL[p.cfg];
@@ -402,9 +414,10 @@ inline FwdPlan plan_fwd(const Geom &g) {
 // with the four waves side by side (each 128 x 32: half the prologue
 // products per MFMA of configuration 0), 5: 64 x 128 with the waves side by
 // side (each 64 x 32: half the products per MFMA of configuration 1).
-constexpr int kBdCfgs = 6;
-constexpr int kBdBR[kBdCfgs] = {128, 64, 128, 128, 256, 64};
-constexpr int kBdBCOL[kBdCfgs] = {128, 128, 64, 128, 256, 128};  // 4: the wide kernel (8 waves, 16-channel K steps)
+// 6: 32 x 128, the waves side by side.
+constexpr int kBdCfgs = 7;
+constexpr int kBdBR[kBdCfgs] = {128, 64, 128, 128, 256, 64, 32};
+constexpr int kBdBCOL[kBdCfgs] = {128, 128, 64, 128, 256, 128, 128};  // 4: the wide kernel (8 waves, 16-channel K steps)
 
 struct BwdDataPlan {
     int cfg;  // pipelined: index into kBd*; generic: 0: 128 x 128, 1: 64 x 128
@@ -491,8 +504,8 @@ inline BwdDataPlan plan_bwd_data(const Geom &g) {
     // the wide kernel: bf16, natural weight tiles, stride 1, 16-channel K steps within one tap
     const bool wide_ok = p.natw && p.s1 && g.O % 16 == 0 && g.KH * g.KW <= 32;
     if (p.veck) {
-        int dflt = 5;
-        if (g.C > 64) dflt = M >= 1024 ? 3 : 2;
+        int dflt = rows32(g.C, g.dt) ? 6 : 5;
+        if (g.C > 64 && dflt != 6) dflt = M >= 1024 ? 3 : 2;
         // (measured: faster where its 256 x 256 tiles fill the GPU at least twice, as on
         // the dense layer and the N=64, 256-channel 56 x 56 layer; on the small maps of
         // VGG-16 the 4-wave tiles win, the wide kernel's 8 waves run their product

@@ -208,6 +208,8 @@ ql_status launch_bwd_data(const Geom &g, const BwdDataPlan &p, const void *gy, c
             QL_BD_PIPE(128, 128, 1, 4, 3);
         else if (p.cfg == 5)
             QL_BD_PIPE(64, 128, 1, 4, 4);
+        else if (p.cfg == 6)
+            QL_BD_PIPE(32, 128, 1, 4, 4);
         else
             QL_BD_PIPE(128, 64, 2, 2, 4);
     } else if (p.cfg == 0) {

@@ -148,3 +148,30 @@ def test_bwd_data_block_orders(shape, bf16, monkeypatch):
         dx.append(got["dx"])
     for order in (1, 2):
         assert np.array_equal(dx[0], dx[order]), f"order {order} differs from order 0"
+
+
+# rows (output channels of the forward, input channels of the input gradient) at the edges of the 32-row tiles
+R32_SHAPES = [(3, 32, 9, 7, 32, 3, 3, 1, 1), (2, 24, 6, 5, 20, 3, 3, 1, 1), (2, 96, 5, 6, 72, 3, 3, 1, 1),
+              (4, 32, 8, 9, 160, 1, 1, 1, 0)]
+
+
+@pytest.mark.parametrize("bf16", [False, True], ids=["fp32", "bf16"])
+@pytest.mark.parametrize("shape", R32_SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_conv_32_row_tiles(shape, bf16, monkeypatch):
+    """The 32-row tiles of the forward and the input gradient, forced (with and
+    without channel-aligned steps in the forward)."""
+    N, C, H, W, O, KH, KW, s, p = shape
+    inp = synth.random_conv_case([61] + list(shape), N, C, H, W, O, KH, KW, s, p, bf16=bf16)
+    y, ta, tb = oracle.conv2d_fwd(inp["x"], inp["wa"], inp["wb"], inp["wc"], inp["ba"], inp["bb"], inp["bc"], s, p)
+    ref = oracle.conv2d_bwd(inp["x"], inp["wa"], inp["wb"], inp["wc"], inp["ba"], inp["bb"], inp["bc"], inp["gy"], s, p)
+    monkeypatch.setenv("QLAYER_FWD_CFG", "7")
+    monkeypatch.setenv("QLAYER_BWD_DATA_CFG", "6")
+    monkeypatch.setenv("QLAYER_FWD_KSPLIT", "0")
+    for ca in "01":
+        print(f"32-row tiles {shape} bf16={bf16} ca={ca}", flush=True)
+        monkeypatch.setenv("QLAYER_FWD_CA", ca)
+        monkeypatch.setenv("QLAYER_BWD_DATA_CA", ca)
+        got = qlh.conv_to_np(qlh.run_conv(inp, s, p, bf16))
+        for k, want in (("y", y), ("ta", ta), ("tb", tb), ("dx", ref["dx"])):
+            e = qlh.relerr(got[k], want)
+            assert e <= qlh.tol(bf16, k == "dx"), f"{k}: normwise relative error {e:.3e}"
