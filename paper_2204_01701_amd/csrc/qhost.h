@@ -45,7 +45,7 @@ constexpr double kReduceSteps = 6.0;  // the reduction kernel's launch and ramp
 // the forward of 64 -> 64 channels, 256 x 8 x 8 maps, 3 x 3, goes from 64 to 40
 // us, 32 -> 64 at stride 2 from 37 to 26, the input gradient of 128 -> 128,
 // 16 x 14 x 14 maps, 1 x 1, from 32 to 24; above 3 the weight gradients slow down.
-constexpr double kF32Step = 3.0;
+// That is one per weighted term: the types with fewer terms run as many fewer MFMAs.
 // A workgroup of two pipelines (one per CU) on the two halves of its K range:
 // the cost of a K step of each pipeline, in the units above.  The two
 // pipelines share the workgroup's barriers, which costs them some of the
@@ -106,6 +106,9 @@ struct Geom {
     }
 };
 
+// Length of a K step in the split model's units (see kReduceSteps).
+inline double step_scale(const Geom &g) { return g.dt == QL_F32 ? g.terms() : 1.0; }
+
 inline ql_status make_geom(const ql_conv_desc *d, Geom &g) {
     if (!d) return QL_EINVAL;
     if (d->n <= 0 || d->c <= 0 || d->h <= 0 || d->w <= 0 || d->o <= 0 || d->kh <= 0 || d->kw <= 0)
@@ -152,9 +155,8 @@ inline ql_status linear_geom(const ql_linear_desc *d, Geom &g) {
 // avoids.  At least min_stages K steps per split, at most kMaxSplitBytes of
 // partial sums (bytes_per_split each).
 inline double plan_splits(int tiles, int stages_total, int min_stages, size_t bytes_per_split, int slots, int &splits,
-                          int &sps, bool f32, size_t max_bytes = kMaxSplitBytes, int pipes = 1,
+                          int &sps, double step_scale, size_t max_bytes = kMaxSplitBytes, int pipes = 1,
                           double shared_round = kSharedRound, double step_cost = 1.0) {
-    const double f32_scale = f32 ? kF32Step : 1.0;
     const int cap_bytes = (int)std::max<size_t>(1, max_bytes / std::max<size_t>(bytes_per_split, 1));
     const int s_max = std::max(1, std::min(stages_total / std::max(min_stages, 1), cap_bytes));
     double best = 0.0;
@@ -172,7 +174,7 @@ inline double plan_splits(int tiles, int stages_total, int min_stages, size_t by
         if (rest > 0) rounds += rest > kNumCUs ? shared_round : 1.0;
         double t = per * rounds * step_cost;
         if (pipes > 1) t = (double)cdiv(per, pipes) * (double)(full + (rest > 0)) * kPipeRound;
-        if (eff > 1) t += ((double)eff * bytes_per_split * 2.0 / kBytesPerStep + kReduceSteps) / f32_scale;
+        if (eff > 1) t += ((double)eff * bytes_per_split * 2.0 / kBytesPerStep + kReduceSteps) / step_scale;
         if (s == 1 || t < best) {
             best = t;
             splits = eff;
@@ -367,7 +369,7 @@ inline FwdPlan plan_fwd(const Geom &g) {
     int kst = p.stages_total;
     if (p.pm) kst = pm_max_taps(g, p.BCOL, M) * (p.Cp / p.KE);
     plan_splits(p.row_tiles * p.col_tiles, kst, env_override("QLAYER_FWD_MINSTAGES", 4), (size_t)3 * M * g.O * 4,
-                p.slots, p.splits, p.sps, g.dt == QL_F32, kMaxSplitBytes, 1, kSharedRoundFwd);
+                p.slots, p.splits, p.sps, step_scale(g), kMaxSplitBytes, 1, kSharedRoundFwd);
     // Where these tiles would split K over workgroups (small outputs: the 4 x 4
     // and 2 x 2 maps of a CIFAR VGG-16), the in-workgroup K split of
     // qconv_fwd_ksplit.h instead: tiles small enough to fill the GPU, no
@@ -538,7 +540,7 @@ inline BwdDataPlan plan_bwd_data(const Geom &g) {
     int kst = p.stages_total;
     if (p.pm) kst = bd_pm_max_taps(g, p.BCOL, M) * (g.O / p.KE);
     plan_splits(p.row_tiles * p.col_tiles, kst, env_override("QLAYER_BWD_DATA_MINSTAGES", 4),
-                (size_t)M * g.C * 4, p.slots, p.splits, p.sps, g.dt == QL_F32);
+                (size_t)M * g.C * 4, p.slots, p.splits, p.sps, step_scale(g));
     // Block order of the split grid: tile-major (each XCD's blocks share pixel
     // tiles: their rows of G, T_a, T_b once, all of the weights) where G, T_a,
     // T_b are at least the weight bytes (M >= C KH KW), split-major otherwise
@@ -661,7 +663,7 @@ inline BwdWeightPlan plan_bwd_weight(const Geom &g, size_t max_split_bytes = kMa
         p.row_tiles = cdiv(KP, p.BKP);
         p.col_tiles = cdiv(g.O, p.BO);
         return plan_splits(p.row_tiles * p.col_tiles, p.stages_total, min_stages, bytes_per_split, p.slots, p.splits,
-                           p.sps, g.dt == QL_F32, max_split_bytes, kBwPipes[cfg], kSharedRound, cfg == 5 ? kFatStep : 1.0);
+                           p.sps, step_scale(g), max_split_bytes, kBwPipes[cfg], kSharedRound, cfg == 5 ? kFatStep : 1.0);
     };
     if (p.pipe && g.ne == NEURON_QUADRA) {
         // the 16 x 16 x 32 kernel: four waves on a 64-channel tile, two such pipelines per
