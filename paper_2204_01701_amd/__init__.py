@@ -18,6 +18,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
 
 __all__ = [
     "QL_F32", "QL_BF16", "QL_NEURON_QUADRA", "QL_NEURON_T4", "QL_NEURON_T4_IDENTITY", "QL_NEURON_T3",
@@ -294,6 +295,113 @@ def _check(func, status):
         raise QLError(func, status)
 
 
+# --- the short way through a call -----------------------------------------------
+# A small layer's pass is a few microseconds of GPU work, so the host's share
+# of a call counts: the checks above, one Python call and several attribute
+# lookups per tensor, took more than the launches did.  _pointers makes the same
+# checks in one loop and returns the pointers; on anything unusual (a wrong
+# tensor, raw pointers, an unknown dtype) it returns None and the caller goes
+# through the checks above, which raise what is to be raised.
+
+_CONV_FIELDS = struct.Struct("14i")  # ConvDesc
+_LINEAR_FIELDS = struct.Struct("5i")  # LinearDesc
+_dtypes = {}  # (filled on the first call: importing this module does not import torch)
+
+
+def _conv_plan(d):
+    """_conv_sizes and the dtype code, from one read of the descriptor."""
+    n, c, h, w, o, kh, kw, sh, sw, ph, pw, dt, _, groups = _CONV_FIELDS.unpack_from(d)
+    if sh < 1 or sw < 1:
+        return None
+    ny = n * ((h + 2 * ph - kh) // sh + 1) * ((w + 2 * pw - kw) // sw + 1) * o
+    return n * h * w * c, o * kh * kw * (1 if groups == c and c > 1 else c), ny, o, dt
+
+
+def _linear_plan(d):
+    b, i, o, dt, _ = _LINEAR_FIELDS.unpack_from(d)
+    return b * i, o * i, b * o, o, dt
+
+
+def _current_stream(dev):
+    """Handle of the current stream of device `dev` (without building a torch.cuda.Stream)."""
+    import torch
+    return torch._C._cuda_getCurrentRawStream(dev)
+
+
+def _pointers(plan, roles, tensors):
+    """The data pointers of `tensors` (None: NULL) and their device index, or None.
+
+    roles: per tensor "x" (shaped like X), "w" (a weight), "y" (an output-side
+    map), "b" (float32 of O) or "g" (a float32 weight gradient)."""
+    if plan is None:
+        return None
+    nx, nw, ny, no, code = plan
+    dt = _dtypes.get(code)
+    if dt is None:
+        if _dtypes:
+            return None
+        import torch
+        _dtypes.update({QL_F32: torch.float32, QL_BF16: torch.bfloat16})
+        dt = _dtypes.get(code)
+    f32 = _dtypes[QL_F32]
+    out, dev = [], -1
+    for role, t in zip(roles, tensors):
+        if t is None:
+            out.append(None)
+            continue
+        if t.__class__ is int:
+            return None
+        if role == "y":
+            n, d = ny, dt
+        elif role == "w":
+            n, d = nw, dt
+        elif role == "x":
+            n, d = nx, dt
+        elif role == "b":
+            n, d = no, f32
+        else:
+            n, d = nw, f32
+        if t.numel() != n or t.dtype is not d or not t.is_cuda or not t.is_contiguous() or dt is None:
+            return None
+        i = t.get_device()
+        if i != dev:
+            if dev >= 0:
+                return None
+            dev = i
+        out.append(t.data_ptr())
+    return (out, dev) if dev >= 0 else None
+
+
+def _call(name, query, desc, plan, roles, tensors, workspace, stream, epi=None, query_epi=False, extra=()):
+    """Run the entry point `name` on checked tensors; False if they need the long way.
+
+    extra: the epilogue's tensors (float32 of O; checked, their pointers are in epi)."""
+    got = _pointers(plan, roles + "b" * len(extra), (*tensors, *extra))
+    if got is None:
+        return False
+    ptrs, dev = got
+    del ptrs[len(tensors):]
+    if stream is None:
+        st = _current_stream(dev)
+    else:
+        st = stream if isinstance(stream, int) else stream.cuda_stream
+    ref = ctypes.byref(desc)
+    L = lib()
+    if workspace is None:
+        need = getattr(L, query)(ref, epi) if query_epi else getattr(L, query)(ref)
+        import torch
+        wp, wn = _workspace(None, need, torch.device("cuda", dev), stream)
+    elif isinstance(workspace, tuple):
+        wp, wn = workspace
+    else:
+        wp, wn = workspace.data_ptr(), workspace.numel() * workspace.element_size()
+    f = getattr(L, name)
+    status = f(ref, *ptrs, epi, wp, wn, st) if query_epi else f(ref, *ptrs, wp, wn, st)
+    if status != 0:
+        raise QLError(name, status)
+    return True
+
+
 # --- the C ABI, one Python function per entry point -------------------------
 
 def qlayer_conv2d_fwd_workspace_size(desc: ConvDesc) -> int:
@@ -302,6 +410,9 @@ def qlayer_conv2d_fwd_workspace_size(desc: ConvDesc) -> int:
 
 def qlayer_conv2d_fwd(desc, x, wa, wb, wc, ba=None, bb=None, bc=None, y=None, ta=None, tb=None,
                       workspace=None, stream=None):
+    if _call("qlayer_conv2d_fwd", "qlayer_conv2d_fwd_workspace_size", desc, _conv_plan(desc), "xwwwbbbyyy",
+             (x, wa, wb, wc, ba, bb, bc, y, ta, tb), workspace, stream):
+        return
     dev = _device(x, wa)
     _check_args(_conv_sizes(desc), desc.dtype, dev, act=[("x", x)], weights=[("wa", wa), ("wb", wb), ("wc", wc)],
                 maps=[("y", y), ("ta", ta), ("tb", tb)], vec32=[("ba", ba), ("bb", bb), ("bc", bc)])
@@ -316,8 +427,11 @@ def qlayer_conv2d_bwd_data_workspace_size(desc: ConvDesc) -> int:
 
 
 def qlayer_conv2d_bwd_data(desc, gy, ta, tb, wa, wb, wc, dx, workspace=None, stream=None):
-    dev = _device(gy, wa)
     t2 = desc.neuron == QL_NEURON_T2  # (its `ta` carries X)
+    if _call("qlayer_conv2d_bwd_data", "qlayer_conv2d_bwd_data_workspace_size", desc, _conv_plan(desc),
+             "yxywwwx" if t2 else "yyywwwx", (gy, ta, tb, wa, wb, wc, dx), workspace, stream):
+        return
+    dev = _device(gy, wa)
     _check_args(_conv_sizes(desc), desc.dtype, dev, act=[("dx", dx)] + ([("ta (X)", ta)] if t2 else []),
                 weights=[("wa", wa), ("wb", wb), ("wc", wc)],
                 maps=[("gy", gy), ("tb", tb)] + ([] if t2 else [("ta", ta)]))
@@ -329,8 +443,11 @@ def qlayer_conv2d_bwd_data(desc, gy, ta, tb, wa, wb, wc, dx, workspace=None, str
 
 def qlayer_conv2d_bwd_data_ex(desc, gy, ta, tb, x, wa, wb, wc, dx, workspace=None, stream=None):
     """qlayer_conv2d_bwd_data with the layer input X (T2&4 needs it; T2 may take it in place of `ta`)."""
-    dev = _device(gy, wa)
     t2 = desc.neuron == QL_NEURON_T2
+    if _call("qlayer_conv2d_bwd_data_ex", "qlayer_conv2d_bwd_data_workspace_size", desc, _conv_plan(desc),
+             "yxyxwwwx" if t2 else "yyyxwwwx", (gy, ta, tb, x, wa, wb, wc, dx), workspace, stream):
+        return
+    dev = _device(gy, wa)
     _check_args(_conv_sizes(desc), desc.dtype, dev, act=[("dx", dx), ("x", x)] + ([("ta (X)", ta)] if t2 else []),
                 weights=[("wa", wa), ("wb", wb), ("wc", wc)],
                 maps=[("gy", gy), ("tb", tb)] + ([] if t2 else [("ta", ta)]))
@@ -346,6 +463,9 @@ def qlayer_conv2d_bwd_weight_workspace_size(desc: ConvDesc) -> int:
 
 def qlayer_conv2d_bwd_weight(desc, x, gy, ta, tb, dwa, dwb, dwc, dba=None, dbb=None, dbc=None,
                              workspace=None, stream=None):
+    if _call("qlayer_conv2d_bwd_weight", "qlayer_conv2d_bwd_weight_workspace_size", desc, _conv_plan(desc),
+             "xyyygggbbb", (x, gy, ta, tb, dwa, dwb, dwc, dba, dbb, dbc), workspace, stream):
+        return
     dev = _device(x, gy)
     _check_args(_conv_sizes(desc), desc.dtype, dev, act=[("x", x)], maps=[("gy", gy), ("ta", ta), ("tb", tb)],
                 w32=[("dwa", dwa), ("dwb", dwb), ("dwc", dwc)], vec32=[("dba", dba), ("dbb", dbb), ("dbc", dbc)])
@@ -376,6 +496,9 @@ def qlayer_linear_fwd_workspace_size(desc: LinearDesc) -> int:
 
 def qlayer_linear_fwd(desc, x, wa, wb, wc, ba=None, bb=None, bc=None, y=None, ta=None, tb=None,
                       workspace=None, stream=None):
+    if _call("qlayer_linear_fwd", "qlayer_linear_fwd_workspace_size", desc, _linear_plan(desc), "xwwwbbbyyy",
+             (x, wa, wb, wc, ba, bb, bc, y, ta, tb), workspace, stream):
+        return
     dev = _device(x, wa)
     _check_args(_linear_sizes(desc), desc.dtype, dev, act=[("x", x)], weights=[("wa", wa), ("wb", wb), ("wc", wc)],
                 maps=[("y", y), ("ta", ta), ("tb", tb)], vec32=[("ba", ba), ("bb", bb), ("bc", bc)])
@@ -396,6 +519,10 @@ def qlayer_conv2d_fwd_ex_workspace_size(desc: ConvDesc, epi=None) -> int:
 def qlayer_conv2d_fwd_ex(desc, x, wa, wb, wc, ba=None, bb=None, bc=None, y=None, ta=None, tb=None, epi=None,
                          workspace=None, stream=None):
     """qlayer_conv2d_fwd with a fused epilogue (an Epilogue, see epilogue())."""
+    extra = [t for _, t in getattr(epi, "tensors", ())]
+    if _call("qlayer_conv2d_fwd_ex", "qlayer_conv2d_fwd_ex_workspace_size", desc, _conv_plan(desc),
+             "xwwwbbbyyy", (x, wa, wb, wc, ba, bb, bc, y, ta, tb), workspace, stream, _epi_ref(epi), True, extra):
+        return
     dev = _device(x, wa)
     _check_args(_conv_sizes(desc), desc.dtype, dev, act=[("x", x)], weights=[("wa", wa), ("wb", wb), ("wc", wc)],
                 maps=[("y", y), ("ta", ta), ("tb", tb)],
@@ -413,6 +540,10 @@ def qlayer_linear_fwd_ex_workspace_size(desc: LinearDesc, epi=None) -> int:
 def qlayer_linear_fwd_ex(desc, x, wa, wb, wc, ba=None, bb=None, bc=None, y=None, ta=None, tb=None, epi=None,
                          workspace=None, stream=None):
     """qlayer_linear_fwd with a fused epilogue (an Epilogue, see epilogue())."""
+    extra = [t for _, t in getattr(epi, "tensors", ())]
+    if _call("qlayer_linear_fwd_ex", "qlayer_linear_fwd_ex_workspace_size", desc, _linear_plan(desc),
+             "xwwwbbbyyy", (x, wa, wb, wc, ba, bb, bc, y, ta, tb), workspace, stream, _epi_ref(epi), True, extra):
+        return
     dev = _device(x, wa)
     _check_args(_linear_sizes(desc), desc.dtype, dev, act=[("x", x)], weights=[("wa", wa), ("wb", wb), ("wc", wc)],
                 maps=[("y", y), ("ta", ta), ("tb", tb)],
@@ -429,6 +560,9 @@ def qlayer_linear_bwd_workspace_size(desc: LinearDesc) -> int:
 
 def qlayer_linear_bwd(desc, x, gy, ta, tb, wa, wb, wc, dx=None, dwa=None, dwb=None, dwc=None,
                       dba=None, dbb=None, dbc=None, workspace=None, stream=None):
+    if _call("qlayer_linear_bwd", "qlayer_linear_bwd_workspace_size", desc, _linear_plan(desc), "xyyywwwxgggbbb",
+             (x, gy, ta, tb, wa, wb, wc, dx, dwa, dwb, dwc, dba, dbb, dbc), workspace, stream):
+        return
     dev = _device(x, gy)
     _check_args(_linear_sizes(desc), desc.dtype, dev, act=[("x", x), ("dx", dx)],
                 weights=[("wa", wa), ("wb", wb), ("wc", wc)], maps=[("gy", gy), ("ta", ta), ("tb", tb)],
@@ -442,6 +576,10 @@ def qlayer_linear_bwd(desc, x, gy, ta, tb, wa, wb, wc, dx=None, dwa=None, dwb=No
 
 def _bwd_relu(name, sizes, wsize, desc, x, gy, y_out, ta, tb, wa, wb, wc, dx, dwa, dwb, dwc, dba, dbb, dbc,
               workspace, stream):
+    plan = _conv_plan(desc) if isinstance(desc, ConvDesc) else _linear_plan(desc)
+    if _call(name, name + "_workspace_size", desc, plan, "xyyyywwwxgggbbb",
+             (x, gy, y_out, ta, tb, wa, wb, wc, dx, dwa, dwb, dwc, dba, dbb, dbc), workspace, stream):
+        return
     dev = _device(x, gy)
     _check_args(sizes, desc.dtype, dev, act=[("x", x), ("dx", dx)], weights=[("wa", wa), ("wb", wb), ("wc", wc)],
                 maps=[("gy", gy), ("y_out", y_out), ("ta", ta), ("tb", tb)],

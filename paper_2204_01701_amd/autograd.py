@@ -77,6 +77,16 @@ def _same_device(x, *others):
             raise ValueError(f"every tensor must be on {x.device}; one is on {t.device}")
 
 
+def _cast_grads(gs, dtype):
+    """The float32 weight gradients (None: no such term) in the weights' dtype, in one launch."""
+    if dtype == torch.float32:
+        return gs
+    src = [g for g in gs if g is not None]
+    out = [torch.empty_like(g, dtype=dtype) for g in src]
+    torch._foreach_copy_(out, src)
+    return out + [None] * (len(gs) - len(out))
+
+
 def _terms(ws, nt):
     if any(w is None for w in ws[:nt]):
         raise ValueError(f"the neuron type has {nt} weighted terms")
@@ -141,7 +151,7 @@ class QuadConv2dFunction(torch.autograd.Function):
             qlayer_conv2d_bwd_relu(d, xn, gyn, relu_y, None if ctx.neuron == QL_NEURON_T2 else ta, tb, *wn, dxn,
                                    *dwn, *(db or [None, None, None]))
             dx = dxn.permute(0, 3, 1, 2) if need_x else None
-            dw = [g.permute(0, 3, 1, 2).to(ctx.wdtype) if g is not None else None for g in dwn]
+            dw = [g.permute(0, 3, 1, 2) if g is not None else None for g in _cast_grads(dwn, ctx.wdtype)]
             db = db or [None, None, None]
             return (dx, *dw, *db, None, None, None, None, None, None)
         if need_x:
@@ -158,7 +168,7 @@ class QuadConv2dFunction(torch.autograd.Function):
                   for i in range(3)] if need_b else None
             qlayer_conv2d_bwd_weight(d, xn, gyn, None if ctx.neuron == QL_NEURON_T2 else ta, tb, *dwn,
                                      *(db or [None, None, None]))
-            dw = [g.permute(0, 3, 1, 2).to(ctx.wdtype) if g is not None else None for g in dwn]
+            dw = [g.permute(0, 3, 1, 2) if g is not None else None for g in _cast_grads(dwn, ctx.wdtype)]
         dw = dw or [None, None, None]
         db = db or [None, None, None]
         return (dx, *dw, *db, None, None, None, None, None, None)
@@ -219,7 +229,7 @@ class QuadLinearFunction(torch.autograd.Function):
             qlayer_linear_bwd_relu(d, xc, gyc, relu_y, ta, tb, *wl, dx, *(dw or [None] * 3), *(db or [None] * 3))
         else:
             qlayer_linear_bwd(d, xc, gyc, ta, tb, *wl, dx, *(dw or [None] * 3), *(db or [None] * 3))
-        dw = [g.to(ctx.wdtype) if g is not None else None for g in dw] if dw is not None else [None, None, None]
+        dw = _cast_grads(dw, ctx.wdtype) if dw is not None else [None, None, None]
         db = db or [None, None, None]
         return (dx, *dw, *db, None, None, None)
 
