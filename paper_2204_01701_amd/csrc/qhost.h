@@ -57,6 +57,10 @@ constexpr double kPipeRound = 1.5;
 // the MFMAs of a 64-channel step), in the same units (measured on the same
 // layers: 1.2 reproduces where it is the fastest of the three kernels).
 constexpr double kFatStep = 1.2;
+// ... one of the 64 x 64 tile: over 30 bf16 shapes from 4 x 4 maps to the VGG-16
+// layers the geometric mean of the weight gradients was 22.0 us at 0.6 and 0.8, 21.2
+// at 0.7 (without this tile on the small ones 22.6; everywhere 23.0).
+constexpr double kSmallStep = 0.7;
 
 // Tuning override: QLAYER_<NAME>=<int> replaces a planner choice (for sweeps).
 inline int env_override(const char *name, int dflt) {
@@ -269,16 +273,11 @@ inline int narrow_waves(long long pixels) {
     return (int)(cdiv(waves, 4) * 4);
 }
 
-// Whether the 32-row tiles serve `rows` GEMM rows (channels) better than the
-// 64-row ones: in fp32, whose MFMAs bound the kernels, wherever they leave
-// fewer empty rows; in bf16, whose copies of the pixel operand do, only up to 32
-// rows.  us per call (64-row against 32-row; forward, input gradient): 32 -> 32
-// channels, 256 x 16 x 16 maps, 3 x 3, fp32 67, 81 against 39, 52, bf16 14.9, 22.6
-// against 12.3, 20.2; 96 -> 96, 128 x 14 x 14, fp32 165, 188 against 121, 172, bf16
-// 25.5, 46.4 against 29.4, 61.2.
-inline bool rows32(int rows, ql_dtype dt) {
-    return dt == QL_F32 ? cdiv(rows, 32) * 32 < cdiv(rows, 64) * 64 : rows <= 32;
-}
+// A K step of a tile configuration relative to the 64 x 128 tile's, for the
+// split model: in fp32 the MFMAs bound a step, in bf16 its copies and their
+// latency do, so a smaller tile saves less there.
+constexpr double kFwdStepBf16[kFwdCfgs] = {1.0, 1.0, 1.0, 1.0, 1.0, 1.0, 1.0, 0.85};
+constexpr double kFwdStepF32[kFwdCfgs] = {1.0, 1.0, 1.0, 1.0, 1.0, 1.0, 1.0, 0.55};
 
 struct FwdPlan {
     int cfg;  // pipelined: index into kFwd*; generic: 0: 128 x 128, 1: 64 x 128
@@ -333,12 +332,14 @@ inline FwdPlan plan_fwd(const Geom &g) {
         p.ws_bytes = p.xpad_bytes + 3 * p.wpad_bytes;
         return p;
     }
+    const int cfg_env = env_override("QLAYER_FWD_CFG", -1), min_stages = env_override("QLAYER_FWD_MINSTAGES", 4);
     if (p.veck) {
-        // 8-wave 128 x 256 tiles where there are enough of them to fill the GPU several times
+        // 8-wave 128 x 256 tiles where there are enough of them to fill the GPU several times,
+        // else the 64 x 128 or the 32 x 128 tile by the split model (below)
         const bool big = g.O >= 128 && (long long)cdiv(g.O, 128) * cdiv(M, 256) >= 4 * kNumCUs;
         // (the 8-wave tile with four stages where the filter has several taps: measured 3 % faster on
         // the N=64, 256-channel 56 x 56 layer, and no faster on the dense layer)
-        p.cfg = env_override("QLAYER_FWD_CFG", big ? (g.KH * g.KW > 1 ? 6 : 4) : rows32(g.O, g.dt) ? 7 : 3);
+        p.cfg = cfg_env >= 0 ? cfg_env : (big ? (g.KH * g.KW > 1 ? 6 : 4) : 3);
         if (p.cfg < 0 || p.cfg >= kFwdCfgs || g.ne != NEURON_QUADRA) p.cfg = 3;  // (the other types: tile 3 only)
         p.BR = kFwdBR[p.cfg];
         p.BCOL = kFwdBCOL[p.cfg];
@@ -368,8 +369,32 @@ inline FwdPlan plan_fwd(const Geom &g) {
     p.pm = p.ca && pm_want;
     int kst = p.stages_total;
     if (p.pm) kst = pm_max_taps(g, p.BCOL, M) * (p.Cp / p.KE);
-    plan_splits(p.row_tiles * p.col_tiles, kst, env_override("QLAYER_FWD_MINSTAGES", 4), (size_t)3 * M * g.O * 4,
-                p.slots, p.splits, p.sps, step_scale(g), kMaxSplitBytes, 1, kSharedRoundFwd);
+    auto fill = [&](int cfg) {
+        p.cfg = cfg;
+        p.BR = kFwdBR[cfg];
+        p.BCOL = kFwdBCOL[cfg];
+        p.slots = kFwdSlots[cfg];
+        p.row_tiles = cdiv(g.O, p.BR);
+        p.col_tiles = cdiv(M, p.BCOL);
+        p.stat_parts = p.col_tiles;
+        return plan_splits(p.row_tiles * p.col_tiles, kst, min_stages, (size_t)3 * M * g.O * 4, p.slots, p.splits,
+                           p.sps, step_scale(g), kMaxSplitBytes, 1, kSharedRoundFwd,
+                           (g.dt == QL_F32 ? kFwdStepF32 : kFwdStepBf16)[cfg]);
+    };
+    // The 32-row tile where it leaves fewer empty rows or, on small outputs, fewer
+    // idle CUs.  us per call (64-row against 32-row): 32 -> 32 channels, 256 x 16 x
+    // 16 maps, 3 x 3, fp32 67 against 39, bf16 14.9 against 12.3; 96 -> 96, 128 x 14 x 14,
+    // fp32 165 against 121, bf16 25.5 against 29.4; 64 -> 64, 256 x 8 x 8, bf16 14.1
+    // against 12.5.  (BCOL is the same, so kst holds for both.)
+    if (p.veck && p.cfg == 3 && g.ne == NEURON_QUADRA && cfg_env < 0) {
+        const double t7 = fill(7), t3 = fill(3);
+        if (t7 < t3) fill(7);
+    } else if (p.veck) {
+        fill(p.cfg);
+    } else {
+        plan_splits(p.row_tiles * p.col_tiles, kst, min_stages, (size_t)3 * M * g.O * 4, p.slots, p.splits, p.sps,
+                    step_scale(g), kMaxSplitBytes, 1, kSharedRoundFwd);
+    }
     // Where these tiles would split K over workgroups (small outputs: the 4 x 4
     // and 2 x 2 maps of a CIFAR VGG-16), the in-workgroup K split of
     // qconv_fwd_ksplit.h instead: tiles small enough to fill the GPU, no
@@ -377,14 +402,25 @@ inline FwdPlan plan_fwd(const Geom &g) {
     // By default only where each wave's K range is at most 768 in bf16 (on
     // longer K the tiled kernel's split-K measured faster: the 512-channel
     // 4 x 4 layers, 1152 per wave, 52 against 47 us per call), 1152 in fp32
-    // (the longest measured: the same layers, 215 against 228 us).
+    // (the longest measured: the same layers, 215 against 228 us).  In bf16 up to
+    // 1024 where there are at most 80 of the 64 x 128 tiles, whether or not they
+    // would split (448 -> 256 channels, 3 x 9 x 9 maps, 3 x 3: 24.1 us tiled, 14.3 here;
+    // a dense layer of 1024 rows, 512 -> 512: 12.7, 9.5; 32 -> 64, 4 x 20 x 20: 9.7, 6.4).
+    // In fp32, whose tiles' MFMAs outweigh the split's traffic, above 320 per wave
+    // only with at least 128 workgroups of its own (448 -> 256, 3 x 9 x 9, 64 of
+    // them: 55.8 us here, 39.4 in split 32-row tiles).
     const int ks_env = env_override("QLAYER_FWD_KSPLIT", -1);
     const int ks_k = (pm_want ? pm_max_taps(g, 64, M) : g.KH * g.KW) * p.Cp;
-    const int ks_kmax = g.dt == QL_BF16 ? 768 : 1152;
+    auto ks_default = [&]() {
+        if (p.cfg != 3 && p.cfg != 7) return false;
+        if (g.dt == QL_F32)
+            return p.splits > 1 && ks_k <= 4 * 1152 && (ks_k <= 4 * 320 || cdiv(g.O, 16) * cdiv(M, 64) >= 128);
+        return (p.splits > 1 && ks_k <= 4 * 768) || (cfg_env < 0 && cdiv(g.O, 64) * cdiv(M, 128) <= 80 && ks_k <= 4 * 1024);
+    };
     if (p.veck && g.ne == NEURON_QUADRA && g.O % 4 == 0 && p.Cp % p.KE == 0 && g.KH * g.KW <= 32 &&
         (long long)g.N * g.H * g.W * p.Cp * (long long)g.esize() < (1LL << 31) &&
         (long long)g.O * K * (long long)g.esize() < (1LL << 31) &&
-        (ks_env >= 0 ? ks_env != 0 : p.splits > 1 && ks_k <= 4 * ks_kmax)) {
+        (ks_env >= 0 ? ks_env != 0 : ks_default())) {
         // the larger tile where its count fills the GPU, else the smaller one (or as forced)
         constexpr int kKsRB[3] = {2, 1, 2}, kKsCB[3] = {4, 4, 2};
         int t = cdiv(g.O, 32) * cdiv(M, 64) >= kNumCUs ? 0 : 1;
@@ -420,6 +456,10 @@ inline FwdPlan plan_fwd(const Geom &g) {
 constexpr int kBdCfgs = 7;
 constexpr int kBdBR[kBdCfgs] = {128, 64, 128, 128, 256, 64, 32};
 constexpr int kBdBCOL[kBdCfgs] = {128, 128, 64, 128, 256, 128, 128};  // 4: the wide kernel (8 waves, 16-channel K steps)
+
+// K steps relative to the 64 x 128 tile's (see kFwdStepBf16).
+constexpr double kBdStepBf16[kBdCfgs] = {1.3, 1.0, 1.0, 1.3, 1.0, 1.0, 0.9};
+constexpr double kBdStepF32[kBdCfgs] = {2.0, 1.0, 1.0, 2.0, 1.0, 1.0, 0.55};
 
 struct BwdDataPlan {
     int cfg;  // pipelined: index into kBd*; generic: 0: 128 x 128, 1: 64 x 128
@@ -505,19 +545,16 @@ inline BwdDataPlan plan_bwd_data(const Geom &g) {
     p.natw = p.veck && !p.pad && g.dt == QL_BF16 && g.C % 8 == 0;
     // the wide kernel: bf16, natural weight tiles, stride 1, 16-channel K steps within one tap
     const bool wide_ok = p.natw && p.s1 && g.O % 16 == 0 && g.KH * g.KW <= 32;
+    // (measured: faster where its 256 x 256 tiles fill the GPU at least twice, as on
+    // the dense layer and the N=64, 256-channel 56 x 56 layer; on the small maps of
+    // VGG-16 the 4-wave tiles win, the wide kernel's 8 waves run their product
+    // arithmetic in step)
+    const bool wide = wide_ok && g.C >= 256 && (long long)cdiv(g.C, 256) * cdiv(M, 256) >= 2 * kNumCUs;
+    const int cfg_env = env_override("QLAYER_BWD_DATA_CFG", -1);
     if (p.veck) {
-        int dflt = rows32(g.C, g.dt) ? 6 : 5;
-        if (g.C > 64 && dflt != 6) dflt = M >= 1024 ? 3 : 2;
-        // (measured: faster where its 256 x 256 tiles fill the GPU at least twice, as on
-        // the dense layer and the N=64, 256-channel 56 x 56 layer; on the small maps of
-        // VGG-16 the 4-wave tiles win, the wide kernel's 8 waves run their product
-        // arithmetic in step)
-        if (wide_ok && g.C >= 256 && (long long)cdiv(g.C, 256) * cdiv(M, 256) >= 2 * kNumCUs) dflt = 4;
-        p.cfg = env_override("QLAYER_BWD_DATA_CFG", dflt);
-        if (p.cfg < 0 || p.cfg >= kBdCfgs || (p.cfg == 4 && !wide_ok)) p.cfg = 0;
+        p.cfg = cfg_env >= 0 ? cfg_env : (wide ? 4 : (g.C > 64 ? 3 : 5));
+        if (p.cfg >= kBdCfgs || (p.cfg == 4 && !wide_ok)) p.cfg = 0;
         if (g.ne != NEURON_QUADRA) p.cfg = g.C > 64 ? 3 : 5;  // (the other types: tiles 3 and 5 only)
-        p.BR = kBdBR[p.cfg];
-        p.BCOL = kBdBCOL[p.cfg];
     } else {
         p.cfg = g.C <= 64 || g.ne != NEURON_QUADRA ? 1 : 0;
         p.BR = p.cfg == 0 ? 128 : 64;
@@ -525,22 +562,53 @@ inline BwdDataPlan plan_bwd_data(const Geom &g) {
     }
     p.KE = p.cfg == 4 && p.veck ? 16 : 64 / (int)g.esize();
     p.slots = 1;
-    p.row_tiles = cdiv(g.C, p.BR);
     // (register-staged kernel at stride > 1: every pixel meets every tap)
     const bool phased = p.veck && phases;
-    p.col_tiles = phased ? g.SH * g.SW * cdiv(phase_pixels, p.BCOL) : cdiv(M, p.BCOL);
     p.stages_total = cdiv(p.veck ? K : g.KH * g.KW * p.Op, p.KE);
     // Channel-aligned K steps (each within one tap) in the 4-wave kernels, and
     // with them, on small padded maps, the position-major order that skips
     // the taps whose output pixel lies outside the map for every position of
     // a pixel tile (the proposed neuron: 5 of 9 taps on a 2 x 2 map).
-    p.ca = p.natw && p.cfg != 4 && g.O % p.KE == 0 && g.KH * g.KW <= 32 &&
-           env_override("QLAYER_BWD_DATA_CA", 1) != 0;
-    p.pm = p.ca && p.s1 && g.ne == NEURON_QUADRA && pm_default(g, env_override("QLAYER_BWD_DATA_POSMAJ", -1));
-    int kst = p.stages_total;
-    if (p.pm) kst = bd_pm_max_taps(g, p.BCOL, M) * (g.O / p.KE);
-    plan_splits(p.row_tiles * p.col_tiles, kst, env_override("QLAYER_BWD_DATA_MINSTAGES", 4),
-                (size_t)M * g.C * 4, p.slots, p.splits, p.sps, step_scale(g));
+    const bool ca_ok = p.natw && p.cfg != 4 && g.O % p.KE == 0 && g.KH * g.KW <= 32;
+    const int ca_env = env_override("QLAYER_BWD_DATA_CA", -1);
+    p.pm = ca_ok && ca_env != 0 && p.s1 && g.ne == NEURON_QUADRA &&
+           pm_default(g, env_override("QLAYER_BWD_DATA_POSMAJ", -1));
+    auto fill = [&](int cfg) {
+        p.cfg = cfg;
+        if (p.veck) {
+            p.BR = kBdBR[cfg];
+            p.BCOL = kBdBCOL[cfg];
+        }
+        p.row_tiles = cdiv(g.C, p.BR);
+        p.col_tiles = phased ? g.SH * g.SW * cdiv(phase_pixels, p.BCOL) : cdiv(M, p.BCOL);
+        int kst = p.stages_total;
+        if (p.pm) kst = bd_pm_max_taps(g, p.BCOL, M) * (g.O / p.KE);
+        return plan_splits(p.row_tiles * p.col_tiles, kst, env_override("QLAYER_BWD_DATA_MINSTAGES", 4),
+                           (size_t)M * g.C * 4, p.slots, p.splits, p.sps, step_scale(g), kMaxSplitBytes, 1,
+                           kSharedRound, p.veck ? (g.dt == QL_F32 ? kBdStepF32 : kBdStepBf16)[cfg] : 1.0);
+    };
+    // The tile by the split model: smaller tiles where they leave fewer empty rows
+    // or idle CUs.  us per call: 128 -> 128 channels, 32 x 14 x 14 maps, 1 x 1, bf16 8.8
+    // in 128 x 128 tiles, 7.0 in 128 x 64, fp32 26.0, 16.2 in 32 x 128; 272 -> 16, 8 x 14 x
+    // 14, 3 x 3, bf16 10.0, 7.0 in 32 x 128; 32 -> 32, 256 x 16 x 16, 3 x 3, fp32 81 in 64 x
+    // 128, 52 in 32 x 128, bf16 22.6, 20.2.
+    double best = fill(p.cfg);
+    if (p.veck && p.cfg != 4 && g.ne == NEURON_QUADRA && cfg_env < 0) {
+        int pick = p.cfg;
+        for (int cfg : {3, 2, 5, 6}) {
+            if (g.C <= 64 && cfg < 5) continue;  // (128-row tiles: half empty)
+            const double t = fill(cfg);
+            if (t < best) {
+                best = t;
+                pick = cfg;
+            }
+        }
+        fill(pick);
+    }
+    // The 64- and 32-row tiles keep the per-lane addresses, which interleave with
+    // the MFMAs (64 -> 64 channels, 3 x 3, bf16: 128 x 32 x 32 maps 65.7 against 70.4 us
+    // with channel-aligned steps, 256 x 8 x 8 maps 16.3 against 18.3).
+    p.ca = ca_ok && ca_env != 0 && (p.pm || ca_env == 1 || (p.cfg != 5 && p.cfg != 6));
     // Block order of the split grid: tile-major (each XCD's blocks share pixel
     // tiles: their rows of G, T_a, T_b once, all of the weights) where G, T_a,
     // T_b are at least the weight bytes (M >= C KH KW), split-major otherwise
@@ -663,7 +731,7 @@ inline BwdWeightPlan plan_bwd_weight(const Geom &g, size_t max_split_bytes = kMa
         p.row_tiles = cdiv(KP, p.BKP);
         p.col_tiles = cdiv(g.O, p.BO);
         return plan_splits(p.row_tiles * p.col_tiles, p.stages_total, min_stages, bytes_per_split, p.slots, p.splits,
-                           p.sps, step_scale(g), max_split_bytes, kBwPipes[cfg], kSharedRound, cfg == 5 ? kFatStep : 1.0);
+                           p.sps, step_scale(g), max_split_bytes, kBwPipes[cfg], kSharedRound, cfg == 5 ? kFatStep : (cfg == 2 ? kSmallStep : 1.0));
     };
     if (p.pipe && g.ne == NEURON_QUADRA) {
         // the 16 x 16 x 32 kernel: four waves on a 64-channel tile, two such pipelines per
@@ -675,8 +743,13 @@ inline BwdWeightPlan plan_bwd_weight(const Geom &g, size_t max_split_bytes = kMa
             // the 128-channel tile only where it has no empty columns
             const double t3 = fill(3), t4 = fill(4);  // (declarators initialise in order)
             const double t5 = g.O % 128 == 0 ? fill(5) : 1e30;
-            const int best = t5 < t3 && t5 < t4 ? 5 : (t4 < t3 ? 4 : 3);
-            if (best != 5) fill(best);
+            int best = t5 < t3 && t5 < t4 ? 5 : (t4 < t3 ? 4 : 3);
+            // the 64 x 64 tile of the 32 x 32 kernel on small outputs, where its ramp is
+            // the shortest (32 -> 64 channels, 4 x 20 x 20 maps, 3 x 3: 11.1 against 13.9 us;
+            // 256 -> 256, 2 x 4 x 4: 6.0 against 7.8)
+            const double t2 = g.dt == QL_BF16 ? fill(2) : 1e30;
+            if (t2 < std::min(t3, std::min(t4, t5))) best = 2;
+            fill(best);
         }
     } else {
         fill(0);  // the other neuron types and fp32: the 128 x 64 tile

@@ -5,6 +5,7 @@ load paths.  Normwise relative error limits: fp32 forward 1e-5, gradients
 """
 import numpy as np
 import pytest
+import torch
 
 import oracle
 import synth
@@ -12,6 +13,7 @@ import synth
 pytestmark = pytest.mark.gpu
 
 import qlh  # noqa: E402
+import paper_2204_01701_amd as ql  # noqa: E402
 
 # (N, C, H, W, O, KH, KW, stride, pad)
 CONV_SHAPES = [
@@ -175,3 +177,29 @@ def test_conv_32_row_tiles(shape, bf16, monkeypatch):
         for k, want in (("y", y), ("ta", ta), ("tb", tb), ("dx", ref["dx"])):
             e = qlh.relerr(got[k], want)
             assert e <= qlh.tol(bf16, k == "dx"), f"{k}: normwise relative error {e:.3e}"
+
+
+@pytest.mark.parametrize("cfg", [3, 7], ids=["64-row", "32-row"])
+@pytest.mark.parametrize("bf16", [False, True], ids=["fp32", "bf16"])
+def test_small_tiles_gather_the_epilogue_sums(cfg, bf16, monkeypatch):
+    """The batch-normalization sums of the 64- and 32-row forward tiles (forced:
+    outputs this small take the small-output forward by default)."""
+    N, C, H, W, O = 3, 32, 9, 7, 96
+    print(f"epilogue sums of tile {cfg} bf16={bf16}", flush=True)
+    monkeypatch.setenv("QLAYER_FWD_CFG", str(cfg))
+    monkeypatch.setenv("QLAYER_FWD_KSPLIT", "0")
+    monkeypatch.setenv("QLAYER_FWD_MINSTAGES", "1000")  # no split-K: the staged epilogue
+    inp = synth.random_conv_case([62, cfg], N, C, H, W, O, 3, 3, 1, 1, bf16=bf16)
+    d = ql.conv_desc(N, C, H, W, O, 3, 3, 1, 1, qlh.qdtype(bf16))
+    y = torch.empty((N, H, W, O), device=qlh.DEV, dtype=qlh.tdtype(bf16))
+    s1, s2 = (torch.empty(O, device=qlh.DEV) for _ in range(2))
+    ql.qlayer_conv2d_fwd_ex(d, qlh.nchw_to_dev(inp["x"], bf16), *(qlh.oihw_to_dev(inp[k], bf16) for k in ("wa", "wb", "wc")),
+                            *(qlh.vec_to_dev(inp[k]) for k in ("ba", "bb", "bc")), y,
+                            epi=ql.epilogue(relu=True, stat_sum=s1, stat_sumsq=s2), ta=None, tb=None)
+    torch.cuda.synchronize()
+    ref, _, _ = oracle.conv2d_fwd(inp["x"], inp["wa"], inp["wb"], inp["wc"], inp["ba"], inp["bb"], inp["bc"], 1, 1)
+    assert qlh.relerr(qlh.nhwc_to_np(y), np.maximum(ref, 0)) <= qlh.tol(bf16, False)
+    v = y.double().reshape(-1, O)
+    # fp32 sums of 189 rows: at most 189 2^-24 times the sum of magnitudes
+    assert torch.all((s1.double() - v.sum(0)).abs() <= 3e-5 * v.abs().sum(0) + 1e-30)
+    assert torch.all((s2.double() - (v * v).sum(0)).abs() <= 3e-5 * (v * v).sum(0) + 1e-30)
