@@ -41,6 +41,7 @@ struct DwArgs {
     // column kernels: M counts columns (image, row group of R rows, column);
     // ng row groups per image, iwid columns per row
     int ng, iwid;
+    int seg;  // row kernels: rows per segment
     const void *zero;  // 16 zero bytes: the source of out-of-range taps (generic kernels)
     int xbytes, pbytes;  // 3 x 3 kernels: bytes of X (and dX) and of an output-side map (< 2^31)
     EpiArgs epi;         // forward epilogue of Y (qargs.h)
@@ -514,6 +515,21 @@ __device__ __forceinline__ void dw_stage_bias(const DwArgs &a, int c0, int CB, f
 // into registers (27 V of them), which would bound the occupancy.
 #define QL_DW_CHUNK_FENCE() asm volatile("" ::: "memory")
 
+// The sums are complete here: without this the compiler sinks each column's
+// arithmetic into the branch that stores it, with all filter rows held for it.
+template <int A, int B>
+__device__ __forceinline__ void dw_pin(float (&v)[A][B]) {
+#pragma unroll
+    for (int i = 0; i < A; ++i)
+#pragma unroll
+        for (int j = 0; j < B; ++j) asm volatile("" : "+v"(v[i][j]));
+}
+template <int A, int B, int C>
+__device__ __forceinline__ void dw_pin(float (&v)[A][B][C]) {
+#pragma unroll
+    for (int i = 0; i < A; ++i) dw_pin(v[i]);
+}
+
 // One column of the forward: its position and the raw input rows it sees.
 template <typename T, int V, bool VEC, int K, int S, int R>
 struct DwFwdCol {
@@ -548,8 +564,10 @@ struct DwFwdCol {
 // Forward, K x K at stride S, by columns: a thread takes V channels of R
 // consecutive output rows of one output column, (R - 1) S + K input rows of
 // K columns loaded once, and each filter value read from LDS serves the R
-// rows.  PF: the next column's loads are issued before the current column's
-// arithmetic (two register buffers).  a.M counts the columns N x ceil(HO / R) x WO.
+// rows.  153 registers in bf16, three waves per SIMD, whose loads overlap the
+// others' arithmetic (a second register buffer for the next column's loads cost
+// a wave: 128 x 32 x 32 maps of 32 channels 16.1 us against 14.3; without dw_pin
+// it ran at one wave per SIMD, 20.4 us).  a.M counts the columns N x ceil(HO / R) x WO.
 template <typename T, int OM, int V, bool VEC, int K, int S, int R>
 __device__ __forceinline__ void dw_fwd_col_compute(const DwArgs &a, const DwFwdCol<T, V, VEC, K, S, R> &b,
                                                    const float *wl, const float *bl, int CB, int cg, int c,
@@ -590,6 +608,7 @@ __device__ __forceinline__ void dw_fwd_col_compute(const DwArgs &a, const DwFwdC
             }
         }
     }
+    dw_pin(acc);
 #pragma unroll
     for (int rr = 0; rr < R; ++rr) {
         if (b.oh0 + rr >= a.HO) break;
@@ -619,7 +638,7 @@ __device__ __forceinline__ void dw_fwd_col_compute(const DwArgs &a, const DwFwdC
     }
 }
 
-template <typename T, int OM, int V, bool VEC, int K, int S, int R, bool PF>
+template <typename T, int OM, int V, bool VEC, int K, int S, int R>
 __global__ __launch_bounds__(kThreads)
 void qconv_dw_fwd_col_kernel(const DwArgs a) {
     constexpr int NTM = om_terms(OM), TAPS = K * K;
@@ -637,29 +656,176 @@ void qconv_dw_fwd_col_kernel(const DwArgs a) {
     if (cleft <= 0 || ch_begin >= ch_end) return;
     const T *__restrict__ x = static_cast<const T *>(a.x);
     const __amdgpu_buffer_rsrc_t xrs = dw_rsrc(a.x, a.xbytes);
-    if constexpr (!PF) {
-        for (int chunk = ch_begin; chunk < ch_end; ++chunk) {
-            QL_DW_CHUNK_FENCE();
-            DwFwdCol<T, V, VEC, K, S, R> b;
-            b.fetch(a, xrs, x, chunk * PL + pl, c, cleft);
-            dw_fwd_col_compute<T, OM>(a, b, wl, bl, CB, cg, c, cleft);
-        }
-        return;
+    for (int chunk = ch_begin; chunk < ch_end; ++chunk) {
+        QL_DW_CHUNK_FENCE();
+        DwFwdCol<T, V, VEC, K, S, R> b;
+        b.fetch(a, xrs, x, chunk * PL + pl, c, cleft);
+        dw_fwd_col_compute<T, OM>(a, b, wl, bl, CB, cg, c, cleft);
     }
-    DwFwdCol<T, V, VEC, K, S, R> b0, b1;
-    int chunk = ch_begin;
-    b0.fetch(a, xrs, x, chunk * PL + pl, c, cleft);
-    // the next fetch is unconditional (clamped, not stored past the end): no
-    // branch between a fetch and its use
-    while (true) {
-        QL_DW_CHUNK_FENCE();
-        b1.fetch(a, xrs, x, (chunk + 1) * PL + pl, c, cleft);
-        dw_fwd_col_compute<T, OM>(a, b0, wl, bl, CB, cg, c, cleft);
-        if (++chunk >= ch_end) break;
-        QL_DW_CHUNK_FENCE();
-        b0.fetch(a, xrs, x, (chunk + 1) * PL + pl, c, cleft);
-        dw_fwd_col_compute<T, OM>(a, b1, wl, bl, CB, cg, c, cleft);
-        if (++chunk >= ch_end) break;
+}
+
+// ---------------------------------------------------------------------------
+// Row kernels (3 x 3, C a multiple of 4): a thread takes 4 channels of WC
+// adjacent columns and walks down a segment of rows, so that each row of the
+// input is loaded once per segment ((WC - 1) S + 3 columns of it, 1.5 loads per
+// output at S 1) and PD rows are on their way while one is computed.  The column
+// kernels load a window per output column, 4.5 loads per output: at two waves
+// per SIMD only about 16 KB of distinct bytes per CU were in flight, which held
+// them at 2.5 TB/s whatever the arithmetic (64 x 56 x 56 maps of 256 channels, bf16:
+// forward 157 us, 115 here; input gradient 171 and 114).  A pixel's channels go to up to 64
+// lanes (512 bytes in bf16), so loads and stores cover whole cache lines.
+// a.M counts the items N x ns x ncg (a.ng = ns row segments of a.seg rows,
+// a.iwid = ncg column groups of WC columns).
+// ---------------------------------------------------------------------------
+// Filters (and biases) of a row kernel in LDS: per group of 4 channels the
+// NTM x TAPS rows of 4 floats, so that a lane reads them at fixed offsets from
+// one base (consecutive lanes 27 or fewer 16-byte slots apart).
+template <typename T, int NTM, int TAPS>
+__device__ __forceinline__ void dw_stage_rows(const DwArgs &a, int c0, int CB, float *wl) {
+    for (int i = threadIdx.x; i < NTM * TAPS * CB; i += kThreads) {
+        const int t = i / (TAPS * CB), rem = i - t * TAPS * CB;
+        const int cl = rem / TAPS, tap = rem - cl * TAPS;  // consecutive lanes on consecutive weights
+        const int c = c0 + cl;
+        wl[((cl >> 2) * (NTM * TAPS) + t * TAPS + tap) * 4 + (cl & 3)] =
+            c < a.C ? to_f32<T>(static_cast<const T *>(a.w[t])[(size_t)c * TAPS + tap]) : 0.0f;
+    }
+}
+template <int NTM>
+__device__ __forceinline__ void dw_stage_rows_bias(const DwArgs &a, int c0, int CB, float *bl) {
+    for (int i = threadIdx.x; i < NTM * CB; i += kThreads) {
+        const int t = i / CB, cl = i - t * CB, c = c0 + cl;
+        bl[((cl >> 2) * NTM + t) * 4 + (cl & 3)] = (a.bias[t] && c < a.C) ? a.bias[t][c] : 0.0f;
+    }
+}
+// The lane's base in those tables, made anew for each row: without the opaque
+// value the compiler reads all 27 filter rows once, ahead of the row loop, into
+// 108 registers (one wave per SIMD, or spills).
+__device__ __forceinline__ const float *dw_row_base(const float *tab, int floats) {
+    asm volatile("" : "+v"(floats));
+    return tab + floats;
+}
+
+// Item `it` of a row kernel: image, first row and first column.
+template <int WC>
+__device__ __forceinline__ void dw_row_item(const DwArgs &a, int it, int &n, int &row0, int &col0) {
+    n = (int)fdiv((uint32_t)it, a.fd_item);
+    const int rem = it - n * a.ng * a.iwid;
+    const int g = (int)fdiv((uint32_t)rem, a.fd_iw);
+    row0 = g * a.seg;
+    col0 = (rem - g * a.iwid) * WC;
+}
+
+// Forward: the 3 rows of the current output row's window and the PD S rows
+// behind them are in registers, moved up after each output row.
+template <typename T, int OM, int S, int WC, int PD>
+__global__ __launch_bounds__(kThreads, 2)
+void qconv_dw_fwd_rows_kernel(const DwArgs a) {
+    constexpr int NTM = om_terms(OM), V = 4, K = 3, TAPS = 9;
+    constexpr int NC = (WC - 1) * S + K;   // input columns
+    constexpr int RN = K + PD * S;         // ring rows
+    extern __shared__ float wl[];  // [NTM][TAPS][CB], then the biases [NTM][CB]
+    const int CB = a.lanes * V;
+    const int cg = threadIdx.x & (a.lanes - 1), pl = threadIdx.x >> a.lsh, PL = kThreads >> a.lsh;
+    int tile, ch_begin, ch_end;
+    dw_chunk_range(a, PL, tile, ch_begin, ch_end);
+    const int c0 = tile * CB;
+    float *bl = wl + NTM * TAPS * CB;
+    dw_stage_rows<T, NTM, TAPS>(a, c0, CB, wl);
+    dw_stage_rows_bias<NTM>(a, c0, CB, bl);
+    __syncthreads();
+    const int c = c0 + V * cg, cleft = a.C - c;
+    if (cleft <= 0) return;
+    const T *__restrict__ x = static_cast<const T *>(a.x);
+    const __amdgpu_buffer_rsrc_t xrs = dw_rsrc(a.x, a.xbytes);
+    for (int chunk = ch_begin; chunk < ch_end; ++chunk) {
+        const int item = chunk * PL + pl;
+        int n, oh0, ow0;
+        dw_row_item<WC>(a, min(item, a.M - 1), n, oh0, ow0);
+        const int oh1 = item < a.M ? min(oh0 + a.seg, a.HO) : 0;  // (past the end: computed, not stored)
+        const int ih0 = oh0 * S - a.PH, iw0 = ow0 * S - a.PW;
+        const int base = ((n * a.H + ih0) * a.W + iw0) * a.C + c, rowc = a.W * a.C;
+        DwRaw<T, V, true> xr[RN][NC];
+        auto load = [&](int row, DwRaw<T, V, true> (&dst)[NC]) {  // input row ih0 + row
+            const bool okr = (unsigned)(ih0 + row) < (unsigned)a.H;
+#pragma unroll
+            for (int j = 0; j < NC; ++j)
+                dst[j].load(xrs, x, base + row * rowc + j * a.C, V, okr & ((unsigned)(iw0 + j) < (unsigned)a.W));
+        };
+#pragma unroll
+        for (int i = 0; i < RN - S; ++i) load(i, xr[i]);
+        // (one body with the rows moved up, 4 to 6 % of its instructions: unrolled over
+        // a rotating ring, the compiler kept the rows' fp32 values across steps, 300
+        // registers)
+#pragma unroll 1
+        for (int st = 0; st < a.seg; ++st) {  // output row oh0 + st
+            {
+                QL_DW_CHUNK_FENCE();
+#pragma unroll
+                for (int i = 0; i < S; ++i) load(st * S + RN - S + i, xr[RN - S + i]);
+                const float *wr = dw_row_base(wl, cg * (NTM * TAPS * V)), *br = dw_row_base(bl, cg * (NTM * V));
+                float acc[WC][NTM][V];
+#pragma unroll
+                for (int t = 0; t < NTM; ++t) {
+                    float bv[V];
+                    dw_lds_row<V>(br, t * V, bv);
+#pragma unroll
+                    for (int p = 0; p < WC; ++p)
+#pragma unroll
+                        for (int k = 0; k < V; ++k) acc[p][t][k] = bv[k];
+                }
+#pragma unroll
+                for (int rr = 0; rr < K; ++rr) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    float xs[NC][V];
+#pragma unroll
+                    for (int j = 0; j < NC; ++j)
+#pragma unroll
+                        for (int k = 0; k < V; ++k) {
+                            const float v = xr[rr][j].get(k);
+                            xs[j][k] = OM == OM_SQIN ? to_f32<T>(from_f32<T>(v * v)) : v;  // T2: X o X in T
+                        }
+#pragma unroll
+                    for (int q = 0; q < K; ++q)
+#pragma unroll
+                        for (int t = 0; t < NTM; ++t) {
+                            float wv[V];
+                            dw_lds_row<V>(wr, (t * TAPS + rr * K + q) * V, wv);
+#pragma unroll
+                            for (int p = 0; p < WC; ++p)
+#pragma unroll
+                                for (int k = 0; k < V; ++k) acc[p][t][k] += wv[k] * xs[p * S + q][k];
+                        }
+                }
+                dw_pin(acc);
+                const int oh = oh0 + st;
+#pragma unroll
+                for (int p = 0; p < WC; ++p) {
+                    if (oh >= oh1 || ow0 + p >= a.WO) continue;
+                    const size_t off = ((size_t)(n * a.HO + oh) * a.WO + ow0 + p) * a.C + c;
+                    float yv[V], xs[V] = {0.0f, 0.0f, 0.0f, 0.0f};
+                    if (OM == OM_PAIR && a.neuron == NEURON_T4I)
+                        dw_ldv<T, V, true>(x + off, cleft, xs);  // the same pixel of X (the map keeps its size)
+#pragma unroll
+                    for (int k = 0; k < V; ++k) {
+                        const float fa = acc[p][0][k];
+                        if constexpr (OM == OM_QUADRA) yv[k] = fa * acc[p][1][k] + acc[p][2][k];
+                        else if constexpr (OM == OM_PAIR) yv[k] = fa * acc[p][1][k] + xs[k];
+                        else if constexpr (OM == OM_SQUARE) yv[k] = fa * fa;
+                        else yv[k] = fa;
+                        yv[k] = epi_apply(a.epi, c + k, yv[k]);
+                    }
+                    if (a.y) dw_stv<T, V, true>(static_cast<T *>(a.y) + off, cleft, yv);
+                    if (a.yta) dw_stv<T, V, true>(static_cast<T *>(a.yta) + off, cleft, acc[p][0]);
+                    if constexpr (NTM >= 2) {
+                        if (a.ytb) dw_stv<T, V, true>(static_cast<T *>(a.ytb) + off, cleft, acc[p][1]);
+                    }
+                }
+            }
+#pragma unroll
+            for (int i = 0; i + S < RN; ++i)
+#pragma unroll
+                for (int j = 0; j < NC; ++j) xr[i][j] = xr[i + S][j];
+        }
     }
 }
 
@@ -753,6 +919,7 @@ __device__ __forceinline__ void dw_bd_col_compute(const DwArgs &a, const DwBdCol
             }
         }
     }
+    dw_pin(acc);
 #pragma unroll
     for (int rr = 0; rr < R; ++rr) {
         if (b.h0 + rr >= a.H) break;
@@ -764,9 +931,10 @@ __device__ __forceinline__ void dw_bd_col_compute(const DwArgs &a, const DwBdCol
 // R consecutive input rows of one input column; input row h takes tap r from
 // output row h + p - r, so the column needs R + K - 1 output rows, whose
 // operands are formed once per row and applied to every input row they feed.
-// PF: the next column's loads are issued before the current column's
-// arithmetic.  a.M counts the columns N x ceil(H / R) x W.
-template <typename T, int OM, int V, bool VEC, int K, int R, bool PF>
+// One register buffer, two waves per SIMD in bf16 (128 x 32 x 32 maps of 32
+// channels 14.2 us; with the next column's loads in a second one 23.3 at one
+// wave).  a.M counts the columns N x ceil(H / R) x W.
+template <typename T, int OM, int V, bool VEC, int K, int R>
 __global__ __launch_bounds__(kThreads)
 void qconv_dw_bwd_data_col_kernel(const DwArgs a) {
     constexpr int NTM = om_terms(OM), NGM = om_gmaps(OM), TAPS = K * K;
@@ -784,27 +952,127 @@ void qconv_dw_bwd_data_col_kernel(const DwArgs a) {
     __amdgpu_buffer_rsrc_t mrs[3];
 #pragma unroll
     for (int m = 0; m < NGM; ++m) mrs[m] = dw_rsrc(maps[m], a.pbytes);
-    if constexpr (!PF) {
-        for (int chunk = ch_begin; chunk < ch_end; ++chunk) {
-            QL_DW_CHUNK_FENCE();
-            DwBdCol<T, OM, V, VEC, K, R> b;
-            b.fetch(a, mrs, maps, chunk * PL + pl, c, cleft);
-            dw_bd_col_compute<T, OM, V, VEC, K, R>(a, b, wl, CB, cg, c, cleft);
-        }
-        return;
+    for (int chunk = ch_begin; chunk < ch_end; ++chunk) {
+        QL_DW_CHUNK_FENCE();
+        DwBdCol<T, OM, V, VEC, K, R> b;
+        b.fetch(a, mrs, maps, chunk * PL + pl, c, cleft);
+        dw_bd_col_compute<T, OM, V, VEC, K, R>(a, b, wl, CB, cg, c, cleft);
     }
-    DwBdCol<T, OM, V, VEC, K, R> b0, b1;
-    int chunk = ch_begin;
-    b0.fetch(a, mrs, maps, chunk * PL + pl, c, cleft);
-    while (true) {
-        QL_DW_CHUNK_FENCE();
-        b1.fetch(a, mrs, maps, (chunk + 1) * PL + pl, c, cleft);
-        dw_bd_col_compute<T, OM, V, VEC, K, R>(a, b0, wl, CB, cg, c, cleft);
-        if (++chunk >= ch_end) break;
-        QL_DW_CHUNK_FENCE();
-        b0.fetch(a, mrs, maps, (chunk + 1) * PL + pl, c, cleft);
-        dw_bd_col_compute<T, OM, V, VEC, K, R>(a, b1, wl, CB, cg, c, cleft);
-        if (++chunk >= ch_end) break;
+}
+
+// Input gradient at stride 1 by rows: output row i, loaded once per segment,
+// feeds the input rows i - PH + r, r < 3, whose sums move through three
+// accumulator rows (row i - PH is complete after it); two output rows of the
+// maps are in registers, one on its way.  One term's operands (G o T_b, G o T_a,
+// G) of the row's WC + 2 columns at a time, each formed once and applied to
+// the 9 taps, each filter value read from LDS once per row.
+template <typename T, int OM, int WC>
+__global__ __launch_bounds__(kThreads, 2)
+void qconv_dw_bwd_data_rows_kernel(const DwArgs a) {
+    constexpr int NTM = om_terms(OM), NGM = om_gmaps(OM), V = 4, K = 3, TAPS = 9;
+    constexpr int NC = WC + K - 1;
+    extern __shared__ float wl[];  // [NTM][TAPS][CB]
+    const int CB = a.lanes * V;
+    const int cg = threadIdx.x & (a.lanes - 1), pl = threadIdx.x >> a.lsh, PL = kThreads >> a.lsh;
+    int tile, ch_begin, ch_end;
+    dw_chunk_range(a, PL, tile, ch_begin, ch_end);
+    const int c0 = tile * CB;
+    dw_stage_rows<T, NTM, TAPS>(a, c0, CB, wl);
+    __syncthreads();
+    const int c = c0 + V * cg, cleft = a.C - c;
+    if (cleft <= 0) return;
+    const T *maps[3] = {static_cast<const T *>(a.gy), static_cast<const T *>(a.ta), static_cast<const T *>(a.tb)};
+    __amdgpu_buffer_rsrc_t mrs[3];
+#pragma unroll
+    for (int m = 0; m < NGM; ++m) mrs[m] = dw_rsrc(maps[m], a.pbytes);
+    for (int chunk = ch_begin; chunk < ch_end; ++chunk) {
+        const int item = chunk * PL + pl;
+        int n, h0, w0;
+        dw_row_item<WC>(a, min(item, a.M - 1), n, h0, w0);
+        const int h1 = item < a.M ? min(h0 + a.seg, a.H) : 0;
+        const int oi0 = h0 + a.PH - (K - 1), oj0 = w0 + a.PW - (K - 1);  // the first output row and column
+        const int base = ((n * a.HO + oi0) * a.WO + oj0) * a.C + c, rowc = a.WO * a.C;
+        DwRaw<T, V, true> gv[2][NC][NGM];
+        auto load = [&](int row, DwRaw<T, V, true> (&dst)[NC][NGM]) {  // output row oi0 + row
+            const bool okr = (unsigned)(oi0 + row) < (unsigned)a.HO;
+#pragma unroll
+            for (int j = 0; j < NC; ++j) {
+                const bool ok = okr & ((unsigned)(oj0 + j) < (unsigned)a.WO);
+#pragma unroll
+                for (int m = 0; m < NGM; ++m) dst[j][m].load(mrs[m], maps[m], base + row * rowc + j * a.C, V, ok);
+            }
+        };
+        float acc[3][WC][V];  // input rows h0 + st - 2 + {0, 1, 2} at step st, rotating
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int p = 0; p < WC; ++p)
+#pragma unroll
+                for (int k = 0; k < V; ++k) acc[i][p][k] = 0.0f;
+        load(0, gv[0]);
+        const int steps = a.seg + K - 1;
+#pragma unroll 1
+        for (int st = 0; st < steps; ++st) {  // output row oi0 + st: input rows h0 + st - 2 + r
+            {
+                QL_DW_CHUNK_FENCE();
+                load(st + 1, gv[1]);
+                const float *wr = dw_row_base(wl, cg * (NTM * TAPS * V));
+#pragma unroll
+                for (int t = 0; t < NTM; ++t) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    float op[NC][V];
+#pragma unroll
+                    for (int j = 0; j < NC; ++j) {
+                        const DwRaw<T, V, true>(&raw)[NGM] = gv[0][j];
+#pragma unroll
+                        for (int k = 0; k < V; ++k) {
+                            const float g = raw[0].get(k);
+                            if constexpr (OM == OM_QUADRA || OM == OM_PAIR)
+                                op[j][k] = t == 2 ? g : g * raw[t == 0 ? 2 : 1].get(k);
+                            else if constexpr (OM == OM_SQUARE)
+                                op[j][k] = 2.0f * g * raw[1].get(k);
+                            else
+                                op[j][k] = g;
+                        }
+                    }
+#pragma unroll
+                    for (int rr = 0; rr < K; ++rr) {
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int q = 0; q < K; ++q) {
+                            float wv[V];
+                            dw_lds_row<V>(wr, (t * TAPS + rr * K + q) * V, wv);
+#pragma unroll
+                            for (int p = 0; p < WC; ++p)
+#pragma unroll
+                                for (int k = 0; k < V; ++k)
+                                    acc[rr][p][k] += wv[k] * op[p + K - 1 - q][k];
+                        }
+                    }
+                }
+                dw_pin(acc);
+                const int h = h0 + st - (K - 1);
+                if (h >= h0 && h < h1) {
+#pragma unroll
+                    for (int p = 0; p < WC; ++p)
+                        if (w0 + p < a.W)
+                            dw_dx_store<T, OM, V, true>(a, ((size_t)(n * a.H + h) * a.W + w0 + p) * a.C + c, cleft,
+                                                        acc[0][p]);
+                }
+            }
+#pragma unroll
+            for (int p = 0; p < WC; ++p)
+#pragma unroll
+                for (int k = 0; k < V; ++k) {
+                    acc[0][p][k] = acc[1][p][k];
+                    acc[1][p][k] = acc[2][p][k];
+                    acc[2][p][k] = 0.0f;
+                }
+#pragma unroll
+            for (int j = 0; j < NC; ++j)
+#pragma unroll
+                for (int m = 0; m < NGM; ++m) gv[0][j][m] = gv[1][j][m];
+        }
     }
 }
 

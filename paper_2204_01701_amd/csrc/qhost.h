@@ -809,9 +809,8 @@ inline bool fwd_stats_fused(const Geom &g, const FwdPlan &p) {
 // 3 x 3 filters at stride 1 or 2 take the column kernels (the input gradient
 // at stride 2 the gathering one); other shapes take the generic kernels.
 // ---------------------------------------------------------------------------
-// Rows per thread of the column kernels and whether they prefetch the next
-// column (chosen by measurement on the N=64, C=256, 56x56 layer: the
-// configurations that fit the registers without spilling).
+// Rows per thread of the column kernels (chosen by measurement on the N=64,
+// C=256, 56x56 layer: the configurations that fit the registers without spilling).
 constexpr int kDwRowsFwd = 4, kDwRowsBd = 4, kDwRowsBw = 2;
 
 struct DwPlan {
@@ -821,6 +820,8 @@ struct DwPlan {
     bool vec;              // C % V == 0: vector loads
     int lanes, lsh, tiles; // channel lanes per pixel, log2, channel slices
     int R;                 // column kernels: rows per thread
+    bool rows;             // row kernels (forward, input gradient at stride 1): segments of `seg` rows
+    int seg;
     long long items;       // work items: columns, or input pixels for the gathering kernel
     int ng, iwid;          // column kernels: row groups per image, columns per row
     int ct, tg;            // generic kernels: channel tiles of kDwCB, tap groups of 9
@@ -829,10 +830,15 @@ struct DwPlan {
     size_t ws_bytes;
 };
 
-inline int dw_lanes(int C, int V) {
+inline int dw_lanes(int C, int V, int most = 8) {
     int l = 1;
-    while (l < 8 && l * V < C) l *= 2;
+    while (l < most && l * V < C) l *= 2;
     return l;
+}
+
+// Columns per thread of the row kernels: as many as the registers take.
+inline int dw_row_cols(const Geom &g, int pass) {
+    return pass == 0 ? (g.SH == 1 ? 4 : 2) : (g.dt == QL_BF16 ? 4 : 2);
 }
 
 // pass: 0 forward, 1 input gradient, 2 weight gradient
@@ -859,6 +865,44 @@ inline DwPlan plan_dw(const Geom &g, int pass) {
     p.ng = cdiv(rows, p.R);
     p.items = p.col ? (long long)g.N * p.ng * p.iwid : (long long)g.N * (pass == 1 ? g.H * g.W : g.HO * g.WO);
     const int PL = kThreads / p.lanes;
+    // The row kernels on large maps: a segment of rows per thread, as many segments
+    // per column as make the fewest row steps of a workgroup slot (the rounds
+    // times a segment's rows and halo), where at least three quarters of the
+    // resident workgroups get a segment of 14 rows or more.  With less work than
+    // that a thread's rows are a serial chain, about 2 us each alone on a SIMD, and
+    // the column kernels' shorter items win (bf16 forward and input gradient, us,
+    // row against column kernels: 64 x 56 x 56 maps of 256 channels 115, 114 against
+    // 170, 213; 128 x 32 x 32 of 32 channels 26.4, 25.2 against 14.3, 14.2).
+    const int rows_env = env_override("QLAYER_DW_ROWS", -1);
+    if (p.col && p.vec && pass != 2 && rows_env != 0) {
+        const int lanes = dw_lanes(g.C, 4, 64), tiles = cdiv(g.C, lanes * 4), ncg = cdiv(p.iwid, dw_row_cols(g, pass));
+        const bool three = pass == 0 ? g.dt == QL_BF16 : g.dt == QL_F32;  // 4-wave workgroups per CU by registers
+        const int slots = kNumCUs * (three ? 3 : 2);
+        long long best = 0;
+        int seg = 0, wgs = 0;
+        for (int ns = 1; ns <= std::max(1, rows / 14); ++ns) {
+            const int sg = cdiv(rows, ns);
+            const int n = cdiv((long long)g.N * ncg * cdiv(rows, sg), kThreads / lanes) * tiles;
+            const long long cost = (long long)cdiv(n, slots) * (sg + 2);
+            if (!seg || cost < best) {
+                best = cost;
+                seg = sg;
+                wgs = n;
+            }
+        }
+        if (rows_env == 1 || (seg >= 14 && 4LL * wgs >= 3LL * slots)) {
+            p.rows = true;
+            p.lanes = lanes;
+            p.lsh = __builtin_ctz(lanes);
+            p.tiles = tiles;
+            p.iwid = ncg;
+            p.seg = seg;
+            p.ng = cdiv(rows, seg);
+            p.items = (long long)g.N * p.ng * ncg;
+            p.grid = std::max(1, std::min(cdiv(p.items, kThreads / lanes), cdiv(slots, tiles))) * tiles;
+            return p;
+        }
+    }
     if (pass != 2) {
         const int chunks = cdiv(p.items, PL);
         const int target = env_override("QLAYER_DW_BLOCKS", 2 * kNumCUs);
@@ -883,7 +927,7 @@ inline DwArgs dw_args(const Geom &g, const DwPlan &p) {
     a.neuron = g.ne;
     a.J = 3 * g.C * (g.KH * g.KW + 1);
     a.lanes = p.lanes; a.lsh = p.lsh; a.tiles = p.tiles;
-    a.ng = p.ng; a.iwid = p.iwid;
+    a.ng = p.ng; a.iwid = p.iwid; a.seg = p.seg;
     a.fd_howo = make_fastdiv(g.HO * g.WO);
     a.fd_wo = make_fastdiv(g.WO);
     a.fd_hw = make_fastdiv(g.H * g.W);

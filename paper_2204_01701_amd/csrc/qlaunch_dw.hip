@@ -7,16 +7,26 @@ namespace host {
 // 3 x 3 kernels of one operand mode and channel vector.
 template <typename T, int OM, int V, bool VEC>
 void dw_launch_k(const DwPlan &p, int pass, int S, const DwArgs &a, dim3 grid, size_t smem, hipStream_t st) {
+    if (p.rows) {
+        if constexpr (V == 4 && VEC) {
+            constexpr bool BF = sizeof(T) == 2;
+            if (pass == 0 && S == 1)
+                hipLaunchKernelGGL((qconv_dw_fwd_rows_kernel<T, OM, 1, 4, BF ? 2 : 1>), grid, dim3(kThreads), smem, st, a);
+            else if (pass == 0)
+                hipLaunchKernelGGL((qconv_dw_fwd_rows_kernel<T, OM, 2, 2, 1>), grid, dim3(kThreads), smem, st, a);
+            else
+                hipLaunchKernelGGL((qconv_dw_bwd_data_rows_kernel<T, OM, BF ? 4 : 2>), grid, dim3(kThreads), smem, st, a);
+        }
+        return;
+    }
     if (pass == 0) {
         if constexpr (V == 4) {
-            if (S == 1) hipLaunchKernelGGL((qconv_dw_fwd_col_kernel<T, OM, V, VEC, 3, 1, kDwRowsFwd, true>), grid, dim3(kThreads), smem, st, a);
-            else hipLaunchKernelGGL((qconv_dw_fwd_col_kernel<T, OM, V, VEC, 3, 2, kDwRowsFwd, true>), grid, dim3(kThreads), smem, st, a);
+            if (S == 1) hipLaunchKernelGGL((qconv_dw_fwd_col_kernel<T, OM, V, VEC, 3, 1, kDwRowsFwd>), grid, dim3(kThreads), smem, st, a);
+            else hipLaunchKernelGGL((qconv_dw_fwd_col_kernel<T, OM, V, VEC, 3, 2, kDwRowsFwd>), grid, dim3(kThreads), smem, st, a);
         }
     } else if (pass == 1) {
-        // prefetching the next column fits the registers with bf16 only
-        constexpr bool PF = sizeof(T) == 2 && V == 4;
         if (!p.col) hipLaunchKernelGGL((qconv_dw_bwd_data_k_kernel<T, OM, V, VEC, 3, 2>), grid, dim3(kThreads), smem, st, a);
-        else if constexpr (V == 4) hipLaunchKernelGGL((qconv_dw_bwd_data_col_kernel<T, OM, V, VEC, 3, kDwRowsBd, PF>), grid, dim3(kThreads), smem, st, a);
+        else if constexpr (V == 4) hipLaunchKernelGGL((qconv_dw_bwd_data_col_kernel<T, OM, V, VEC, 3, kDwRowsBd>), grid, dim3(kThreads), smem, st, a);
     } else if constexpr (V == 4) {
         if (S == 1) hipLaunchKernelGGL((qconv_dw_bwd_weight_col_kernel<T, OM, V, VEC, 3, 1, kDwRowsBw>), grid, dim3(kThreads), 0, st, a);
         else hipLaunchKernelGGL((qconv_dw_bwd_weight_col_kernel<T, OM, V, VEC, 3, 2, kDwRowsBw>), grid, dim3(kThreads), 0, st, a);
