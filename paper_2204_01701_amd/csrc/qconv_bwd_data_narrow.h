@@ -1,5 +1,5 @@
 // qconv_bwd_data_narrow.h -- input gradient of the quadratic convolution
-// layer (arXiv 2204.01701, section 4.3, eq:SD) for narrow layers: at most 32
+// layer (arXiv 2204.01701, section 4.3, eq:SD) for narrow layers: at most 16
 // input channels and a short reduction K = KH * KW * O (the 16-channel stages
 // of a CIFAR ResNet), where the tiled kernels spend most of their time on
 // per-tile overhead:
@@ -43,9 +43,8 @@ __global__ __launch_bounds__(kThreads, 2) void qconv_bwd_data_narrow_kernel(cons
     constexpr int VEC = Elem<T>::VEC;
     constexpr int CK = narrow_chunk<T>();
     const int lane = threadIdx.x & 63, li = lane & 15, lg = lane >> 4;
-    const T *__restrict__ gy = static_cast<const T *>(a.gy);
-    const T *__restrict__ ta = static_cast<const T *>(a.ta);
-    const T *__restrict__ tb = static_cast<const T *>(a.tb);
+    const uint32_t gbytes = (uint32_t)(a.N * a.HO * a.WO * a.O) * (uint32_t)sizeof(T);
+    const __amdgpu_buffer_rsrc_t grs[3] = {raw_rsrc(a.gy, gbytes), raw_rsrc(a.ta, gbytes), raw_rsrc(a.tb, gbytes)};
 
     // This wave's phase, its rank among the phase's waves and their number: wave
     // u of every a.units belongs to the phase with unit_end[phase - 1] <= u < unit_end[phase].
@@ -81,14 +80,13 @@ __global__ __launch_bounds__(kThreads, 2) void qconv_bwd_data_narrow_kernel(cons
     v4u wf[3][CB][NCH];
 #pragma unroll
     for (int t = 0; t < 3; ++t) {
-        const T *__restrict__ wt = static_cast<const T *>(a.wt[t]);
+        const __amdgpu_buffer_rsrc_t wrs = raw_rsrc(a.wt[t], (uint32_t)(a.C * a.K) * (uint32_t)sizeof(T));
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb) {
             const int c = 16 * cb + li;
 #pragma unroll
             for (int ch = 0; ch < NCH; ++ch) {
-                wf[t][cb][ch] = (c < a.C && kin[ch]) ? *reinterpret_cast<const v4u *>(wt + (size_t)c * a.K + kw[ch])
-                                                     : v4u{0u, 0u, 0u, 0u};
+                wf[t][cb][ch] = narrow_run<T>(wrs, c * a.K + kw[ch], (c < a.C) & kin[ch]);
             }
         }
     }
@@ -115,28 +113,42 @@ __global__ __launch_bounds__(kThreads, 2) void qconv_bwd_data_narrow_kernel(cons
             w = rem - h * ph.wp;
             p = (n * a.H + ph.h0 + a.SH * h) * a.W + ph.w0 + a.SW * w;
         }
-        const size_t nbase = (size_t)n * a.HO * a.WO;
+        const int nbase = n * a.HO * a.WO;
         f32x4n_t acc[CB];
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb) acc[cb] = f32x4n_t{0.0f, 0.0f, 0.0f, 0.0f};
+        // Chunks in groups of GC: a group's runs are all loaded before its products.
+        // (A phase's taps may end early, so a long reduction takes small groups there: the
+        // layer of the header in fp32 42 us in pairs, 55 in fours; all at once where they
+        // fit: 16 -> 8 channels of the same maps 23 us in fp32, 29 in pairs.)
+        constexpr int GC = NCH <= 5 ? NCH : (S1 ? (NCH + 1) / 2 : 2);
 #pragma unroll
-        for (int ch = 0; ch < NCH; ++ch) {
-            if (!S1 && CK * ch >= K) continue;  // (wave-uniform: past the phase's taps)
-            // the output pixel tap (r, q) of this input pixel reads, if any
-            const int oh = h + ph.oh0 - kr[ch], ow = w + ph.ow0 - kq[ch];
-            const bool ok = pok && kin[ch] && (unsigned)oh < (unsigned)a.HO && (unsigned)ow < (unsigned)a.WO;
-            const size_t off = (nbase + (size_t)oh * a.WO + ow) * a.O + ko[ch];
-            const v4u zero = {0u, 0u, 0u, 0u};
-            const v4u g = ok ? *reinterpret_cast<const v4u *>(gy + off) : zero;
-            const v4u va = ok ? *reinterpret_cast<const v4u *>(ta + off) : zero;
-            const v4u vb = ok ? *reinterpret_cast<const v4u *>(tb + off) : zero;
-            v4u ga, gb;
-            prologue_frag<T>(g, va, vb, ga, gb);
+        for (int c0 = 0; c0 < NCH; c0 += GC) {
+            if (!S1 && CK * c0 >= K) continue;  // (wave-uniform: past the phase's taps)
+            v4u run[GC][3];  // of G, T_a, T_b
 #pragma unroll
-            for (int cb = 0; cb < CB; ++cb) {
-                narrow_mfma<T>(wf[0][cb][ch], ga, acc[cb]);
-                narrow_mfma<T>(wf[1][cb][ch], gb, acc[cb]);
-                narrow_mfma<T>(wf[2][cb][ch], g, acc[cb]);
+            for (int u = 0; u < GC && c0 + u < NCH; ++u) {
+                const int ch = c0 + u;
+                if (!S1 && GC > 2 && CK * ch >= K) continue;
+                // the output pixel tap (r, q) of this input pixel reads, if any
+                const int oh = h + ph.oh0 - kr[ch], ow = w + ph.ow0 - kq[ch];
+                const bool ok = pok & kin[ch] & ((unsigned)oh < (unsigned)a.HO) & ((unsigned)ow < (unsigned)a.WO);
+                const int off = (nbase + oh * a.WO + ow) * a.O + ko[ch];
+#pragma unroll
+                for (int t = 0; t < 3; ++t) run[u][t] = narrow_run<T>(grs[t], off, ok);
+            }
+#pragma unroll
+            for (int u = 0; u < GC && c0 + u < NCH; ++u) {
+                const int ch = c0 + u;
+                if (!S1 && GC > 2 && CK * ch >= K) continue;
+                v4u ga, gb;
+                prologue_frag<T>(run[u][0], run[u][1], run[u][2], ga, gb);
+#pragma unroll
+                for (int cb = 0; cb < CB; ++cb) {
+                    narrow_mfma<T>(wf[0][cb][ch], ga, acc[cb]);
+                    narrow_mfma<T>(wf[1][cb][ch], gb, acc[cb]);
+                    narrow_mfma<T>(wf[2][cb][ch], run[u][0], acc[cb]);
+                }
             }
         }
         if (pok) {

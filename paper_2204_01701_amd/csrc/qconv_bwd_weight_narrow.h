@@ -19,7 +19,7 @@
 //     lane and fragment, lane = (pixel, run group)) and the runs of G, T_a,
 //     T_b, form the products G o T_b, G o T_a in fp32 (the bias sums add
 //     them before rounding) and write all of it to LDS as pixel rows, the
-//     next step's loads already in flight where the registers allow;
+//     next step's loads then in flight behind its products;
 //   - the MFMA operands come back transposed (pixels as the reduction index):
 //     bf16 by ds_read_b64_tr_b16 into v_mfma_f32_16x16x32_bf16, fp32 by
 //     ds_read_b32 into v_mfma_f32_16x16x4f32 (rows padded by 16 bytes, so
@@ -32,6 +32,7 @@
 #include "qargs.h"
 #include "qdevice.h"
 #include "qpipe.h"
+#include "qconv_fwd_narrow.h"
 
 namespace ql {
 
@@ -72,9 +73,9 @@ __device__ __forceinline__ void bwd_weight_narrow_body(const BwdWeightArgs &a, c
     char *const xt = smem + wave * WAVE_LDS;
     char *const pt = xt + XT;
     const int px = lane % KE, rg = lane / KE;
-    const T *__restrict__ x = static_cast<const T *>(a.x);
-    const T *__restrict__ gsrc[3] = {static_cast<const T *>(a.gy), static_cast<const T *>(a.ta),
-                                     static_cast<const T *>(a.tb)};
+    const __amdgpu_buffer_rsrc_t xrs = raw_rsrc(a.x, (uint32_t)(a.N * a.H * a.W * a.C) * (uint32_t)sizeof(T));
+    const uint32_t gbytes = (uint32_t)(a.M * a.O) * (uint32_t)sizeof(T);
+    const __amdgpu_buffer_rsrc_t grs[3] = {raw_rsrc(a.gy, gbytes), raw_rsrc(a.ta, gbytes), raw_rsrc(a.tb, gbytes)};
 
     // this lane's X runs: fragment i, k' = 16 i + VEC rg .. + VEC (one tap)
     int xr[NF], xq[NF], xc[NF];
@@ -103,24 +104,21 @@ __device__ __forceinline__ void bwd_weight_narrow_body(const BwdWeightArgs &a, c
 
     auto load = [&](int s, v4u *xv, v4u *gv) {
         const int m = s * KE + px;
-        const bool mok = s < s_end && m < a.M;
+        const bool mok = (s < s_end) & (m < a.M);
         const int mm = mok ? m : 0;
         const int n = (int)fdiv((uint32_t)mm, a.fd_howo);
         const int rem = mm - n * a.HO * a.WO;
         const int oh = (int)fdiv((uint32_t)rem, a.fd_wo);
         const int ow = rem - oh * a.WO;
         const int h0 = oh * a.SH - a.PH, w0 = ow * a.SW - a.PW;
-        const v4u zero = {0u, 0u, 0u, 0u};
 #pragma unroll
         for (int i = 0; i < NF; ++i) {
             const int ih = h0 + xr[i], iw = w0 + xq[i];
-            const bool ok = mok && kok[i] && (unsigned)ih < (unsigned)a.H && (unsigned)iw < (unsigned)a.W;
-            xv[i] = ok ? *reinterpret_cast<const v4u *>(x + ((size_t)(n * a.H + ih) * a.W + iw) * a.C + xc[i]) : zero;
+            const bool ok = mok & kok[i] & ((unsigned)ih < (unsigned)a.H) & ((unsigned)iw < (unsigned)a.W);
+            xv[i] = narrow_run<T>(xrs, ((n * a.H + ih) * a.W + iw) * a.C + xc[i], ok);
         }
-        const bool gok = mok && ook;
-        const size_t off = (size_t)mm * a.O + ob0 + o0;
 #pragma unroll
-        for (int u = 0; u < 3; ++u) gv[u] = gok ? *reinterpret_cast<const v4u *>(gsrc[u] + off) : zero;
+        for (int u = 0; u < 3; ++u) gv[u] = narrow_run<T>(grs[u], mm * a.O + ob0 + o0, mok & ook);
     };
 
     f32x4w_t acc[3][NF];
@@ -134,11 +132,9 @@ __device__ __forceinline__ void bwd_weight_narrow_body(const BwdWeightArgs &a, c
 #pragma unroll
         for (int e = 0; e < VEC; ++e) dsum[t][e] = 0.0f;
 
-    constexpr bool PF = NF <= 6;  // load the next step during this one (longer rows: its registers would spill)
     v4u xv[NF], gv[3];
-    if constexpr (PF) load(s_begin, xv, gv);
+    load(s_begin, xv, gv);
     for (int s = s_begin; s < s_end; ++s) {
-        if constexpr (!PF) load(s, xv, gv);
         // the step's rows into LDS: X runs, then G o T_b, G o T_a, G
         float fa[VEC], fb[VEC];
 #pragma unroll
@@ -157,9 +153,7 @@ __device__ __forceinline__ void bwd_weight_narrow_body(const BwdWeightArgs &a, c
         *reinterpret_cast<v4u *>(pt + px * PP + rg * 16) = vpack<T>(fa);
         *reinterpret_cast<v4u *>(pt + PT + px * PP + rg * 16) = vpack<T>(fb);
         *reinterpret_cast<v4u *>(pt + 2 * PT + px * PP + rg * 16) = gv[0];
-        if constexpr (PF) {
-            if (s + 1 < s_end) load(s + 1, xv, gv);  // (registers free once written)
-        }
+        load(s + 1, xv, gv);  // the next step's (registers free once written; past the last step zeros)
         wave_lds_sync();
         if constexpr (BF) {
             v4u bt[3];

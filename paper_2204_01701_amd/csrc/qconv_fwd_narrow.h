@@ -1,5 +1,5 @@
 // qconv_fwd_narrow.h -- forward of the quadratic convolution layer (arXiv
-// 2204.01701, section 3.1, eq:2ndneuron3) for narrow layers: at most 32 output
+// 2204.01701, section 3.1, eq:2ndneuron3) for narrow layers: at most 16 output
 // channels and a short reduction J = KH * KW * C (the 16-channel stages of a
 // CIFAR ResNet and its stem), where the tiled implicit GEMM spends most of
 // its time on per-tile overhead (three 64-row term blocks for 16 channels).
@@ -14,7 +14,7 @@
 //   - the three terms' weight fragments (rows o, all of J) are loaded once per
 //     wave and stay in registers; each wave then takes every (waves)-th block
 //     of 16 output pixels, loading the next block's X runs before the current
-//     block's MFMAs where the registers allow (J of at most 6 runs per lane);
+//     block's MFMAs;
 //   - the 16 x 16 accumulator layout puts pixel l % 16 and channels
 //     4 (l / 16) .. +4 in lane l, so the epilogue forms Y = T_a o T_b + T_c
 //     (with the fused scale, shift, ReLU when asked) in place and each map of
@@ -30,6 +30,7 @@
 
 #include "qargs.h"
 #include "qdevice.h"
+#include "qpipe.h"
 
 namespace ql {
 
@@ -53,6 +54,22 @@ template <> __device__ __forceinline__ void narrow_mfma<float>(const v4u &a, con
 // groups of a 16 x 16 operand: 32 bf16 or 16 fp32.
 template <typename T> constexpr int narrow_chunk() { return 4 * Elem<T>::VEC; }
 
+// A 16-byte run at element offset `e` of a tensor below 2^31 bytes, or zeros:
+// a buffer load past the end where !ok.  Behind a condition each load had a
+// branch of its own, and in the input gradient a wait: one latency per chunk.
+// (16 -> 16 channels, 256 x 32 x 32 maps, 3 x 3, us per pass with branches and
+// now, fwd, input gradient, weight gradient: fp32 59, 76, 56 and 46, 54, 53, where
+// the MFMAs of a pass take 24 at the rate of a large fp32 product; bf16 14.5, 26,
+// 27 and 13, 21, 26.)
+template <typename T> __device__ __forceinline__ v4u narrow_run(__amdgpu_buffer_rsrc_t rs, int e, bool ok) {
+    const uint32_t off = ok ? (uint32_t)e * (uint32_t)sizeof(T) : 0x80000000u;
+    return __builtin_bit_cast(v4u, __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0));
+}
+// A float vector of n values (NULL: all zero reads).
+__device__ __forceinline__ float narrow_vec(const float *p, int n, int i) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(raw_rsrc(p, p ? n * 4 : 0), i * 4, 0, 0));
+}
+
 // OB: 16-channel row blocks per term (O <= 16 OB, O a multiple of 4).  NCH:
 // reduction chunks (J <= NCH narrow_chunk).  EPI: the fused epilogue on Y.
 // C (the channels the kernel sees) is a multiple of the run length, so no
@@ -62,7 +79,7 @@ __global__ __launch_bounds__(kThreads, 2) void qconv_fwd_narrow_kernel(const Fwd
     constexpr int VEC = Elem<T>::VEC;
     constexpr int CK = narrow_chunk<T>();
     const int lane = threadIdx.x & 63, li = lane & 15, lg = lane >> 4;
-    const T *__restrict__ x = static_cast<const T *>(a.x);
+    const __amdgpu_buffer_rsrc_t xrs = raw_rsrc(a.x, (uint32_t)(a.N * a.H * a.W * a.C) * (uint32_t)sizeof(T));
 
     // This lane's reduction runs: k = CK ch + VEC lg .. + VEC, tap (r, q), channel c.
     int kdr[NCH], kdq[NCH], kc[NCH];
@@ -81,15 +98,14 @@ __global__ __launch_bounds__(kThreads, 2) void qconv_fwd_narrow_kernel(const Fwd
     v4u wf[3][OB][NCH];
 #pragma unroll
     for (int t = 0; t < 3; ++t) {
-        const T *__restrict__ w = static_cast<const T *>(a.w[t]);
+        const __amdgpu_buffer_rsrc_t wrs = raw_rsrc(a.w[t], (uint32_t)(a.O * a.K) * (uint32_t)sizeof(T));
 #pragma unroll
         for (int ob = 0; ob < OB; ++ob) {
             const int o = 16 * ob + li;
 #pragma unroll
             for (int ch = 0; ch < NCH; ++ch) {
                 const int k = CK * ch + VEC * lg;
-                wf[t][ob][ch] = (o < a.O && kin[ch]) ? *reinterpret_cast<const v4u *>(w + (size_t)o * a.K + k)
-                                                     : v4u{0u, 0u, 0u, 0u};
+                wf[t][ob][ch] = narrow_run<T>(wrs, o * a.K + k, (o < a.O) & kin[ch]);
             }
         }
     }
@@ -102,26 +118,35 @@ __global__ __launch_bounds__(kThreads, 2) void qconv_fwd_narrow_kernel(const Fwd
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const int o = 16 * ob + 4 * lg + v;
-                bias[t][ob][v] = (a.bias[t] != nullptr && o < a.O) ? a.bias[t][o] : 0.0f;
+                bias[t][ob][v] = narrow_vec(a.bias[t], a.O, o);
             }
+    float esc[OB][4], esh[OB][4];  // the epilogue's scale and shift of those channels
+    if constexpr (EPI) {
+#pragma unroll
+        for (int ob = 0; ob < OB; ++ob)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                esc[ob][v] = narrow_vec(a.epi.scale, a.O, 16 * ob + 4 * lg + v);
+                esh[ob][v] = narrow_vec(a.epi.shift, a.O, 16 * ob + 4 * lg + v);
+            }
+    }
 
     // X runs of the block's pixel m = 16 b + li (zero outside the image or past J or M).
     auto load_x = [&](int b, v4u *xf) {
         const int m = 16 * b + li;
         const bool mok = m < a.M;
-        const int mm = mok ? m : a.M - 1;
+        const int mm = min(m, a.M - 1);
         const int n = (int)fdiv((uint32_t)mm, a.fd_howo);
         const int rem = mm - n * a.HO * a.WO;
         const int oh = (int)fdiv((uint32_t)rem, a.fd_wo);
         const int ow = rem - oh * a.WO;
         const int h0 = oh * a.SH, w0 = ow * a.SW;
-        const size_t nbase = (size_t)n * a.H * a.W;
+        const int nbase = n * a.H * a.W;
 #pragma unroll
         for (int ch = 0; ch < NCH; ++ch) {
             const int ih = h0 + kdr[ch], iw = w0 + kdq[ch];
-            const bool ok = mok && kin[ch] && (unsigned)ih < (unsigned)a.H && (unsigned)iw < (unsigned)a.W;
-            xf[ch] = ok ? *reinterpret_cast<const v4u *>(x + (nbase + (size_t)ih * a.W + iw) * a.C + kc[ch])
-                        : v4u{0u, 0u, 0u, 0u};
+            const bool ok = mok & kin[ch] & ((unsigned)ih < (unsigned)a.H) & ((unsigned)iw < (unsigned)a.W);
+            xf[ch] = narrow_run<T>(xrs, (nbase + ih * a.W + iw) * a.C + kc[ch], ok);
         }
     };
 
@@ -138,16 +163,11 @@ __global__ __launch_bounds__(kThreads, 2) void qconv_fwd_narrow_kernel(const Fwd
     for (int ob = 0; ob < OB; ++ob)
 #pragma unroll
         for (int v = 0; v < 4; ++v) ssum[ob][v] = ssq[ob][v] = 0.0f;
-    constexpr bool PF = NCH <= 6;  // prefetch the next block (longer J: its registers would spill)
     v4u xf[NCH];
-    if constexpr (PF) load_x(b, xf);
+    load_x(b, xf);
     for (; b < nblk; b += nw) {
-        v4u xn[PF ? NCH : 1];
-        if constexpr (PF) {
-            if (b + nw < nblk) load_x(b + nw, xn);
-        } else {
-            load_x(b, xf);
-        }
+        v4u xn[NCH];  // the wave's next block (past the last: zeros)
+        load_x(b + nw, xn);
         f32x4n_t acc[3][OB];
 #pragma unroll
         for (int t = 0; t < 3; ++t)
@@ -171,7 +191,11 @@ __global__ __launch_bounds__(kThreads, 2) void qconv_fwd_narrow_kernel(const Fwd
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
                     yv[v] = acc[0][ob][v] * acc[1][ob][v] + acc[2][ob][v];
-                    if constexpr (EPI) yv[v] = epi_apply(a.epi, o + v, yv[v]);
+                    if constexpr (EPI) {
+                        if (a.epi.scale) yv[v] *= esc[ob][v];
+                        if (a.epi.shift) yv[v] += esh[ob][v];
+                        if (a.epi.relu) yv[v] = fmaxf(yv[v], 0.0f);
+                    }
                 }
                 if (y) store4<T>(y + off, yv[0], yv[1], yv[2], yv[3]);
                 if (stats) {
@@ -186,10 +210,8 @@ __global__ __launch_bounds__(kThreads, 2) void qconv_fwd_narrow_kernel(const Fwd
                 if (tb) store4<T>(tb + off, acc[1][ob][0], acc[1][ob][1], acc[1][ob][2], acc[1][ob][3]);
             }
         }
-        if constexpr (PF) {
 #pragma unroll
-            for (int ch = 0; ch < NCH; ++ch) xf[ch] = xn[ch];
-        }
+        for (int ch = 0; ch < NCH; ++ch) xf[ch] = xn[ch];
     }
     if (stats) {
         // this wave's part: the 16 lanes of channel group lg add in a fixed butterfly

@@ -266,6 +266,13 @@ constexpr int kFwdBCOL[kFwdCfgs] = {128, 256, 128, 128, 256, 256, 256, 128};
 // Workgroups one CU holds at once (limited by LDS stages and registers).
 constexpr int kFwdSlots[kFwdCfgs] = {1, 1, 1, 2, 1, 1, 1, 2};
 
+// Whether the narrow kernels can address a layer: their buffer loads take
+// 32-bit byte offsets, with those from 2^31 on meaning "zero".
+inline bool narrow_fits(const Geom &g, int C, int O) {
+    const long long lim = (1LL << 31) / g.esize();
+    return (long long)g.N * g.H * g.W * C < lim && (long long)g.N * g.HO * g.WO * O < lim;
+}
+
 // Waves of the narrow kernels (a multiple of the four per workgroup): one per
 // 16-pixel block up to three per SIMD, then more blocks per wave.
 inline int narrow_waves(long long pixels) {
@@ -285,7 +292,7 @@ struct FwdPlan {
     int row_tiles, col_tiles, splits, sps, stages_total;
     bool veck;
     bool smallc;  // KH KW C + bias columns <= 32, 32 or 64 output channels: qconv_fwd_smallc_kernel, no workspace
-    bool narrow;  // at most 32 output channels, short J: qconv_fwd_narrow_kernel (OB row blocks, NCH chunks)
+    bool narrow;  // at most 16 output channels, short J: qconv_fwd_narrow_kernel (OB row blocks, NCH chunks)
     int ob, nch;
     bool ksplit;  // small outputs: qconv_fwd_ksplit_kernel (tiles of 3 x 16 krb rows by 16 kcb pixels, K split by waves)
     int krb, kcb;
@@ -324,7 +331,7 @@ inline FwdPlan plan_fwd(const Geom &g) {
     // (one 16-channel row block: two measured slower than the tiled kernel on the
     // 16 -> 32-channel stride-2 layer of a CIFAR ResNet)
     if (p.veck && g.ne == NEURON_QUADRA && g.O % 4 == 0 && p.ob == 1 && p.nch <= 9 &&
-        env_override("QLAYER_FWD_NARROW", 1) != 0) {
+        narrow_fits(g, p.Cp, g.O) && env_override("QLAYER_FWD_NARROW", 1) != 0) {
         p.narrow = true;
         p.splits = 1;
         p.KE = 64 / (int)g.esize();
@@ -468,7 +475,7 @@ struct BwdDataPlan {
     bool veck, s1;
     bool natw;    // weights read untransposed through natural LDS tiles (bf16, C % 8 == 0)
     bool smallc;  // C <= 4: per-pixel partial sums by MFMA, then a gather over the taps
-    bool narrow;  // at most 32 input channels, short K: qconv_bwd_data_narrow_kernel (CB row blocks, NCH chunks)
+    bool narrow;  // at most 16 input channels, short K: qconv_bwd_data_narrow_kernel (CB row blocks, NCH chunks)
     int cb, nch;
     bool ca, pm;  // channel-aligned K steps; position-major order with taps skipped (BwdDataArgs)
     int order;  // block order of the split-K grid (tile_coord)
@@ -535,7 +542,7 @@ inline BwdDataPlan plan_bwd_data(const Geom &g) {
     p.cb = cdiv(g.C, 16);
     p.nch = cdiv(K, 4 * g.vec());
     if (p.veck && g.ne == NEURON_QUADRA && g.C % 4 == 0 && p.cb == 1 && p.nch <= 9 &&
-        env_override("QLAYER_BWD_DATA_NARROW", 1) != 0) {
+        narrow_fits(g, g.C, p.Op) && env_override("QLAYER_BWD_DATA_NARROW", 1) != 0) {
         p.narrow = true;
         p.splits = 1;
         p.wt_bytes = align_up(3 * (size_t)p.Op * g.KH * g.KW * g.C * g.esize());
@@ -646,6 +653,7 @@ constexpr int kBwPipes[kBwCfgs] = {1, 1, 1, 1, 2, 1};  // pipelines per workgrou
 
 struct BwdWeightPlan {
     bool narrow;  // KH KW C <= 144: qconv_bwd_weight_narrow_kernel (NF fragments, NOB 16-channel slices)
+    bool few;     // a few-channel layer on the padded copy of X (refused where its scratch does not fit)
     int nf, nob;
     int cfg;   // pipelined path only
     bool pipe; // bf16 and vectorizable: pipelined kernel; otherwise the generic one
@@ -704,7 +712,8 @@ inline BwdWeightPlan plan_bwd_weight(const Geom &g, size_t max_split_bytes = kMa
     // channels, 3 x 3, us at four steps per wave everywhere and now: 64 x 16 x 16
     // maps fp32 22.6 -> 17.8, bf16 18.6 -> 15.1; 16 x 8 x 8 maps fp32 22.4 -> 14.)
     p.nf = cdiv(KP, 16);
-    if (narrow_shape) {
+    p.few = p.padc && !p.pado && g.C < 2 * g.vec() && (g.dt == QL_BF16 || narrow_shape);
+    if (narrow_shape && narrow_fits(g, p.Cp, p.Op)) {
         p.narrow = true;
         p.nob = cdiv(p.Op, 16);
         p.stages_total = cdiv(M, g.dt == QL_BF16 ? 32 : 16);

@@ -228,8 +228,7 @@ ql_status bwd_weight_common(const Geom &g, const void *x, const void *gy, const 
             // Padded copies that do not fit: the register-staged kernel, which needs none.
             // (Not on the few-channel layers, C below two vectors and O whole vectors:
             // they are refused here, as the header says.)
-            const bool few = g.C < 2 * g.vec() && !p.pado && (g.dt == QL_BF16 || p.narrow);
-            if (p.ws_bytes > kScratchBytes && (p.padc || p.pado) && !few)
+            if (p.ws_bytes > kScratchBytes && (p.padc || p.pado) && !p.few)
                 p = plan_bwd_weight(g, (kScratchBytes - 2 * kAlign) / (kpo + 1) * kpo, false);
         }
         if (p.ws_bytes > kScratchBytes) return QL_EWORKSPACE;

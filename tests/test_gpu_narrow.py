@@ -7,8 +7,10 @@ filter, 16 -> 8 channels, O < 16, and the weight gradient of wider layers
 (up to 64 channels) in 16-channel slices.  Normwise limits as in
 test_gpu_parity."""
 import pytest
+import torch
 
 import oracle
+import paper_2204_01701_amd as ql
 import synth
 
 pytestmark = pytest.mark.gpu
@@ -53,3 +55,38 @@ def test_narrow_paths_match_oracle(shape, bf16, narrow, monkeypatch):
     for k in KEYS_FWD + KEYS_GRAD:
         e = qlh.relerr(got[k], ref[k])
         assert e <= qlh.tol(bf16, k in KEYS_GRAD), f"{k}: normwise relative error {e:.3e}"
+
+
+@pytest.mark.parametrize("shape", [(32, 16, 1024, 1024, 16, 1), (33, 8, 1024, 2048, 8, 2)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_maps_from_2_31_bytes_leave_the_narrow_kernels(shape):
+    """The narrow kernels address maps below 2^31 bytes; a layer whose fp32 X is
+    at or past that takes the tiled kernels, and agrees with the same layer
+    called on batches of a few images (narrow).  Either side is within the fp32
+    limit of the exact result, so the two are within twice that."""
+    n, c, h, w, o, s = shape
+    dev, part = torch.device("cuda"), 8
+    gen = torch.Generator(device=dev).manual_seed(9)
+    r = lambda *sh: torch.randn(*sh, device=dev, generator=gen)  # noqa: E731
+    x, ws, bs = r(n, h, w, c), [r(o, 3, 3, c) / (9 * c) ** 0.5 for _ in range(3)], [r(o) for _ in range(3)]
+    assert x.numel() * 4 >= 2 ** 31
+
+    def run(x):
+        d = ql.conv_desc(x.shape[0], c, h, w, o, 3, 3, s, 1, ql.QL_F32)
+        maps = [torch.empty(x.shape[0], d.ho, d.wo, o, device=dev) for _ in range(3)]
+        dx, dw, db = torch.empty_like(x), [torch.empty_like(v) for v in ws], [torch.empty_like(b) for b in bs]
+        ql.qlayer_conv2d_fwd(d, x, *ws, *bs, *maps)
+        ql.qlayer_conv2d_bwd_data(d, maps[0], maps[1], maps[2], *ws, dx)
+        ql.qlayer_conv2d_bwd_weight(d, x, maps[0], maps[1], maps[2], *dw, *db)
+        return maps + [dx], dw + db
+
+    whole, grads = run(x)
+    total = None
+    for i in range(0, n, part):
+        got, gi = run(x[i:i + part])
+        for k, (a, b) in enumerate(zip(whole, got)):
+            a = a[i:i + part]
+            assert float((a - b).norm() / b.norm()) <= 2 * qlh.tol(False, k == 3), (i, k)
+        total = [v.double() for v in gi] if total is None else [t + v for t, v in zip(total, gi)]
+    for k, (a, b) in enumerate(zip(grads, total)):
+        assert float((a - b).norm() / b.norm()) <= 2 * qlh.tol(False, True), k
