@@ -342,7 +342,6 @@ _KERNEL_FAMILY = [
     (r"qconv_fwd_narrow_kernel<", "fwd", True),
     (r"qconv_fwd_ksplit_kernel<", "fwd", True),
     (r"qconv_fwd_combine_kernel<", "fwd", False),
-    (r"qconv_pad_channels_kernel<[^,>]+, 4>", "fwd", False),
     (r"qconv_bwd_data_kernel<", "bwd_data", True),
     (r"qconv_bwd_data_generic_kernel<", "bwd_data", True),
     (r"qconv_bwd_data_wide_kernel<", "bwd_data", True),
@@ -359,7 +358,7 @@ _KERNEL_FAMILY = [
     (r"qconv_bwd_weight_reduce_kernel<", "bwd_weight", False),
     (r"qconv_bwd_weight_reduce2d_kernel<", "bwd_weight", False),
     (r"qconv_bwd_weight_reduce2dv_kernel[<(]", "bwd_weight", False),
-    (r"qconv_pad_channels_kernel<[^,>]+, 1>", "bwd_weight", False),
+    (r"qconv_pad_rows_kernel<", "bwd_weight", False),  # (of these layers only the stem's weight gradient pads)
 ]
 
 
