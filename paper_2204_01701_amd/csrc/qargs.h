@@ -80,7 +80,8 @@ struct FwdArgs {
     FastDiv fd_howo, fd_wo, fd_c, fd_kw, fd_n, fd_cps;
 };
 
-// Stride offsets (phases) the input gradient's kernels tell apart at most.
+// Stride offsets (phases) whose shares of the waves the narrow input gradient's
+// arguments list; past that each phase gets the same share.
 constexpr int kMaxPhases = 64;
 
 // Input gradient: rows = input channels, columns = input pixels,
@@ -105,7 +106,8 @@ struct BwdDataArgs {
     int pm, ops;
     int order;  // block order of the split-K grid (tile_coord)
     // Narrow kernel at stride > 1: the waves are shared out in rounds of `units`,
-    // one per tap of each phase (BwdPhase; at least one); unit_end: their prefix sums.
+    // one per tap of each phase (BwdPhase; at least one); unit_end: their prefix sums
+    // (past kMaxPhases phases: one unit per phase, unit_end unused).
     int units;
     uint16_t unit_end[kMaxPhases];
     FastDiv fd_hw, fd_w, fd_o, fd_kw, fd_sh, fd_sw, fd_n, fd_ops;

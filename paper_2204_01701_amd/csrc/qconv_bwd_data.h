@@ -64,7 +64,8 @@ __global__ __launch_bounds__(kThreads) void qconv_bwd_data_kernel(const BwdDataA
     // position-major); else this tile's phase and its column tile in it.
     const int nph = S1 ? 1 : a.SH * a.SW;
     const int ct = S1 ? tc.ct : tc.ct / nph;
-    const BwdPhase ph(S1 ? 0 : tc.ct - ct * nph, a.H, a.W, a.KH, a.KW, S1 ? 1 : a.SH, S1 ? 1 : a.SW, a.PH, a.PW);
+    const BwdPhase ph = S1 ? BwdPhase(a.H, a.W, a.KH, a.KW, a.PH, a.PW)
+                           : BwdPhase(tc.ct - ct * nph, a.H, a.W, a.KH, a.KW, a.PH, a.PW, a.fd_sh, a.fd_sw);
     const int mp = S1 ? a.M : a.N * ph.hp * ph.wp;  // GEMM columns of the phase
     if (!S1 && ct * BCOL >= mp) return;
     const int KP = S1 ? a.K : ph.rp * ph.qp * a.O;

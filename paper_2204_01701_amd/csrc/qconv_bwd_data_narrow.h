@@ -47,18 +47,26 @@ __global__ __launch_bounds__(kThreads, 2) void qconv_bwd_data_narrow_kernel(cons
     const __amdgpu_buffer_rsrc_t grs[3] = {raw_rsrc(a.gy, gbytes), raw_rsrc(a.ta, gbytes), raw_rsrc(a.tb, gbytes)};
 
     // This wave's phase, its rank among the phase's waves and their number: wave
-    // u of every a.units belongs to the phase with unit_end[phase - 1] <= u < unit_end[phase].
+    // u of every a.units belongs to the phase with unit_end[phase - 1] <= u < unit_end[phase]
+    // (past kMaxPhases phases: to phase u).
     const int nw = gridDim.x * (kThreads / 64);
     const int wid = blockIdx.x * (kThreads / 64) + wave_id();
     int phase = 0, rank = wid, ranks = nw;
     if constexpr (!S1) {
         const int round = wid / a.units, u = wid - round * a.units;
-        while (u >= a.unit_end[phase]) ++phase;  // (u < units = the last phase's end)
-        const int at = phase ? a.unit_end[phase - 1] : 0, n = a.unit_end[phase] - at;
+        int at = u, n = 1;
+        if (a.SH * a.SW <= kMaxPhases) {
+            while (u >= a.unit_end[phase]) ++phase;  // (u < units = the last phase's end)
+            at = phase ? a.unit_end[phase - 1] : 0;
+            n = a.unit_end[phase] - at;
+        } else {
+            phase = u;
+        }
         rank = round * n + u - at;
         ranks = (nw / a.units) * n + min(max(nw % a.units - at, 0), n);
     }
-    const BwdPhase ph(phase, a.H, a.W, a.KH, a.KW, S1 ? 1 : a.SH, S1 ? 1 : a.SW, a.PH, a.PW);
+    const BwdPhase ph = S1 ? BwdPhase(a.H, a.W, a.KH, a.KW, a.PH, a.PW)
+                           : BwdPhase(phase, a.H, a.W, a.KH, a.KW, a.PH, a.PW, a.fd_sh, a.fd_sw);
     const int K = S1 ? a.K : ph.rp * ph.qp * a.O;
     const int mp = S1 ? a.M : a.N * ph.hp * ph.wp;
 

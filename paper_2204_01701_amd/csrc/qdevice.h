@@ -324,27 +324,33 @@ __device__ __forceinline__ TileCoord tile_coord(int bid, int order, int row_tile
 // pixel (h0 + SH hh, w0 + SW ww), hh < hp, ww < wp, and tap (r0 + SH ri,
 // q0 + SW qi), ri < rp, qi < qp, meet at output pixel (oh0 + hh - ri,
 // ow0 + ww - qi).  Phases without pixels or taps have hp, wp, rp or qp 0.
-// (hp and wp serve the host's plan too.)
 struct BwdPhase {
     int h0, w0, hp, wp, r0, q0, rp, qp, oh0, ow0;
-    __host__ __device__ static int first(int phase, int pad, int stride) {  // the first pixel of the phase
-        const int d = (phase - pad) % stride;
-        return d < 0 ? d + stride : d;
-    }
-    __host__ __device__ static int count(int x0, int size, int stride) {
-        return x0 < size ? (size - 1 - x0) / stride + 1 : 0;
-    }
-    __host__ __device__ BwdPhase(int phase, int H, int W, int KH, int KW, int SH, int SW, int PH, int PW) {
-        r0 = phase / SW;
+    // stride 1: the whole map is the one phase
+    __device__ BwdPhase(int H, int W, int KH, int KW, int PH, int PW)
+        : h0(0), w0(0), hp(H), wp(W), r0(0), q0(0), rp(KH), qp(KW), oh0(PH), ow0(PW) {}
+    __device__ BwdPhase(int phase, int H, int W, int KH, int KW, int PH, int PW, const FastDiv &fh, const FastDiv &fw) {
+        const int SW = (int)fw.d;
+        r0 = (int)fdiv((uint32_t)phase, fw);
         q0 = phase - r0 * SW;
-        h0 = first(r0, PH, SH);
-        w0 = first(q0, PW, SW);
-        hp = count(h0, H, SH);
-        wp = count(w0, W, SW);
-        rp = count(r0, KH, SH);
-        qp = count(q0, KW, SW);
-        oh0 = (h0 + PH - r0) / SH;
-        ow0 = (w0 + PW - q0) / SW;
+        h0 = first(r0, PH, fh);
+        w0 = first(q0, PW, fw);
+        hp = count(h0, H, fh);
+        wp = count(w0, W, fw);
+        rp = count(r0, KH, fh);
+        qp = count(q0, KW, fw);
+        oh0 = (int)fdiv((uint32_t)(h0 + PH - r0), fh);  // (never negative)
+        ow0 = (int)fdiv((uint32_t)(w0 + PW - q0), fw);
+    }
+    // the first pixel of the phase: (phase - pad) mod stride
+    __device__ static int first(int phase, int pad, const FastDiv &f) {
+        const int x = pad - phase, s = (int)f.d;
+        if (x <= 0) return -x;  // (phase < stride)
+        const int m = x - (int)fdiv((uint32_t)x, f) * s;
+        return m ? s - m : 0;
+    }
+    __device__ static int count(int x0, int size, const FastDiv &f) {
+        return x0 < size ? (int)fdiv((uint32_t)(size - 1 - x0), f) + 1 : 0;
     }
 };
 

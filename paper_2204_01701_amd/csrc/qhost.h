@@ -488,15 +488,31 @@ struct BwdDataPlan {
     size_t wt_bytes, gpad_bytes, part_bytes, ws_bytes;  // workspace: [weights][G, T_a, T_b padded][split partials]
 };
 
-// At stride > 1 the kernels split the input pixels into phases (BwdPhase): the
-// most taps and the most pixels of any phase.
+// At stride > 1 the kernels split the input pixels into phases (BwdPhase), one
+// per stride offset: the most taps and the most pixels of any phase.
 inline void bwd_phase_extents(const Geom &g, int &taps, int &pixels) {
-    taps = pixels = 0;
-    for (int i = 0; i < g.SH * g.SW; ++i) {
-        const BwdPhase ph(i, g.H, g.W, g.KH, g.KW, g.SH, g.SW, g.PH, g.PW);
-        taps = std::max(taps, ph.rp * ph.qp);
-        pixels = std::max(pixels, g.N * ph.hp * ph.wp);
-    }
+    taps = cdiv(g.KH, g.SH) * cdiv(g.KW, g.SW);
+    pixels = g.N * cdiv(g.H, g.SH) * cdiv(g.W, g.SW);
+}
+
+// Whether a strided layer takes the phases: up to kMaxPhases, or one for each
+// wave of the narrow kernel, always.  Past that where their tiles (at least one
+// per phase, its ramp priced at four K steps) and K steps, spread over the CUs,
+// take no longer than the register-staged kernel, in which every pixel meets
+// every tap and a step takes about four times as long.  us per call in the
+// register-staged kernel and by phases, bf16: 16 x 16 patches at stride 16, 32 x 224 x 224
+// maps of 8 channels -> 768, 1190000 and 963; 3 x 3 at stride 100, 2 x 300 x 300, 64 ->
+// 64, 513 and 72; 1 x 1 at stride 32, 4 x 128 x 128, 64 -> 64, 29 and 10.
+inline bool bwd_phased(const Geom &g, int Op) {
+    const long long P = (long long)g.SH * g.SW, M = (long long)g.N * g.H * g.W;
+    if (P <= std::max(kMaxPhases, narrow_waves(M))) return true;
+    int taps, pixels;
+    bwd_phase_extents(g, taps, pixels);
+    const long long tiles = cdiv(pixels, 128), whole = cdiv(M, 128);
+    const long long steps = (long long)g.KH * g.KW * cdiv(Op, 64 / (int)g.esize());
+    auto rounds = [](long long work) { return (work + kNumCUs - 1) / kNumCUs; };
+    return P <= (1 << 20) / tiles &&
+           4 * rounds(P * tiles) + rounds(tiles * steps) <= 4 * (4 * rounds(whole) + rounds(whole * steps));
 }
 
 inline BwdDataPlan plan_bwd_data(const Geom &g) {
@@ -525,16 +541,14 @@ inline BwdDataPlan plan_bwd_data(const Geom &g) {
             return p;
         }
     }
-    p.pad = g.pad_o();
+    p.s1 = g.SH == 1 && g.SW == 1;
+    const bool phases = !p.s1 && bwd_phased(g, g.opad());
+    p.pad = g.pad_o() && (p.s1 || phases);  // (the register-staged kernel takes the maps as they are)
     p.Op = p.pad ? g.opad() : g.O;
     if (p.pad) p.gpad_bytes = align_up((size_t)g.N * g.HO * g.WO * p.Op * g.esize());
     const size_t gpads = om_gmaps(g.om()) * p.gpad_bytes;
-    p.s1 = g.SH == 1 && g.SW == 1;
     const int M = g.N * g.H * g.W;
     int taps = g.KH * g.KW, phase_pixels = M;  // of one phase (stride 1: the whole map)
-    // (a phase per stride offset: past kMaxPhases the register-staged kernel,
-    // which gathers each tap's pixel)
-    const bool phases = !p.s1 && (long long)g.SH * g.SW <= kMaxPhases;
     if (phases) bwd_phase_extents(g, taps, phase_pixels);
     const int K = taps * p.Op;
     p.veck = p.Op % g.vec() == 0 && (p.s1 || phases);
@@ -542,6 +556,7 @@ inline BwdDataPlan plan_bwd_data(const Geom &g) {
     p.cb = cdiv(g.C, 16);
     p.nch = cdiv(K, 4 * g.vec());
     if (p.veck && g.ne == NEURON_QUADRA && g.C % 4 == 0 && p.cb == 1 && p.nch <= 9 &&
+        (p.s1 || (long long)g.SH * g.SW <= std::max(kMaxPhases, narrow_waves(M))) &&  // (a wave per phase)
         narrow_fits(g, g.C, p.Op) && env_override("QLAYER_BWD_DATA_NARROW", 1) != 0) {
         p.narrow = true;
         p.splits = 1;

@@ -106,12 +106,15 @@ ql_status launch_bwd_data(const Geom &g, const BwdDataPlan &p, const void *gy, c
     a.fd_ops = make_fastdiv(a.ops);
     a.order = p.order;
     if (p.narrow) {
-        if (!p.s1)
+        if (!p.s1 && g.SH * g.SW > kMaxPhases) {
+            a.units = g.SH * g.SW;
+        } else if (!p.s1) {
+            auto taps = [](int first, int size, int stride) { return first < size ? (size - 1 - first) / stride + 1 : 0; };
             for (int i = 0; i < g.SH * g.SW; ++i) {
-                const BwdPhase ph(i, g.H, g.W, g.KH, g.KW, g.SH, g.SW, g.PH, g.PW);
-                a.units += std::max(ph.rp * ph.qp, 1);
+                a.units += std::max(taps(i / g.SW, g.KH, g.SH) * taps(i % g.SW, g.KW, g.SW), 1);
                 a.unit_end[i] = (uint16_t)a.units;
             }
+        }
         // (a whole round of units, so that every phase of a strided layer has a wave)
         const dim3 grid((unsigned)(cdiv(std::max(narrow_waves(a.M), a.units), kThreads / 64)));
 #define QL_BD_NARROW(CB, NCH)                                                                                        \

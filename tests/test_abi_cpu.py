@@ -370,3 +370,19 @@ def test_relu_backward_validation(L):
     needl = L.qlayer_linear_bwd_relu_workspace_size(ctypes.byref(dl))
     assert needl >= 64 * 48 * 4
     assert L.qlayer_linear_bwd_relu(ctypes.byref(dl), *no_y, FAKE, needl, None) == QL_EINVAL
+
+
+@pytest.mark.parametrize("patch,hw", [(8, 224), (16, 224), (9, 225)])
+def test_patch_layers_keep_the_tiled_input_gradient(L, patch, hw):
+    """A bf16 layer with filter = stride and channels on the vector reads its weights
+    where they are, however many stride offsets there are: the tiled kernels need
+    no transposed copy of the weights (the register-staged one does)."""
+    d = ql.conv_desc(32, 16, hw, hw, 768, patch, patch, patch, 0, ql.QL_BF16)
+    assert ql.qlayer_conv2d_bwd_data_workspace_size(d) == 0
+
+
+def test_register_staged_input_gradient_needs_no_padded_maps(L):
+    """A 1 x 1 filter at stride 70 on one 70 x 70 image takes the kernel that gathers:
+    transposed weights (3 x 301 x 1500 fp32) and no copies of G, T_a, T_b."""
+    d = ql.conv_desc(1, 1500, 70, 70, 301, 1, 1, 70, 0, ql.QL_F32)
+    assert ql.qlayer_conv2d_bwd_data_workspace_size(d) <= 3 * 301 * 1500 * 4 + 256

@@ -2,8 +2,9 @@
 meets only the taps of its stride offset): maps that the strides do not
 divide, strides that differ, phases without taps (a filter smaller than the
 stride) or without pixels (a map smaller than it), split-K, the narrow kernel
-(C <= 16), padded channels, and a stride with too many phases, against the
-fp64 oracle element by element."""
+(C <= 16), padded channels, strides with more phases than the narrow kernel's
+arguments list, and one with too many, against the fp64 oracle element by
+element."""
 import numpy as np
 import pytest
 import torch
@@ -28,7 +29,11 @@ SHAPES = [
     (1, 8, 1, 6, 32, 3, (2, 2), 1),       # phases without pixels
     (4, 256, 5, 5, 256, 3, (2, 2), 1),    # split-K
     (16, 20, 9, 9, 30, 3, (2, 2), 1),     # O off the vector: padded copies
-    (1, 16, 20, 20, 16, 9, (9, 9), 0),    # 81 phases: the register-staged kernel
+    (1, 16, 20, 20, 16, 9, (9, 9), 0),    # narrow, 81 phases, 25 pixels each or fewer
+    (8, 16, 45, 38, 32, 9, (10, 9), 3),   # narrow, 90 phases, some without taps
+    (3, 40, 33, 20, 48, 10, (10, 10), 1), # tiles, 100 phases
+    (1, 72, 12, 30, 64, 5, (5, 17), 2),   # tiles, 85 phases, most without taps or with few pixels
+    (1, 24, 70, 70, 30, 1, (70, 70), 0),  # a filter much smaller than the stride: the register-staged kernel
 ]
 
 
