@@ -811,8 +811,31 @@ inline void pad_segment(PadSegments &sg, int &n, const void *src, void *dst, lon
 template <typename T>
 inline ql_status launch_pad(const PadSegments &sg, int n, hipStream_t st) {
     uint32_t most = 0;
-    for (int i = 0; i < n; ++i) most = std::max(most, sg.total[i]);
-    hipLaunchKernelGGL((qconv_pad_rows_kernel<T>), dim3(grid_1d(most), n), dim3(kThreads), 0, st, sg);
+    int c = sg.c[0];  // the channel count of every tensor, if they agree and it is below one vector
+    for (int i = 0; i < n; ++i) {
+        most = std::max(most, sg.total[i]);
+        if (sg.c[i] != c || sg.c[i] >= Elem<T>::VEC) c = 0;
+    }
+    const dim3 grid(grid_1d(most), n), block(kThreads);
+#define QL_PAD_SHORT(C)                                                                                   \
+    case C:                                                                                               \
+        if constexpr (C < Elem<T>::VEC) {                                                                 \
+            hipLaunchKernelGGL((qconv_pad_short_rows_kernel<T, C>), grid, block, 0, st, sg);              \
+            return hip_status();                                                                          \
+        }                                                                                                 \
+        break
+    switch (c) {
+        QL_PAD_SHORT(1);
+        QL_PAD_SHORT(2);
+        QL_PAD_SHORT(3);
+        QL_PAD_SHORT(4);
+        QL_PAD_SHORT(5);
+        QL_PAD_SHORT(6);
+        QL_PAD_SHORT(7);
+        default: break;
+    }
+#undef QL_PAD_SHORT
+    hipLaunchKernelGGL((qconv_pad_rows_kernel<T>), grid, block, 0, st, sg);
     return hip_status();
 }
 

@@ -24,7 +24,7 @@ SHAPES = [
     (2, 60, 1, 1, 10, 1, 1, 0),     # too little work to pay for the copies: the register-staged kernels
     (4, 16, 7, 7, 130, 1, 1, 0),    # C on the vector, O past one 128-row tile
     (5, 131, 4, 4, 64, 3, 1, 1),    # O on the vector, few pixels: split-K
-]
+] + [(3, c, 6, 5, 24, 3, 1, 1) for c in (1, 2, 3, 5, 6, 7)]  # rows below one vector (fp32: up to 3)
 CASES = [(0, s) for s in SHAPES] + [(n, (2, 33, 5, 6, 33, 3, 1, 1)) for n in (T4, T4I, T3, T2, T24)]
 
 
