@@ -726,16 +726,32 @@ inline BwdWeightPlan plan_bwd_weight(const Geom &g, size_t max_split_bytes = kMa
     // four steps per wave, the partial sums within max_split_bytes.  (16 -> 16
     // channels, 3 x 3, us at four steps per wave everywhere and now: 64 x 16 x 16
     // maps fp32 22.6 -> 17.8, bf16 18.6 -> 15.1; 16 x 8 x 8 maps fp32 22.4 -> 14.)
+    // Below 16 splits the reduction adds them one after the other in each thread,
+    // 2 us and 0.3 for each, which few steps do not pay for: there the count that
+    // the measured step times make the fastest, one included.  (us at one step
+    // per wave and now, bf16: 3 -> 16, 3 x 3, 4 x 9 x 9 maps 14.9, 13.2; 16 -> 16, 1 x 1,
+    // 768 pixels 7.9, 6.7; 8 -> 8, 3 x 3, 1024 pixels 12.3, 11.4.)
     p.nf = cdiv(KP, 16);
     p.few = p.padc && !p.pado && g.C < 2 * g.vec() && (g.dt == QL_BF16 || narrow_shape);
     if (narrow_shape && narrow_fits(g, p.Cp, p.Op)) {
         p.narrow = true;
         p.nob = cdiv(p.Op, 16);
         p.stages_total = cdiv(M, g.dt == QL_BF16 ? 32 : 16);
-        // (one workgroup up to two steps per wave: a reduction would cost what it saves)
-        int splits = p.stages_total <= 8 ? 1 : std::max(cdiv(p.stages_total, 16),
-                                                        std::min(cdiv(kNumCUs, p.nob), cdiv(p.stages_total, 4)));
+        int splits = std::max(cdiv(p.stages_total, 16), std::min(cdiv(kNumCUs, p.nob), cdiv(p.stages_total, 4)));
         splits = std::min(std::max(1, 2 * kNumCUs / p.nob), splits);
+        if (splits < 16) {
+            const double step = g.dt == QL_BF16 ? 0.1 * p.nf + 0.3 : 0.22 * p.nf + 0.25;  // us, one step of a wave
+            double best = step * cdiv(p.stages_total, 4);
+            const int most = splits;
+            splits = 1;
+            for (int s = 2; s <= most; ++s) {
+                const double t = step * cdiv(p.stages_total, 4 * s) + 2.0 + 0.3 * s;
+                if (t < best) {
+                    best = t;
+                    splits = s;
+                }
+            }
+        }
         splits = env_override("QLAYER_BWD_WEIGHT_NARROW_SPLITS", splits);
         splits = std::max(1, std::min(splits, (int)std::max<size_t>(1, max_split_bytes / bytes_per_split)));
         p.sps = cdiv(p.stages_total, splits);

@@ -386,3 +386,12 @@ def test_register_staged_input_gradient_needs_no_padded_maps(L):
     transposed weights (3 x 301 x 1500 fp32) and no copies of G, T_a, T_b."""
     d = ql.conv_desc(1, 1500, 70, 70, 301, 1, 1, 70, 0, ql.QL_F32)
     assert ql.qlayer_conv2d_bwd_data_workspace_size(d) <= 3 * 301 * 1500 * 4 + 256
+
+
+@pytest.mark.parametrize("shape", [(4, 3, 9, 16, 3), (2, 16, 8, 16, 3), (12, 16, 8, 16, 1)])
+def test_narrow_weight_gradient_of_few_pixels_is_one_workgroup(L, shape):
+    """So few pixels that a second launch would cost more than the steps it saves: no
+    partial sums, the workspace holds the padded copy of X at most."""
+    n, c, hw, o, k = shape
+    d = ql.conv_desc(n, c, hw, hw, o, k, k, 1, k // 2, ql.QL_BF16)
+    assert ql.qlayer_conv2d_bwd_weight_workspace_size(d) <= (n * hw * hw * 16 + 255 if c % 8 else 0)
