@@ -95,18 +95,68 @@ struct Geom {
     // Not for layers of a few million flops and less, where a pass is about the
     // launches and the copy is one more (a dense layer of 4 rows, 16 -> 73,
     // called from Python: 38 us for the three passes as it is, 45 padded); few
-    // input channels (below two vectors) are always padded, as one copied vector
-    // per pixel and tap is what the pipelined kernels need there.
+    // input channels (below two vectors) are always padded in the forward, as one
+    // copied vector per pixel and tap is what the pipelined kernels need there.
     int cpad() const { return (C + vec() - 1) / vec() * vec(); }
     int opad() const { return (O + vec() - 1) / vec() * vec(); }
-    bool pad_pays() const { return 6.0 * N * HO * WO * KH * KW * (double)C * O >= 2e6; }
-    bool pad_c() const {
-        return C % vec() != 0 && (C < 2 * vec() || pad_pays()) && (long long)N * H * W * cpad() <= kMaxElems &&
-               3LL * O * KH * KW * cpad() <= kMaxElems;
+    double flops() const { return 2.0 * terms() * N * HO * WO * KH * KW * (double)C * O; }  // of a pass
+    bool pad_pays() const { return 6.0 * N * HO * WO * KH * KW * (double)C * O >= 2e6; }  // (counted at three terms)
+    bool few_c() const { return C < 2 * vec(); }
+    bool pad_c_fits() const {
+        return C % vec() != 0 && (long long)N * H * W * cpad() <= kMaxElems && 3LL * O * KH * KW * cpad() <= kMaxElems;
     }
-    bool pad_o() const {
-        return O % vec() != 0 && pad_pays() && (long long)N * HO * WO * opad() <= kMaxElems &&
-               3LL * C * KH * KW * opad() <= kMaxElems;
+    bool pad_o_fits() const {
+        return O % vec() != 0 && (long long)N * HO * WO * opad() <= kMaxElems && 3LL * C * KH * KW * opad() <= kMaxElems;
+    }
+    // A filter smaller than its stride reads few of the pixels that the copy of X
+    // moves: not where the copy is large and the layer's work is not (1 x 1 / 4,
+    // 227 x 60 x 60 maps, 204 -> 116, bf16: forward 112 us as it is, 171 padded).
+    bool pad_x_skips() const {
+        const double bytes = (double)N * H * W * cpad() * esize();
+        return SH > KH && SW > KW && bytes > 1e7 && flops() < 64 * bytes;
+    }
+    // The passes' lines, from 5000 layers of random sizes timed both ways (for each
+    // line the geometric mean of time as it is over time padded, below and above).
+    // Forward: a reduction of one K step of the pipelined kernels onto 16
+    // channels or fewer is as fast in the register-staged kernel (175 x 22 x 22, 25 -> 6,
+    // 1 x 1, bf16: 13.5 us, 14.5 padded).  The types with fewer matrix products
+    // gain less from the fp32 pipeline: only a reduction of 48 to 256, or 1 GFLOP
+    // (0.77 and 0.99 outside, 1.15 and 1.35 inside).
+    bool pad_fwd() const {
+        if (!pad_c_fits() || few_c()) return pad_c_fits();
+        if (!pad_pays() || pad_x_skips()) return false;
+        const int K = KH * KW * C;
+        if (dt == QL_BF16 || ne == NEURON_QUADRA) return K > 64 / (int)esize() || O > 16;
+        return flops() >= 1e9 || (K > 48 && K <= 256);
+    }
+    // Input gradient: where the reduction over the output channels is a step or
+    // two, the copies cost what they save on all but the proposed neuron in
+    // bf16 (dense 1612 x 308 -> 10, T2, fp32: 8.3 us, 12.7 padded; 104 x 35 x 35, 48 -> 14, 1 x 1 / 2,
+    // fp32: 26.5, 36.5; bf16 0.97 below, 1.9 above; fp32, other types, 0.80 and 1.3).
+    bool pad_bwd_data() const {
+        if (!pad_o_fits() || !pad_pays()) return false;
+        const bool s1 = SH == 1 && SW == 1;
+        const int K = KH * KW * O;
+        const long long px = (long long)N * H * W;
+        const double bytes = (double)om_gmaps(om()) * N * HO * WO * opad() * esize();
+        if (dt == QL_BF16)
+            return ne == NEURON_QUADRA || K > 40 || flops() >= 5e7 || (C <= 64 && (!s1 || px >= 4096));
+        if (ne == NEURON_QUADRA) return !(K <= 48 && bytes > 3.3e5 && s1) && !(K <= 16 && bytes > 3e6);
+        return K > 40 && (flops() >= 1e9 || !s1 || px >= 2048 || C <= 64);
+    }
+    // Weight gradient: the fp32 pipelined kernels gain little over the
+    // register-staged one and take a copy and a reduction more, so in fp32 only
+    // from 0.3 GFLOP or 20000 pixels (64 -> 5, 8 x 6 x 6 maps, 3 x 3: 10.5 us as it is, 15.6
+    // padded; 0.83 below, 1.35 above), the narrow kernel from 32 MFLOP (0.96 and 2.0).
+    bool pad_bwd_weight(bool narrow) const {
+        if (!(C % vec() == 0 || pad_c_fits()) || !(O % vec() == 0 || pad_o_fits())) return false;
+        const bool offc = C % vec() != 0, offo = O % vec() != 0;
+        if (!offc && !offo) return false;
+        if (offo || !few_c()) {
+            if (!pad_pays() || (offc && pad_x_skips())) return false;
+        }
+        if (dt == QL_BF16 || (narrow && offc && few_c() && !offo)) return true;
+        return flops() >= (narrow ? 3.2e7 : 3e8) || (long long)N * HO * WO >= 20000;
     }
 };
 
@@ -316,7 +366,7 @@ inline FwdPlan plan_fwd(const Geom &g) {
         p.splits = 1;
         return p;
     }
-    p.pad = g.pad_c();
+    p.pad = g.pad_fwd();
     p.Cp = p.pad ? g.cpad() : g.C;
     const int M = g.N * g.HO * g.WO, K = g.KH * g.KW * p.Cp;
     p.veck = p.Cp % g.vec() == 0;
@@ -543,7 +593,7 @@ inline BwdDataPlan plan_bwd_data(const Geom &g) {
     }
     p.s1 = g.SH == 1 && g.SW == 1;
     const bool phases = !p.s1 && bwd_phased(g, g.opad());
-    p.pad = g.pad_o() && (p.s1 || phases);  // (the register-staged kernel takes the maps as they are)
+    p.pad = g.pad_bwd_data() && (p.s1 || phases);  // (the register-staged kernel takes the maps as they are)
     p.Op = p.pad ? g.opad() : g.O;
     if (p.pad) p.gpad_bytes = align_up((size_t)g.N * g.HO * g.WO * p.Op * g.esize());
     const size_t gpads = om_gmaps(g.om()) * p.gpad_bytes;
@@ -689,23 +739,22 @@ inline BwdWeightPlan plan_bwd_weight(const Geom &g, size_t max_split_bytes = kMa
     // the narrow kernel: rows k' of at most 144 (after the channel padding)
     const bool f32_pipe = g.ne == NEURON_QUADRA && env_override("QLAYER_BWD_WEIGHT_F32_PIPE", 1) != 0;
     may_pad = may_pad && (g.dt == QL_BF16 || f32_pipe);
-    p.padc = may_pad && g.pad_c();
-    p.pado = may_pad && g.pad_o();
-    p.Cp = p.padc ? g.cpad() : g.C;
-    p.Op = p.pado ? g.opad() : g.O;
-    p.veck = p.Cp % g.vec() == 0 && p.Op % g.vec() == 0;
-    if (!p.veck) {  // (one of the two cannot be padded: neither)
-        p.padc = p.pado = false;
-        p.Cp = g.C;
-        p.Op = g.O;
-    }
     // (wider layers, up to 64 channels, in 16-channel slices, one per workgroup row of the
     // grid: by default in fp32, where the 16 -> 32-channel stride-2 CIFAR ResNet layer
     // measured 37 against 66 us per call; in bf16 it and the VGG-16 stem were no faster)
     const int narrow_max_o = env_override("QLAYER_BWD_WEIGHT_NARROW_MAXO", g.dt == QL_F32 ? 64 : 16);
-    const bool narrow_shape = g.ne == NEURON_QUADRA && (p.Op <= 16 || (p.Op % 16 == 0 && p.Op <= narrow_max_o)) &&
-                              p.veck && cdiv(g.KH * g.KW * p.Cp, 16) <= 9 &&
-                              env_override("QLAYER_BWD_WEIGHT_NARROW", 1) != 0;
+    auto narrow_dims = [&](int Cp, int Op) {
+        return g.ne == NEURON_QUADRA && (Op <= 16 || (Op % 16 == 0 && Op <= narrow_max_o)) && Cp % g.vec() == 0 &&
+               Op % g.vec() == 0 && cdiv(g.KH * g.KW * Cp, 16) <= 9 && narrow_fits(g, Cp, Op) &&
+               env_override("QLAYER_BWD_WEIGHT_NARROW", 1) != 0;
+    };
+    const bool pad = may_pad && g.pad_bwd_weight(narrow_dims(g.cpad(), g.opad()));
+    p.padc = pad && g.C % g.vec() != 0;
+    p.pado = pad && g.O % g.vec() != 0;
+    p.Cp = p.padc ? g.cpad() : g.C;
+    p.Op = p.pado ? g.opad() : g.O;
+    p.veck = p.Cp % g.vec() == 0 && p.Op % g.vec() == 0;
+    const bool narrow_shape = narrow_dims(p.Cp, p.Op);
     const int M = g.N * g.HO * g.WO, KP = g.KH * g.KW * p.Cp, KPO = g.KH * g.KW * g.C;
     // pipelined kernels: bf16 every neuron type; fp32 the proposed neuron (the 16 x 16 kernel's fp32 form)
     p.pipe = p.veck && (g.dt == QL_BF16 || f32_pipe);
@@ -733,7 +782,7 @@ inline BwdWeightPlan plan_bwd_weight(const Geom &g, size_t max_split_bytes = kMa
     // 768 pixels 7.9, 6.7; 8 -> 8, 3 x 3, 1024 pixels 12.3, 11.4.)
     p.nf = cdiv(KP, 16);
     p.few = p.padc && !p.pado && g.C < 2 * g.vec() && (g.dt == QL_BF16 || narrow_shape);
-    if (narrow_shape && narrow_fits(g, p.Cp, p.Op)) {
+    if (narrow_shape) {
         p.narrow = true;
         p.nob = cdiv(p.Op, 16);
         p.stages_total = cdiv(M, g.dt == QL_BF16 ? 32 : 16);

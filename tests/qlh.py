@@ -182,3 +182,12 @@ def check_elementwise(name: str, kind: str, got, ref, mag, bf16: bool, K: int) -
     assert r <= 1.0, (f"{name}: element {np.unravel_index(worst, ratio.shape)} off by "
                       f"{err.reshape(-1)[worst]:.3e} > bound {bound.reshape(-1)[worst]:.3e}")
     return r
+
+
+def kernel_names(fn):
+    """Names of the device kernels that fn() launches (empty where the profiler records none)."""
+    from torch.profiler import ProfilerActivity, profile
+    with profile(activities=[ProfilerActivity.CUDA]) as prof:
+        fn()
+        torch.cuda.synchronize()
+    return [e.name for e in prof.events() if e.device_type == torch.autograd.DeviceType.CUDA]
