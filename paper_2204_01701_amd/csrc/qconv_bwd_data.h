@@ -252,8 +252,16 @@ __global__ __launch_bounds__(kThreads) void qconv_bwd_data_kernel(const BwdDataA
             }
             return;
         }
+        // The predicates are bitwise, so that the K loop stays one block and its MFMAs
+        // interleave (as && the compiler branches around them: 72 -> 81 us in fp32 on 32 -> 32
+        // channels, 256 x 16 x 16 maps); not in the 128 x 128 tiles of natural weights, which run
+        // faster with the branches (488 -> 504 channels, 71 x 10 x 10, 3 x 3: 172 us, 194 bitwise;
+        // the 128 x 64 tiles of 128 -> 88, 64 x 16 x 16, 3 x 3 / 2: 14.1, 12.8).
+        constexpr bool LAZY = NATW && BR == 128 && BCOL == 128;
         const int k = s * KE + kcol * VEC;
-        const bool kin = live & (k < KP);
+        bool kin;
+        if constexpr (LAZY) kin = live && k < KP;
+        else kin = live & (k < KP);
         const int tap = (int)fdiv((uint32_t)k, a.fd_o);
         const int o = k - tap * a.O;
         const int r = tap_row(tap);
@@ -266,7 +274,9 @@ __global__ __launch_bounds__(kThreads) void qconv_bwd_data_kernel(const BwdDataA
                 const int kr = s * KE + row;
                 int tapr = (int)fdiv((uint32_t)kr, a.fd_o);
                 const int orow = kr - tapr * a.O;
-                const bool ok = live & wc_ok & (kr < KP) & (t < 3);
+                bool ok;
+                if constexpr (LAZY) ok = live && wc_ok && kr < KP && t < 3;
+                else ok = live & wc_ok & (kr < KP) & (t < 3);
                 if constexpr (!S1) {
                     const int ri = tap_row(tapr);
                     tapr = wtap(ri, tapr - ri * QP);
@@ -285,10 +295,9 @@ __global__ __launch_bounds__(kThreads) void qconv_bwd_data_kernel(const BwdDataA
 #pragma unroll
         for (int j = 0; j < NIP; ++j) {
             const int hi = hh[j] - r, wi = ww[j] - q;
-            // (bitwise: as && the compiler branched around it, which split the K loop's
-            // block and kept its MFMAs from interleaving, 72 -> 81 us in fp32 on 32 -> 32
-            // channels, 256 x 16 x 16 maps)
-            const bool ok = ((unsigned)hi < (unsigned)a.HO) & ((unsigned)wi < (unsigned)a.WO) & kin & (goff[j] >= 0);
+            bool ok;
+            if constexpr (LAZY) ok = (unsigned)hi < (unsigned)a.HO && (unsigned)wi < (unsigned)a.WO && kin && goff[j] >= 0;
+            else ok = ((unsigned)hi < (unsigned)a.HO) & ((unsigned)wi < (unsigned)a.WO) & kin & (goff[j] >= 0);
             const int p = goff[j] + (hi * a.WO + wi) * a.O + o;
 #pragma unroll
             for (int u = 0; u < NGM; ++u)
