@@ -108,12 +108,12 @@ struct Geom {
     bool pad_o_fits() const {
         return O % vec() != 0 && (long long)N * HO * WO * opad() <= kMaxElems && 3LL * C * KH * KW * opad() <= kMaxElems;
     }
-    // A filter smaller than its stride reads few of the pixels that the copy of X
-    // moves: not where the copy is large and the layer's work is not (1 x 1 / 4,
+    // Where the filter reads less than a tenth of the pixels that the copy of X
+    // moves: not if the copy is large and the layer's work is not (1 x 1 / 4,
     // 227 x 60 x 60 maps, 204 -> 116, bf16: forward 112 us as it is, 171 padded).
     bool pad_x_skips() const {
         const double bytes = (double)N * H * W * cpad() * esize();
-        return SH > KH && SW > KW && bytes > 1e7 && flops() < 64 * bytes;
+        return 10.0 * KH * KW * HO * WO < (double)H * W && bytes > 3e7 && flops() < 64 * bytes;
     }
     // The passes' lines, from 5000 layers of random sizes timed both ways (for each
     // line the geometric mean of time as it is over time padded, below and above).
@@ -121,7 +121,7 @@ struct Geom {
     // channels or fewer is as fast in the register-staged kernel (175 x 22 x 22, 25 -> 6,
     // 1 x 1, bf16: 13.5 us, 14.5 padded).  The types with fewer matrix products
     // gain less from the fp32 pipeline: only a reduction of 48 to 256, or 1 GFLOP
-    // (0.77 and 0.99 outside, 1.15 and 1.35 inside).
+    // (0.76 up to 48, 1.0 to 1.15 up to 256, 0.96 above; 1.35 from 1 GFLOP).
     bool pad_fwd() const {
         if (!pad_c_fits() || few_c()) return pad_c_fits();
         if (!pad_pays() || pad_x_skips()) return false;
@@ -132,7 +132,8 @@ struct Geom {
     // Input gradient: where the reduction over the output channels is a step or
     // two, the copies cost what they save on all but the proposed neuron in
     // bf16 (dense 1612 x 308 -> 10, T2, fp32: 8.3 us, 12.7 padded; 104 x 35 x 35, 48 -> 14, 1 x 1 / 2,
-    // fp32: 26.5, 36.5; bf16 0.97 below, 1.9 above; fp32, other types, 0.80 and 1.3).
+    // fp32: 26.5, 36.5; bf16, other types, 0.91 to 1.0 below, 1.8 above; fp32, proposed
+    // neuron, 0.89 to 1.08 and 1.3 to 2; other types 0.73 to 0.93 and 1.0 to 1.55).
     bool pad_bwd_data() const {
         if (!pad_o_fits() || !pad_pays()) return false;
         const bool s1 = SH == 1 && SW == 1;
@@ -141,13 +142,14 @@ struct Geom {
         const double bytes = (double)om_gmaps(om()) * N * HO * WO * opad() * esize();
         if (dt == QL_BF16)
             return ne == NEURON_QUADRA || K > 40 || flops() >= 5e7 || (C <= 64 && (!s1 || px >= 4096));
-        if (ne == NEURON_QUADRA) return !(K <= 48 && bytes > 3.3e5 && s1) && !(K <= 16 && bytes > 3e6);
+        if (ne == NEURON_QUADRA) return C <= 32 || (!(K <= 48 && bytes > 3.3e5 && s1) && !(K <= 16 && bytes > 3e6));
         return K > 40 && (flops() >= 1e9 || !s1 || px >= 2048 || C <= 64);
     }
     // Weight gradient: the fp32 pipelined kernels gain little over the
     // register-staged one and take a copy and a reduction more, so in fp32 only
     // from 0.3 GFLOP or 20000 pixels (64 -> 5, 8 x 6 x 6 maps, 3 x 3: 10.5 us as it is, 15.6
-    // padded; 0.83 below, 1.35 above), the narrow kernel from 32 MFLOP (0.96 and 2.0).
+    // padded; 0.68 to 0.94 below, 1.05 to 1.45 above), the narrow kernel from 32 MFLOP
+    // (0.84 to 1.05 and 0.98 to 3.7).
     bool pad_bwd_weight(bool narrow) const {
         if (!(C % vec() == 0 || pad_c_fits()) || !(O % vec() == 0 || pad_o_fits())) return false;
         const bool offc = C % vec() != 0, offo = O % vec() != 0;
