@@ -57,10 +57,14 @@ constexpr double kPipeRound = 1.5;
 // the MFMAs of a 64-channel step), in the same units (measured on the same
 // layers: 1.2 reproduces where it is the fastest of the three kernels).
 constexpr double kFatStep = 1.2;
-// ... one of the 64 x 64 tile: over 30 bf16 shapes from 4 x 4 maps to the VGG-16
-// layers the geometric mean of the weight gradients was 22.0 us at 0.6 and 0.8, 21.2
-// at 0.7 (without this tile on the small ones 22.6; everywhere 23.0).
-constexpr double kSmallStep = 0.7;
+// A tile's ramp (first loads, epilogue) in K steps, for the choice between tiles;
+// the split counts are searched without it.  Fitted on 1200 layers of random
+// sizes timed in every tile: weight gradients in the tile chosen 0.4 % slower than in
+// the best (geometric mean; 1.0 % without the ramps, 13 of 630 bf16 layers more than 6 %
+// slower than before the 64 x 64 tile was weighed at all, 4 with them), fp32 input
+// gradients 0.5 % (1.1 %), fp32 forwards 0.2 %.
+constexpr double kBwRamp = 8.0, kBwRampSmall = 4.0, kSmallStep = 0.9;  // weight gradient; its 64 x 64 tile (and that tile's step)
+constexpr double kBdRampF32 = 1.0, kFwdRampF32 = 0.5;
 
 // Tuning override: QLAYER_<NAME>=<int> replaces a planner choice (for sweeps).
 inline int env_override(const char *name, int dflt) {
@@ -209,13 +213,14 @@ inline ql_status linear_geom(const ql_linear_desc *d, Geom &g) {
 // partial sums and the reduction.  A count that leaves a few CUs with a second
 // workgroup in the last round costs a whole shared round, which the search
 // avoids.  At least min_stages K steps per split, at most kMaxSplitBytes of
-// partial sums (bytes_per_split each).
+// partial sums (bytes_per_split each).  Returns the modelled time, a ramp of
+// `ramp` steps per round added.
 inline double plan_splits(int tiles, int stages_total, int min_stages, size_t bytes_per_split, int slots, int &splits,
                           int &sps, double step_scale, size_t max_bytes = kMaxSplitBytes, int pipes = 1,
-                          double shared_round = kSharedRound, double step_cost = 1.0) {
+                          double shared_round = kSharedRound, double step_cost = 1.0, double ramp = 0.0) {
     const int cap_bytes = (int)std::max<size_t>(1, max_bytes / std::max<size_t>(bytes_per_split, 1));
     const int s_max = std::max(1, std::min(stages_total / std::max(min_stages, 1), cap_bytes));
-    double best = 0.0;
+    double best = 0.0, cost = 0.0;
     splits = 1;
     // Each partition once, by its K steps per split: cdiv(stages_total, per - 1) is
     // the next count whose splits are shorter (at most 2 sqrt(stages_total) of
@@ -229,17 +234,21 @@ inline double plan_splits(int tiles, int stages_total, int min_stages, size_t by
         double rounds = (double)full * (slots > 1 ? shared_round : 1.0);
         if (rest > 0) rounds += rest > kNumCUs ? shared_round : 1.0;
         double t = per * rounds * step_cost;
-        if (pipes > 1) t = (double)cdiv(per, pipes) * (double)(full + (rest > 0)) * kPipeRound;
+        if (pipes > 1) {
+            rounds = (double)(full + (rest > 0));
+            t = (double)cdiv(per, pipes) * rounds * kPipeRound;
+        }
         if (eff > 1) t += ((double)eff * bytes_per_split * 2.0 / kBytesPerStep + kReduceSteps) / step_scale;
         if (s == 1 || t < best) {
             best = t;
+            cost = t + ramp * rounds;
             splits = eff;
         }
         if (per == 1) break;
     }
     sps = cdiv(stages_total, splits);
     splits = cdiv(stages_total, sps);
-    return best;
+    return cost;
 }
 
 // Taps (r, q) in bounds for output position pos = (oh, ow): a bit mask.
@@ -438,7 +447,7 @@ inline FwdPlan plan_fwd(const Geom &g) {
         p.stat_parts = p.col_tiles;
         return plan_splits(p.row_tiles * p.col_tiles, kst, min_stages, (size_t)3 * M * g.O * 4, p.slots, p.splits,
                            p.sps, step_scale(g), kMaxSplitBytes, 1, kSharedRoundFwd,
-                           (g.dt == QL_F32 ? kFwdStepF32 : kFwdStepBf16)[cfg]);
+                           (g.dt == QL_F32 ? kFwdStepF32 : kFwdStepBf16)[cfg], g.dt == QL_F32 ? kFwdRampF32 : 0.0);
     };
     // The 32-row tile where it leaves fewer empty rows or, on small outputs, fewer
     // idle CUs.  us per call (64-row against 32-row): 32 -> 32 channels, 256 x 16 x
@@ -465,16 +474,25 @@ inline FwdPlan plan_fwd(const Geom &g) {
     // 1024 where there are at most 80 of the 64 x 128 tiles, whether or not they
     // would split (448 -> 256 channels, 3 x 9 x 9 maps, 3 x 3: 24.1 us tiled, 14.3 here;
     // a dense layer of 1024 rows, 512 -> 512: 12.7, 9.5; 32 -> 64, 4 x 20 x 20: 9.7, 6.4).
+    // Past one workgroup per CU only from 128 to 768 per wave (1 x 1, 2 x 49 x 49, 32 -> 128,
+    // 304 of them: 7.1 us tiled, 8.2 here; dense 911 x 3488 -> 320, 300 of them: 27.3, 32.8;
+    // by the size of the reduction, below 512, from 512 to 3072 and above, time here over time tiled
+    // 1.03, 0.78 and 1.10 on 60 layers).
     // In fp32, whose tiles' MFMAs outweigh the split's traffic, above 320 per wave
-    // only with at least 128 workgroups of its own (448 -> 256, 3 x 9 x 9, 64 of
-    // them: 55.8 us here, 39.4 in split 32-row tiles).
+    // only with at least 88 workgroups of its own (time here over time tiled on 90
+    // layers of random sizes: 1.14 to 1.46 below, 0.91 above; 64 -> 544, 3 x 8 x 8, 5 x 5,
+    // 102 of them: 27.1 us here, 36.0 tiled; 448 -> 256, 3 x 9 x 9, 3 x 3, 64 of them: 55.8, 39.4).
     const int ks_env = env_override("QLAYER_FWD_KSPLIT", -1);
     const int ks_k = (pm_want ? pm_max_taps(g, 64, M) : g.KH * g.KW) * p.Cp;
     auto ks_default = [&]() {
         if (p.cfg != 3 && p.cfg != 7) return false;
         if (g.dt == QL_F32)
-            return p.splits > 1 && ks_k <= 4 * 1152 && (ks_k <= 4 * 320 || cdiv(g.O, 16) * cdiv(M, 64) >= 128);
-        return (p.splits > 1 && ks_k <= 4 * 768) || (cfg_env < 0 && cdiv(g.O, 64) * cdiv(M, 128) <= 80 && ks_k <= 4 * 1024);
+            return p.splits > 1 && ks_k <= 4 * 1152 && (ks_k <= 4 * 320 || cdiv(g.O, 16) * cdiv(M, 64) >= 88);
+        if (p.splits > 1 && ks_k <= 4 * 768) return true;
+        const int wide = cdiv(g.O, 32) * cdiv(M, 64);  // workgroups (of the larger tile where they fill the GPU)
+        const bool one_each = (wide >= kNumCUs ? wide : cdiv(g.O, 16) * cdiv(M, 64)) <= kNumCUs;
+        return cfg_env < 0 && cdiv(g.O, 64) * cdiv(M, 128) <= 80 &&
+               (one_each ? ks_k <= 4 * 1024 : ks_k >= 4 * 128 && ks_k <= 4 * 768);
     };
     if (p.veck && g.ne == NEURON_QUADRA && g.O % 4 == 0 && p.Cp % p.KE == 0 && g.KH * g.KW <= 32 &&
         (long long)g.N * g.H * g.W * p.Cp * (long long)g.esize() < (1LL << 31) &&
@@ -518,7 +536,7 @@ constexpr int kBdBCOL[kBdCfgs] = {128, 128, 64, 128, 256, 128, 128};  // 4: the 
 
 // K steps relative to the 64 x 128 tile's (see kFwdStepBf16).
 constexpr double kBdStepBf16[kBdCfgs] = {1.3, 1.0, 1.0, 1.3, 1.0, 1.0, 0.9};
-constexpr double kBdStepF32[kBdCfgs] = {2.0, 1.0, 1.0, 2.0, 1.0, 1.0, 0.55};
+constexpr double kBdStepF32[kBdCfgs] = {2.0, 1.0, 1.0, 1.9, 1.0, 1.0, 0.6};
 
 struct BwdDataPlan {
     int cfg;  // pipelined: index into kBd*; generic: 0: 128 x 128, 1: 64 x 128
@@ -647,6 +665,7 @@ inline BwdDataPlan plan_bwd_data(const Geom &g) {
     const int ca_env = env_override("QLAYER_BWD_DATA_CA", -1);
     p.pm = ca_ok && ca_env != 0 && p.s1 && g.ne == NEURON_QUADRA &&
            pm_default(g, env_override("QLAYER_BWD_DATA_POSMAJ", -1));
+    const int min_stages = env_override("QLAYER_BWD_DATA_MINSTAGES", 4);
     auto fill = [&](int cfg) {
         p.cfg = cfg;
         if (p.veck) {
@@ -657,9 +676,10 @@ inline BwdDataPlan plan_bwd_data(const Geom &g) {
         p.col_tiles = phased ? g.SH * g.SW * cdiv(phase_pixels, p.BCOL) : cdiv(M, p.BCOL);
         int kst = p.stages_total;
         if (p.pm) kst = bd_pm_max_taps(g, p.BCOL, M) * (g.O / p.KE);
-        return plan_splits(p.row_tiles * p.col_tiles, kst, env_override("QLAYER_BWD_DATA_MINSTAGES", 4),
-                           (size_t)M * g.C * 4, p.slots, p.splits, p.sps, step_scale(g), kMaxSplitBytes, 1,
-                           kSharedRound, p.veck ? (g.dt == QL_F32 ? kBdStepF32 : kBdStepBf16)[cfg] : 1.0);
+        return plan_splits(p.row_tiles * p.col_tiles, kst, min_stages, (size_t)M * g.C * 4, p.slots, p.splits, p.sps,
+                           step_scale(g), kMaxSplitBytes, 1, kSharedRound,
+                           p.veck ? (g.dt == QL_F32 ? kBdStepF32 : kBdStepBf16)[cfg] : 1.0,
+                           g.dt == QL_F32 ? kBdRampF32 : 0.0);
     };
     // The tile by the split model: smaller tiles where they leave fewer empty rows
     // or idle CUs.  us per call: 128 -> 128 channels, 32 x 14 x 14 maps, 1 x 1, bf16 8.8
@@ -671,6 +691,8 @@ inline BwdDataPlan plan_bwd_data(const Geom &g) {
         int pick = p.cfg;
         for (int cfg : {3, 2, 5, 6}) {
             if (g.C <= 64 && cfg < 5) continue;  // (128-row tiles: half empty)
+            // (maps of four pixels: 416 -> 64 channels, 209 x 2 x 2, 5 x 5, 14.5 us in 128 x 64, 17.5 in 32 x 128)
+            if (g.C > 64 && cfg >= 5 && p.pm) continue;
             const double t = fill(cfg);
             if (t < best) {
                 best = t;
@@ -822,7 +844,7 @@ inline BwdWeightPlan plan_bwd_weight(const Geom &g, size_t max_split_bytes = kMa
         p.row_tiles = cdiv(KP, p.BKP);
         p.col_tiles = cdiv(g.O, p.BO);
         return plan_splits(p.row_tiles * p.col_tiles, p.stages_total, min_stages, bytes_per_split, p.slots, p.splits,
-                           p.sps, step_scale(g), max_split_bytes, kBwPipes[cfg], kSharedRound, cfg == 5 ? kFatStep : (cfg == 2 ? kSmallStep : 1.0));
+                           p.sps, step_scale(g), max_split_bytes, kBwPipes[cfg], kSharedRound, cfg == 5 ? kFatStep : cfg == 2 ? kSmallStep : 1.0, cfg == 2 ? kBwRampSmall : kBwRamp);
     };
     if (p.pipe && g.ne == NEURON_QUADRA) {
         // the 16 x 16 x 32 kernel: four waves on a 64-channel tile, two such pipelines per

@@ -65,3 +65,21 @@ F32, BF16 = ql.QL_F32, ql.QL_BF16
 def test_passes_that_take_padded_copies(shape, dtype, neuron, padded):
     got = launches(shape, dtype, neuron)
     assert [p for p, names in got.items() if any("qconv_pad_" in n for n in names)] == padded.split()
+
+
+@pytest.mark.parametrize("shape,dtype,neuron,groups,which,kernel", [
+    # tiles: the template arguments after the type are rows, columns
+    ((77, 400, 35, 4, 3, 1), F32, Q, 1, "bwd_data", "qconv_bwd_data_kernel<float, 128, 128"),   # many 32-row tiles
+    ((32, 32, 16, 32, 3, 1), F32, Q, 1, "bwd_data", "qconv_bwd_data_kernel<float, 32, 128"),    # one, no empty rows
+    ((209, 416, 2, 64, 5, 1), BF16, Q, 1, "bwd_data", "qconv_bwd_data_kernel<unsigned short, 128, 64"),  # four pixels
+    ((12, 176, 22, 304, 3, 1), BF16, Q, 1, "bwd_weight", "qconv_bwd_weight16_kernel<"),  # too many steps for 64 x 64
+    ((2, 256, 4, 256, 3, 1), BF16, Q, 1, "bwd_weight", "qconv_bwd_weight_kernel<64, 64"),
+    ((3407, 16, 1, 848, 1, 1), F32, Q, 1, "fwd", "qconv_fwd_kernel<float, 64, 128"),     # one K step: the ramp decides
+    ((2, 32, 49, 128, 1, 1), BF16, Q, 1, "fwd", "qconv_fwd_kernel<"),                    # nothing to split among waves
+    ((911, 3488, 1, 320, 1, 1), BF16, Q, 1, "fwd", "qconv_fwd_kernel<"),                 # two rounds of long reductions
+    ((3, 64, 8, 544, 5, 1), F32, Q, 1, "fwd", "qconv_fwd_ksplit_kernel<"),               # 102 workgroups
+    ((3, 448, 9, 256, 3, 1), F32, Q, 1, "fwd", "qconv_fwd_kernel<"),                     # 64 workgroups
+], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else None)
+def test_kernel_of_a_pass(shape, dtype, neuron, groups, which, kernel):
+    names = launches(shape, dtype, neuron, groups, (which,))[which]
+    assert any(kernel in n for n in names), names
