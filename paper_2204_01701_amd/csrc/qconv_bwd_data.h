@@ -254,10 +254,10 @@ __global__ __launch_bounds__(kThreads) void qconv_bwd_data_kernel(const BwdDataA
         }
         // The predicates are bitwise, so that the K loop stays one block and its MFMAs
         // interleave (as && the compiler branches around them: 72 -> 81 us in fp32 on 32 -> 32
-        // channels, 256 x 16 x 16 maps); not in the 128 x 128 tiles of natural weights, which run
+        // channels, 256 x 16 x 16 maps); not in the proposed neuron's 128 x 128 tiles of natural weights, which run
         // faster with the branches (488 -> 504 channels, 71 x 10 x 10, 3 x 3: 172 us, 194 bitwise;
         // the 128 x 64 tiles of 128 -> 88, 64 x 16 x 16, 3 x 3 / 2: 14.1, 12.8).
-        constexpr bool LAZY = NATW && BR == 128 && BCOL == 128;
+        constexpr bool LAZY = NATW && BR == 128 && BCOL == 128 && OM == OM_QUADRA;
         const int k = s * KE + kcol * VEC;
         bool kin;
         if constexpr (LAZY) kin = live && k < KP;
