@@ -82,6 +82,7 @@ __global__ __launch_bounds__(kThreads) void qconv_bwd_data_kernel(const BwdDataA
         if constexpr (S1) return ri * a.KW + qi;
         else return (ph.r0 + a.SH * ri) * a.KW + ph.q0 + a.SW * qi;
     };
+    const RunDiv dwp(S1 ? 1 : ph.wp), dhw(S1 ? 1 : ph.hp * ph.wp);
     // image and position of GEMM column m
     auto pixel = [&](int m, int &n, int &hh, int &ww) {
         if constexpr (S1) {
@@ -90,9 +91,9 @@ __global__ __launch_bounds__(kThreads) void qconv_bwd_data_kernel(const BwdDataA
             hh = (int)fdiv((uint32_t)rem, a.fd_w);
             ww = rem - hh * a.W;
         } else {
-            const uint32_t hw = ph.hp * ph.wp, rem = (uint32_t)m % hw;
-            n = (uint32_t)m / hw;
-            hh = rem / (uint32_t)ph.wp;
+            n = (int)dhw.div((uint32_t)m);
+            const int rem = m - n * ph.hp * ph.wp;
+            hh = (int)dwp.div((uint32_t)rem);
             ww = rem - hh * ph.wp;
         }
     };

@@ -55,7 +55,19 @@ __global__ __launch_bounds__(kThreads, 2) void qconv_bwd_data_narrow_kernel(cons
     if constexpr (!S1) {
         const int round = wid / a.units, u = wid - round * a.units;
         int at = u, n = 1;
-        if (a.SH * a.SW <= kMaxPhases) {
+        const int nph = a.SH * a.SW;
+        if (nph <= 8) {  // (fixed indices: a walk down the list waits for the scalar cache at each entry)
+            at = 0;
+            n = a.units;
+#pragma unroll
+            for (int i = 7; i >= 0; --i) {
+                const bool past = (i < nph) & (u >= a.unit_end[i]);
+                phase += past;
+                at = max(at, past ? (int)a.unit_end[i] : 0);
+                n = i < nph && !past ? (int)a.unit_end[i] : n;
+            }
+            n -= at;
+        } else if (nph <= kMaxPhases) {
             while (u >= a.unit_end[phase]) ++phase;  // (u < units = the last phase's end)
             at = phase ? a.unit_end[phase - 1] : 0;
             n = a.unit_end[phase] - at;
@@ -67,6 +79,7 @@ __global__ __launch_bounds__(kThreads, 2) void qconv_bwd_data_narrow_kernel(cons
     }
     const BwdPhase ph = S1 ? BwdPhase(a.H, a.W, a.KH, a.KW, a.PH, a.PW)
                            : BwdPhase(phase, a.H, a.W, a.KH, a.KW, a.PH, a.PW, a.fd_sh, a.fd_sw);
+    const RunDiv dqp(S1 ? 1 : ph.qp), dwp(S1 ? 1 : ph.wp), dhw(S1 ? 1 : ph.hp * ph.wp);
     const int K = S1 ? a.K : ph.rp * ph.qp * a.O;
     const int mp = S1 ? a.M : a.N * ph.hp * ph.wp;
 
@@ -80,7 +93,7 @@ __global__ __launch_bounds__(kThreads, 2) void qconv_bwd_data_narrow_kernel(cons
         kin[ch] = k < K;
         const int tap = kin[ch] ? (int)fdiv((uint32_t)k, a.fd_o) : 0;
         ko[ch] = k - tap * a.O;
-        kr[ch] = S1 ? (int)fdiv((uint32_t)tap, a.fd_kw) : tap / max(ph.qp, 1);
+        kr[ch] = S1 ? (int)fdiv((uint32_t)tap, a.fd_kw) : (int)dqp.div((uint32_t)tap);
         kq[ch] = tap - kr[ch] * (S1 ? a.KW : ph.qp);
         kw[ch] = S1 ? k : ((ph.r0 + a.SH * kr[ch]) * a.KW + ph.q0 + a.SW * kq[ch]) * a.O + ko[ch];
     }
@@ -114,10 +127,9 @@ __global__ __launch_bounds__(kThreads, 2) void qconv_bwd_data_narrow_kernel(cons
             w = rem - h * a.W;
             p = m;
         } else {
-            const uint32_t hw = ph.hp * ph.wp;
-            n = (uint32_t)pp / hw;
-            const uint32_t rem = pp - n * hw;
-            h = rem / (uint32_t)ph.wp;
+            n = (int)dhw.div((uint32_t)pp);
+            const int rem = pp - n * ph.hp * ph.wp;
+            h = (int)dwp.div((uint32_t)rem);
             w = rem - h * ph.wp;
             p = (n * a.H + ph.h0 + a.SH * h) * a.W + ph.w0 + a.SW * w;
         }

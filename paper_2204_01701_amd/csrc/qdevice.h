@@ -318,6 +318,18 @@ __device__ __forceinline__ TileCoord tile_coord(int bid, int order, int row_tile
     return c;
 }
 
+// Division by a divisor that a kernel forms itself: one division sets up
+// m = floor((2^32 - 1) / d) >= 2^32 / d - 1, so that mulhi(n, m) is the quotient of
+// any 32-bit n or one less.
+struct RunDiv {
+    uint32_t d, m;
+    __device__ __forceinline__ explicit RunDiv(int divisor) : d((uint32_t)max(divisor, 1)), m(0xffffffffu / d) {}
+    __device__ __forceinline__ uint32_t div(uint32_t n) const {
+        const uint32_t q = __umulhi(n, m);
+        return q + (n - q * d >= d ? 1u : 0u);
+    }
+};
+
 // Input gradient at stride S: input pixel (h, w) meets only the taps (r, q)
 // with r = (h + PH) mod SH and q = (w + PW) mod SW, the pixel's phase.  The
 // pixels of one phase and its taps form a stride-1 problem of their own:
