@@ -530,6 +530,19 @@ __device__ __forceinline__ void dw_pin(float (&v)[A][B][C]) {
     for (int i = 0; i < A; ++i) dw_pin(v[i]);
 }
 
+// The types of one term hold a third of the proposed neuron's filter rows and
+// sums, and need less help: on whole vectors at stride 1, T2 in bf16 loads the
+// next column during this one (two register buffers; forward of 352 channels, 151 x
+// 56 x 56 maps, 280 us, 350 with one buffer), and the input gradients of T2, and of
+// T3 in fp32, leave the sums to the compiler (the same layer, T2, bf16 299 us, 401
+// pinned; 288 channels, 251 x 41 x 41, T2, fp32 272, 444).
+template <typename T, int OM, bool VEC, int S> constexpr bool dw_col_prefetch() {
+    return OM == OM_SQIN && sizeof(T) == 2 && VEC && S == 1;
+}
+template <typename T, int OM, bool VEC> constexpr bool dw_bd_pinned() {
+    return !VEC || (OM != OM_SQIN && !(OM == OM_SQUARE && sizeof(T) == 4));
+}
+
 // One column of the forward: its position and the raw input rows it sees.
 template <typename T, int V, bool VEC, int K, int S, int R>
 struct DwFwdCol {
@@ -608,7 +621,7 @@ __device__ __forceinline__ void dw_fwd_col_compute(const DwArgs &a, const DwFwdC
             }
         }
     }
-    dw_pin(acc);
+    if constexpr (!dw_col_prefetch<T, OM, VEC, S>()) dw_pin(acc);
 #pragma unroll
     for (int rr = 0; rr < R; ++rr) {
         if (b.oh0 + rr >= a.HO) break;
@@ -656,11 +669,29 @@ void qconv_dw_fwd_col_kernel(const DwArgs a) {
     if (cleft <= 0 || ch_begin >= ch_end) return;
     const T *__restrict__ x = static_cast<const T *>(a.x);
     const __amdgpu_buffer_rsrc_t xrs = dw_rsrc(a.x, a.xbytes);
-    for (int chunk = ch_begin; chunk < ch_end; ++chunk) {
+    if constexpr (!dw_col_prefetch<T, OM, VEC, S>()) {
+        for (int chunk = ch_begin; chunk < ch_end; ++chunk) {
+            QL_DW_CHUNK_FENCE();
+            DwFwdCol<T, V, VEC, K, S, R> b;
+            b.fetch(a, xrs, x, chunk * PL + pl, c, cleft);
+            dw_fwd_col_compute<T, OM>(a, b, wl, bl, CB, cg, c, cleft);
+        }
+        return;
+    }
+    // the next fetch is unconditional (clamped, not stored past the end): no
+    // branch between a fetch and its use
+    DwFwdCol<T, V, VEC, K, S, R> b0, b1;
+    int chunk = ch_begin;
+    b0.fetch(a, xrs, x, chunk * PL + pl, c, cleft);
+    while (true) {
         QL_DW_CHUNK_FENCE();
-        DwFwdCol<T, V, VEC, K, S, R> b;
-        b.fetch(a, xrs, x, chunk * PL + pl, c, cleft);
-        dw_fwd_col_compute<T, OM>(a, b, wl, bl, CB, cg, c, cleft);
+        b1.fetch(a, xrs, x, (chunk + 1) * PL + pl, c, cleft);
+        dw_fwd_col_compute<T, OM>(a, b0, wl, bl, CB, cg, c, cleft);
+        if (++chunk >= ch_end) break;
+        QL_DW_CHUNK_FENCE();
+        b0.fetch(a, xrs, x, (chunk + 1) * PL + pl, c, cleft);
+        dw_fwd_col_compute<T, OM>(a, b1, wl, bl, CB, cg, c, cleft);
+        if (++chunk >= ch_end) break;
     }
 }
 
@@ -919,7 +950,7 @@ __device__ __forceinline__ void dw_bd_col_compute(const DwArgs &a, const DwBdCol
             }
         }
     }
-    dw_pin(acc);
+    if constexpr (dw_bd_pinned<T, OM, VEC>()) dw_pin(acc);
 #pragma unroll
     for (int rr = 0; rr < R; ++rr) {
         if (b.h0 + rr >= a.H) break;
@@ -952,11 +983,27 @@ void qconv_dw_bwd_data_col_kernel(const DwArgs a) {
     __amdgpu_buffer_rsrc_t mrs[3];
 #pragma unroll
     for (int m = 0; m < NGM; ++m) mrs[m] = dw_rsrc(maps[m], a.pbytes);
-    for (int chunk = ch_begin; chunk < ch_end; ++chunk) {
+    if constexpr (!dw_col_prefetch<T, OM, VEC, 1>()) {
+        for (int chunk = ch_begin; chunk < ch_end; ++chunk) {
+            QL_DW_CHUNK_FENCE();
+            DwBdCol<T, OM, V, VEC, K, R> b;
+            b.fetch(a, mrs, maps, chunk * PL + pl, c, cleft);
+            dw_bd_col_compute<T, OM, V, VEC, K, R>(a, b, wl, CB, cg, c, cleft);
+        }
+        return;
+    }
+    DwBdCol<T, OM, V, VEC, K, R> b0, b1;
+    int chunk = ch_begin;
+    b0.fetch(a, mrs, maps, chunk * PL + pl, c, cleft);
+    while (true) {
         QL_DW_CHUNK_FENCE();
-        DwBdCol<T, OM, V, VEC, K, R> b;
-        b.fetch(a, mrs, maps, chunk * PL + pl, c, cleft);
-        dw_bd_col_compute<T, OM, V, VEC, K, R>(a, b, wl, CB, cg, c, cleft);
+        b1.fetch(a, mrs, maps, (chunk + 1) * PL + pl, c, cleft);
+        dw_bd_col_compute<T, OM, V, VEC, K, R>(a, b0, wl, CB, cg, c, cleft);
+        if (++chunk >= ch_end) break;
+        QL_DW_CHUNK_FENCE();
+        b0.fetch(a, mrs, maps, (chunk + 1) * PL + pl, c, cleft);
+        dw_bd_col_compute<T, OM, V, VEC, K, R>(a, b1, wl, CB, cg, c, cleft);
+        if (++chunk >= ch_end) break;
     }
 }
 

@@ -972,6 +972,19 @@ inline int dw_lanes(int C, int V, int most = 8) {
     return l;
 }
 
+// Channel lanes of the row kernels, 4 channels each: 64, or on layers of several
+// slices the count of 64, 32 and 16 (a cache line in bf16) that leaves the fewest
+// lanes of the last slice empty.  Of 280 channels in slices of 256 nearly half
+// are: 133 x 33 x 33 maps, bf16, forward 182 us in 64 lanes, 115 in 16 (160 in the
+// column kernels), input gradient 285, 124 (186); 288 channels, 114 x 54 x 54, stride
+// 2, fp32 forward 209, 120 (150).
+inline int dw_row_lanes(int C) {
+    int best = dw_lanes(C, 4, 64);
+    for (int l = 32; C > 256 && l >= 16; l /= 2)
+        if (cdiv(C, l * 4) * l < cdiv(C, best * 4) * best) best = l;
+    return best;
+}
+
 // Columns per thread of the row kernels: as many as the registers take.
 inline int dw_row_cols(const Geom &g, int pass) {
     return pass == 0 ? (g.SH == 1 ? 4 : 2) : (g.dt == QL_BF16 ? 4 : 2);
@@ -1009,9 +1022,13 @@ inline DwPlan plan_dw(const Geom &g, int pass) {
     // the column kernels' shorter items win (bf16 forward and input gradient, us,
     // row against column kernels: 64 x 56 x 56 maps of 256 channels 115, 114 against
     // 170, 213; 128 x 32 x 32 of 32 channels 26.4, 25.2 against 14.3, 14.2).
+    // (T2 moves a third of the proposed neuron's bytes per product, and reads X again at
+    // every store of the input gradient: in bf16 its column kernels are the faster ones,
+    // 352 channels, 151 x 56 x 56 maps, 334 us against 482, 176 channels, 158 x 47 x 47, 170 against 174.)
     const int rows_env = env_override("QLAYER_DW_ROWS", -1);
-    if (p.col && p.vec && pass != 2 && rows_env != 0) {
-        const int lanes = dw_lanes(g.C, 4, 64), tiles = cdiv(g.C, lanes * 4), ncg = cdiv(p.iwid, dw_row_cols(g, pass));
+    const bool t2 = g.ne == NEURON_T2 && g.dt == QL_BF16 && rows_env != 1;
+    if (p.col && p.vec && pass != 2 && rows_env != 0 && !t2) {
+        const int lanes = dw_row_lanes(g.C), tiles = cdiv(g.C, lanes * 4), ncg = cdiv(p.iwid, dw_row_cols(g, pass));
         const bool three = pass == 0 ? g.dt == QL_BF16 : g.dt == QL_F32;  // 4-wave workgroups per CU by registers
         const int slots = kNumCUs * (three ? 3 : 2);
         long long best = 0;

@@ -79,6 +79,10 @@ def test_passes_that_take_padded_copies(shape, dtype, neuron, padded):
     ((911, 3488, 1, 320, 1, 1), BF16, Q, 1, "fwd", "qconv_fwd_kernel<"),                 # two rounds of long reductions
     ((3, 64, 8, 544, 5, 1), F32, Q, 1, "fwd", "qconv_fwd_ksplit_kernel<"),               # 102 workgroups
     ((3, 448, 9, 256, 3, 1), F32, Q, 1, "fwd", "qconv_fwd_kernel<"),                     # 64 workgroups
+    # depthwise
+    ((64, 256, 56, 256, 3, 1), BF16, Q, 256, "bwd_data", "qconv_dw_bwd_data_rows_kernel"),
+    ((151, 352, 56, 352, 3, 1), BF16, T2, 352, "bwd_data", "qconv_dw_bwd_data_col_kernel"),
+    ((151, 352, 56, 352, 3, 1), BF16, T2, 352, "fwd", "qconv_dw_fwd_col_kernel"),
 ], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else None)
 def test_kernel_of_a_pass(shape, dtype, neuron, groups, which, kernel):
     names = launches(shape, dtype, neuron, groups, (which,))[which]
