@@ -327,11 +327,14 @@ constexpr int kFwdBCOL[kFwdCfgs] = {128, 256, 128, 128, 256, 256, 256, 128};
 // Workgroups one CU holds at once (limited by LDS stages and registers).
 constexpr int kFwdSlots[kFwdCfgs] = {1, 1, 1, 2, 1, 1, 1, 2};
 
-// Whether the narrow kernels can address a layer: their buffer loads take
-// 32-bit byte offsets, with those from 2^31 on meaning "zero".
-inline bool narrow_fits(const Geom &g, int C, int O) {
-    const long long lim = (1LL << 31) / g.esize();
-    return (long long)g.N * g.H * g.W * C < lim && (long long)g.N * g.HO * g.WO * O < lim;
+// Images that one launch of a narrow kernel addresses: its buffer loads take 32-bit
+// byte offsets, with those from 2^31 on meaning "zero".  Larger layers are launched
+// in equal groups of that many images; 0 where a single image is too large (the
+// tiled kernels, whose addresses have 64 bits, take such a layer).
+inline int narrow_images(const Geom &g, int C, int O) {
+    const long long image = std::max((long long)g.H * g.W * C, (long long)g.HO * g.WO * O) * (long long)g.esize();
+    const long long most = std::min<long long>(g.N, env_override("QLAYER_NARROW_BYTES", 0x7fffffff) / image);
+    return most > 0 ? cdiv(g.N, cdiv(g.N, most)) : 0;
 }
 
 // Waves of the narrow kernels (a multiple of the four per workgroup): one per
@@ -354,7 +357,7 @@ struct FwdPlan {
     bool veck;
     bool smallc;  // KH KW C + bias columns <= 32, 32 or 64 output channels: qconv_fwd_smallc_kernel, no workspace
     bool narrow;  // at most 16 output channels, short J: qconv_fwd_narrow_kernel (OB row blocks, NCH chunks)
-    int ob, nch;
+    int ob, nch, ni;  // ... NI images per launch
     bool ksplit;  // small outputs: qconv_fwd_ksplit_kernel (tiles of 3 x 16 krb rows by 16 kcb pixels, K split by waves)
     int krb, kcb;
     int stat_parts;  // partial sums of the epilogue statistics the kernel writes (fused path)
@@ -392,11 +395,12 @@ inline FwdPlan plan_fwd(const Geom &g) {
     // (one 16-channel row block: two measured slower than the tiled kernel on the
     // 16 -> 32-channel stride-2 layer of a CIFAR ResNet)
     if (p.veck && g.ne == NEURON_QUADRA && g.O % 4 == 0 && p.ob == 1 && p.nch <= 9 &&
-        narrow_fits(g, p.Cp, g.O) && env_override("QLAYER_FWD_NARROW", 1) != 0) {
+        narrow_images(g, p.Cp, g.O) > 0 && env_override("QLAYER_FWD_NARROW", 1) != 0) {
         p.narrow = true;
         p.splits = 1;
         p.KE = 64 / (int)g.esize();
-        p.stat_parts = narrow_waves(M);
+        p.ni = narrow_images(g, p.Cp, g.O);
+        for (int n = 0; n < g.N; n += p.ni) p.stat_parts += narrow_waves((long long)std::min(p.ni, g.N - n) * g.HO * g.WO);
         p.ws_bytes = p.xpad_bytes + 3 * p.wpad_bytes;
         return p;
     }
@@ -546,7 +550,7 @@ struct BwdDataPlan {
     bool natw;    // weights read untransposed through natural LDS tiles (bf16, C % 8 == 0)
     bool smallc;  // C <= 4: per-pixel partial sums by MFMA, then a gather over the taps
     bool narrow;  // at most 16 input channels, short K: qconv_bwd_data_narrow_kernel (CB row blocks, NCH chunks)
-    int cb, nch;
+    int cb, nch, ni;  // ... NI images per launch
     bool ca, pm;  // channel-aligned K steps; position-major order with taps skipped (BwdDataArgs)
     int order;  // block order of the split-K grid (tile_coord)
     int fused_rb; // ... stride 1: both steps in one kernel, bands of fused_rb input rows (0: two kernels)
@@ -627,8 +631,9 @@ inline BwdDataPlan plan_bwd_data(const Geom &g) {
     p.nch = cdiv(K, 4 * g.vec());
     if (p.veck && g.ne == NEURON_QUADRA && g.C % 4 == 0 && p.cb == 1 && p.nch <= 9 &&
         (p.s1 || (long long)g.SH * g.SW <= std::max(kMaxPhases, narrow_waves(M))) &&  // (a wave per phase)
-        narrow_fits(g, g.C, p.Op) && env_override("QLAYER_BWD_DATA_NARROW", 1) != 0) {
+        narrow_images(g, g.C, p.Op) > 0 && env_override("QLAYER_BWD_DATA_NARROW", 1) != 0) {
         p.narrow = true;
+        p.ni = narrow_images(g, g.C, p.Op);
         p.splits = 1;
         p.wt_bytes = align_up(3 * (size_t)p.Op * g.KH * g.KW * g.C * g.esize());
         p.ws_bytes = p.wt_bytes + gpads;
@@ -743,7 +748,7 @@ constexpr int kBwPipes[kBwCfgs] = {1, 1, 1, 1, 2, 1};  // pipelines per workgrou
 struct BwdWeightPlan {
     bool narrow;  // KH KW C <= 144: qconv_bwd_weight_narrow_kernel (NF fragments, NOB 16-channel slices)
     bool few;     // a few-channel layer on the padded copy of X (refused where its scratch does not fit)
-    int nf, nob;
+    int nf, nob, ni;  // ... NI images per launch
     int cfg;   // pipelined path only
     bool pipe; // bf16 and vectorizable: pipelined kernel; otherwise the generic one
     int BKP, BO, KE, slots;
@@ -753,6 +758,10 @@ struct BwdWeightPlan {
     int Cp, Op;
     // workspace: [X padded][G, T_a, T_b padded][dW partials][db partials]
     size_t xpad_bytes, gpad_bytes, dw_bytes, db_bytes, ws_bytes;
+    // splits of the narrow kernel's launch on the images from n on
+    int narrow_splits(const Geom &g, int n) const {
+        return cdiv(cdiv((long long)std::min(ni, g.N - n) * g.HO * g.WO, g.dt == QL_BF16 ? 32 : 16), sps);
+    }
 };
 
 // max_split_bytes: cap on the dW partial sums (the no-allocation entry point
@@ -767,9 +776,13 @@ inline BwdWeightPlan plan_bwd_weight(const Geom &g, size_t max_split_bytes = kMa
     // grid: by default in fp32, where the 16 -> 32-channel stride-2 CIFAR ResNet layer
     // measured 37 against 66 us per call; in bf16 it and the VGG-16 stem were no faster)
     const int narrow_max_o = env_override("QLAYER_BWD_WEIGHT_NARROW_MAXO", g.dt == QL_F32 ? 64 : 16);
+    const size_t bytes_per_split = (size_t)3 * g.O * g.KH * g.KW * g.C * 4;
+    const int most_splits = (int)std::min<size_t>(0x7fffffff, std::max<size_t>(1, max_split_bytes / bytes_per_split));
     auto narrow_dims = [&](int Cp, int Op) {
-        return g.ne == NEURON_QUADRA && (Op <= 16 || (Op % 16 == 0 && Op <= narrow_max_o)) && Cp % g.vec() == 0 &&
-               Op % g.vec() == 0 && cdiv(g.KH * g.KW * Cp, 16) <= 9 && narrow_fits(g, Cp, Op) &&
+        const int ni = narrow_images(g, Cp, Op);
+        return ni > 0 && cdiv(g.N, ni) <= most_splits && g.ne == NEURON_QUADRA &&
+               (Op <= 16 || (Op % 16 == 0 && Op <= narrow_max_o)) && Cp % g.vec() == 0 && Op % g.vec() == 0 &&
+               cdiv(g.KH * g.KW * Cp, 16) <= 9 &&
                env_override("QLAYER_BWD_WEIGHT_NARROW", 1) != 0;
     };
     const bool pad = may_pad && g.pad_bwd_weight(narrow_dims(g.cpad(), g.opad()));
@@ -793,7 +806,6 @@ inline BwdWeightPlan plan_bwd_weight(const Geom &g, size_t max_split_bytes = kMa
     // generic kernel's steps are latency-bound: down to one step each (the
     // 64 -> 10 head of a CIFAR ResNet at batch 256, 53 -> 17 us).
     const int min_stages = env_override("QLAYER_BWD_WEIGHT_MINSTAGES", p.pipe ? 2 : 1);
-    const size_t bytes_per_split = (size_t)3 * g.O * KPO * 4;
     // Narrow layers: the whole gradient of a 16-channel slice is one tile; about
     // one workgroup per CU in all down to one K step per wave, two per CU from
     // four steps per wave, the partial sums within max_split_bytes.  (16 -> 16
@@ -809,7 +821,8 @@ inline BwdWeightPlan plan_bwd_weight(const Geom &g, size_t max_split_bytes = kMa
     if (narrow_shape) {
         p.narrow = true;
         p.nob = cdiv(p.Op, 16);
-        p.stages_total = cdiv(M, g.dt == QL_BF16 ? 32 : 16);
+        p.ni = narrow_images(g, p.Cp, p.Op);
+        p.stages_total = cdiv((long long)p.ni * g.HO * g.WO, g.dt == QL_BF16 ? 32 : 16);  // of one launch
         int splits = std::max(cdiv(p.stages_total, 16), std::min(cdiv(kNumCUs, p.nob), cdiv(p.stages_total, 4)));
         splits = std::min(std::max(1, 2 * kNumCUs / p.nob), splits);
         if (splits < 16) {
@@ -826,9 +839,10 @@ inline BwdWeightPlan plan_bwd_weight(const Geom &g, size_t max_split_bytes = kMa
             }
         }
         splits = env_override("QLAYER_BWD_WEIGHT_NARROW_SPLITS", splits);
-        splits = std::max(1, std::min(splits, (int)std::max<size_t>(1, max_split_bytes / bytes_per_split)));
+        splits = std::max(1, std::min(splits, most_splits / cdiv(g.N, p.ni)));
         p.sps = cdiv(p.stages_total, splits);
-        p.splits = cdiv(p.stages_total, p.sps);
+        p.splits = 0;
+        for (int n = 0; n < g.N; n += p.ni) p.splits += p.narrow_splits(g, n);
         if (p.splits > 1) {
             p.dw_bytes = align_up((size_t)p.splits * 3 * g.O * KPO * sizeof(float));
             p.db_bytes = align_up((size_t)p.splits * 3 * g.O * sizeof(float));

@@ -115,8 +115,6 @@ ql_status launch_bwd_data(const Geom &g, const BwdDataPlan &p, const void *gy, c
                 a.unit_end[i] = (uint16_t)a.units;
             }
         }
-        // (a whole round of units, so that every phase of a strided layer has a wave)
-        const dim3 grid((unsigned)(cdiv(std::max(narrow_waves(a.M), a.units), kThreads / 64)));
 #define QL_BD_NARROW(CB, NCH)                                                                                        \
     do {                                                                                                             \
         if (p.s1)                                                                                                    \
@@ -124,20 +122,33 @@ ql_status launch_bwd_data(const Geom &g, const BwdDataPlan &p, const void *gy, c
         else                                                                                                         \
             hipLaunchKernelGGL((qconv_bwd_data_narrow_kernel<T, CB, NCH, false>), grid, dim3(kThreads), 0, st, a); \
     } while (0)
-        switch (p.nch) {
-            case 1: QL_BD_NARROW(1, 1); break;
-            case 2: QL_BD_NARROW(1, 2); break;
-            case 3: QL_BD_NARROW(1, 3); break;
-            case 4: QL_BD_NARROW(1, 4); break;
-            case 5: QL_BD_NARROW(1, 5); break;
-            case 6: QL_BD_NARROW(1, 6); break;
-            case 7: QL_BD_NARROW(1, 7); break;
-            case 8: QL_BD_NARROW(1, 8); break;
-            case 9: QL_BD_NARROW(1, 9); break;
-            default: return QL_EINVAL;  // (the planner takes no other shape)
+        for (int n0 = 0; n0 < g.N; n0 += p.ni) {  // (one launch below 2^31 bytes)
+            const size_t goff = (size_t)n0 * g.HO * g.WO * p.Op;
+            a.N = std::min(p.ni, g.N - n0);
+            a.M = a.N * g.H * g.W;
+            a.gy = static_cast<const T *>(maps[0]) + goff;
+            a.ta = static_cast<const T *>(maps[1]) + goff;
+            a.tb = static_cast<const T *>(maps[2]) + goff;
+            a.dx = static_cast<T *>(dx) + (size_t)n0 * g.H * g.W * g.C;
+            // (a whole round of units, so that every phase of a strided layer has a wave)
+            const dim3 grid((unsigned)(cdiv(std::max(narrow_waves(a.M), a.units), kThreads / 64)));
+            switch (p.nch) {
+                case 1: QL_BD_NARROW(1, 1); break;
+                case 2: QL_BD_NARROW(1, 2); break;
+                case 3: QL_BD_NARROW(1, 3); break;
+                case 4: QL_BD_NARROW(1, 4); break;
+                case 5: QL_BD_NARROW(1, 5); break;
+                case 6: QL_BD_NARROW(1, 6); break;
+                case 7: QL_BD_NARROW(1, 7); break;
+                case 8: QL_BD_NARROW(1, 8); break;
+                case 9: QL_BD_NARROW(1, 9); break;
+                default: return QL_EINVAL;  // (the planner takes no other shape)
+            }
+            s = hip_status();
+            if (s != QL_OK) return s;
         }
 #undef QL_BD_NARROW
-        return hip_status();
+        return QL_OK;
     }
     const dim3 grid(p.row_tiles * p.col_tiles * p.splits), block(kThreads);
     // channel-aligned K steps (each within one tap): natural weight tiles, O a multiple of KE

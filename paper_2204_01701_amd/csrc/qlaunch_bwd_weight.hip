@@ -90,22 +90,37 @@ ql_status launch_bwd_weight(const Geom &g, const BwdWeightPlan &p, const void *x
     a.neuron = g.ne;
     if (p.narrow) {
 #define QL_BW_NARROW(NF) \
-    hipLaunchKernelGGL((qconv_bwd_weight_narrow_kernel<T, NF>), dim3(p.splits, p.nob), dim3(kThreads), 0, st, a)
-        switch (p.nf) {
-            case 1: QL_BW_NARROW(1); break;
-            case 2: QL_BW_NARROW(2); break;
-            case 3: QL_BW_NARROW(3); break;
-            case 4: QL_BW_NARROW(4); break;
-            case 5: QL_BW_NARROW(5); break;
-            case 6: QL_BW_NARROW(6); break;
-            case 7: QL_BW_NARROW(7); break;
-            case 8: QL_BW_NARROW(8); break;
-            case 9: QL_BW_NARROW(9); break;
-            default: return QL_EINVAL;  // (the planner takes no other shape)
+    hipLaunchKernelGGL((qconv_bwd_weight_narrow_kernel<T, NF>), dim3(splits, p.nob), dim3(kThreads), 0, st, b)
+        BwdWeightArgs b = a;
+        for (int n0 = 0; n0 < g.N; n0 += p.ni) {  // (one launch below 2^31 bytes)
+            const int splits = p.narrow_splits(g, n0);
+            const size_t moff = (size_t)n0 * g.HO * g.WO * p.Op;
+            b.N = std::min(p.ni, g.N - n0);
+            b.M = b.N * g.HO * g.WO;
+            b.stages_total = cdiv(b.M, g.dt == QL_BF16 ? 32 : 16);
+            b.x = static_cast<const T *>(a.x) + (size_t)n0 * g.H * g.W * C;
+            b.gy = static_cast<const T *>(a.gy) + moff;
+            b.ta = static_cast<const T *>(a.ta) + moff;
+            b.tb = static_cast<const T *>(a.tb) + moff;
+            switch (p.nf) {
+                case 1: QL_BW_NARROW(1); break;
+                case 2: QL_BW_NARROW(2); break;
+                case 3: QL_BW_NARROW(3); break;
+                case 4: QL_BW_NARROW(4); break;
+                case 5: QL_BW_NARROW(5); break;
+                case 6: QL_BW_NARROW(6); break;
+                case 7: QL_BW_NARROW(7); break;
+                case 8: QL_BW_NARROW(8); break;
+                case 9: QL_BW_NARROW(9); break;
+                default: return QL_EINVAL;  // (the planner takes no other shape)
+            }
+            const ql_status s = hip_status();
+            if (s != QL_OK) return s;
+            b.ws_dw += (size_t)splits * 3 * g.O * g.KH * g.KW * g.C;
+            b.ws_db += (size_t)splits * 3 * g.O;
         }
 #undef QL_BW_NARROW
-        const ql_status s = hip_status();
-        if (s != QL_OK || p.splits == 1) return s;
+        if (p.splits == 1) return QL_OK;
         return reduce_bw_partials(g, p.splits, a, dwa, dwb, dwc, dba, dbb, dbc, st);
     }
     const dim3 grid(p.row_tiles * p.col_tiles * p.splits), block(kThreads);

@@ -85,7 +85,6 @@ ql_status launch_fwd(const Geom &g, const FwdPlan &p, const void *x, const void 
     a.fd_cps = make_fastdiv(std::max(1, a.cps));
     a.neuron = g.ne;
     if (p.narrow) {
-        const dim3 grid((unsigned)(narrow_waves(a.M) / (kThreads / 64)));
         const bool ep = epi.scale || epi.shift || epi.relu || stat_part != nullptr;
 #define QL_FWD_NARROW(OB, NCH)                                                                                  \
     do {                                                                                                        \
@@ -94,20 +93,33 @@ ql_status launch_fwd(const Geom &g, const FwdPlan &p, const void *x, const void 
         else                                                                                                    \
             hipLaunchKernelGGL((qconv_fwd_narrow_kernel<T, OB, NCH, false>), grid, dim3(kThreads), 0, st, a); \
     } while (0)
-        switch (p.nch) {
-            case 1: QL_FWD_NARROW(1, 1); break;
-            case 2: QL_FWD_NARROW(1, 2); break;
-            case 3: QL_FWD_NARROW(1, 3); break;
-            case 4: QL_FWD_NARROW(1, 4); break;
-            case 5: QL_FWD_NARROW(1, 5); break;
-            case 6: QL_FWD_NARROW(1, 6); break;
-            case 7: QL_FWD_NARROW(1, 7); break;
-            case 8: QL_FWD_NARROW(1, 8); break;
-            case 9: QL_FWD_NARROW(1, 9); break;
-            default: return QL_EINVAL;  // (the planner takes no other shape)
+        for (int n0 = 0; n0 < g.N; n0 += p.ni) {  // (one launch below 2^31 bytes)
+            const size_t yoff = (size_t)n0 * g.HO * g.WO * g.O;
+            auto at = [&](void *m) { return m ? static_cast<T *>(m) + yoff : nullptr; };
+            a.N = std::min(p.ni, g.N - n0);
+            a.M = a.N * g.HO * g.WO;
+            a.y = at(y); a.ta = at(ta); a.tb = at(tb);
+            const int waves = narrow_waves(a.M);
+            const dim3 grid((unsigned)(waves / (kThreads / 64)));
+            switch (p.nch) {
+                case 1: QL_FWD_NARROW(1, 1); break;
+                case 2: QL_FWD_NARROW(1, 2); break;
+                case 3: QL_FWD_NARROW(1, 3); break;
+                case 4: QL_FWD_NARROW(1, 4); break;
+                case 5: QL_FWD_NARROW(1, 5); break;
+                case 6: QL_FWD_NARROW(1, 6); break;
+                case 7: QL_FWD_NARROW(1, 7); break;
+                case 8: QL_FWD_NARROW(1, 8); break;
+                case 9: QL_FWD_NARROW(1, 9); break;
+                default: return QL_EINVAL;  // (the planner takes no other shape)
+            }
+            const ql_status s0 = hip_status();
+            if (s0 != QL_OK) return s0;
+            a.x = static_cast<const T *>(a.x) + (size_t)a.N * g.H * g.W * C;
+            if (a.stat_part) a.stat_part += (size_t)waves * 2 * g.O;
         }
 #undef QL_FWD_NARROW
-        return hip_status();
+        return QL_OK;
     }
     if (p.ksplit) return launch_fwd_ksplit<T>(p, a, epi.scale || epi.shift || epi.relu || stat_part != nullptr, st);
     if (p.xsq_bytes) {

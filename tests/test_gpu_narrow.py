@@ -59,10 +59,10 @@ def test_narrow_paths_match_oracle(shape, bf16, narrow, monkeypatch):
 
 @pytest.mark.parametrize("shape", [(32, 16, 1024, 1024, 16, 1), (33, 8, 1024, 2048, 8, 2)],
                          ids=lambda s: "x".join(map(str, s)))
-def test_maps_from_2_31_bytes_leave_the_narrow_kernels(shape):
+def test_maps_from_2_31_bytes_match_parts(shape):
     """The narrow kernels address maps below 2^31 bytes; a layer whose fp32 X is
-    at or past that takes the tiled kernels, and agrees with the same layer
-    called on batches of a few images (narrow).  Either side is within the fp32
+    at or past that is launched in groups of images, and agrees with the same
+    layer called on batches of a few images.  Either side is within the fp32
     limit of the exact result, so the two are within twice that."""
     n, c, h, w, o, s = shape
     dev, part = torch.device("cuda"), 8
@@ -90,3 +90,37 @@ def test_maps_from_2_31_bytes_leave_the_narrow_kernels(shape):
         total = [v.double() for v in gi] if total is None else [t + v for t, v in zip(total, gi)]
     for k, (a, b) in enumerate(zip(grads, total)):
         assert float((a - b).norm() / b.norm()) <= 2 * qlh.tol(False, True), k
+
+
+@pytest.mark.parametrize("bf16", [False, True], ids=["fp32", "bf16"])
+@pytest.mark.parametrize("shape", [(5, 16, 12, 12, 16, 3, 1), (7, 16, 11, 9, 8, 3, 2), (4, 3, 9, 9, 16, 3, 1)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_groups_of_images_match_oracle(shape, bf16, monkeypatch):
+    """A layer launched in groups of two images (the limit in bytes lowered to
+    that), the last group smaller, with the forward's fused epilogue and sums."""
+    n, c, h, w, o, k, s = shape
+    print(f"narrow groups {shape} bf16={bf16}", flush=True)
+    cp = -(-c // 8) * 8 if bf16 else -(-c // 4) * 4
+    ho, wo = (h + 2 - k) // s + 1, (w + 2 - k) // s + 1
+    image = max(h * w * cp, ho * wo * o) * (2 if bf16 else 4)
+    monkeypatch.setenv("QLAYER_NARROW_BYTES", str(2 * image + image // 2))
+    inp = synth.random_conv_case([820] + list(shape), n, c, h, w, o, k, k, s, 1, bf16=bf16)
+    got = qlh.conv_to_np(qlh.run_conv(inp, s, 1, bf16))
+    y, ta, tb = oracle.conv2d_fwd(*(inp[v] for v in ("x", "wa", "wb", "wc", "ba", "bb", "bc")), s, 1)
+    ref = oracle.conv2d_bwd(*(inp[v] for v in ("x", "wa", "wb", "wc", "ba", "bb", "bc", "gy")), s, 1)
+    ref.update({"y": y, "ta": ta, "tb": tb})
+    for key in KEYS_FWD + KEYS_GRAD:
+        e = qlh.relerr(got[key], ref[key])
+        assert e <= qlh.tol(bf16, key in KEYS_GRAD), f"{key}: normwise relative error {e:.3e}"
+    d = ql.conv_desc(n, c, h, w, o, k, k, s, 1, qlh.qdtype(bf16))
+    out = torch.full((n, ho, wo, o), float("nan"), device=qlh.DEV, dtype=qlh.tdtype(bf16))
+    s1, s2 = (torch.full((o,), float("nan"), device=qlh.DEV) for _ in range(2))
+    ql.qlayer_conv2d_fwd_ex(d, qlh.nchw_to_dev(inp["x"], bf16), *(qlh.oihw_to_dev(inp[v], bf16) for v in ("wa", "wb", "wc")),
+                            *(qlh.vec_to_dev(inp[v]) for v in ("ba", "bb", "bc")), out,
+                            epi=ql.epilogue(relu=True, stat_sum=s1, stat_sumsq=s2))
+    torch.cuda.synchronize()
+    assert qlh.relerr(qlh.nhwc_to_np(out), y.clip(min=0)) <= qlh.tol(bf16, False)
+    v = out.double().reshape(-1, o)
+    u = v.shape[0] * 2.0 ** -24  # an fp32 sum of that many rows
+    assert torch.all((s1.double() - v.sum(0)).abs() <= u * v.abs().sum(0))
+    assert torch.all((s2.double() - (v * v).sum(0)).abs() <= 2 * u * (v * v).sum(0))

@@ -83,6 +83,10 @@ def test_passes_that_take_padded_copies(shape, dtype, neuron, padded):
     ((64, 256, 56, 256, 3, 1), BF16, Q, 256, "bwd_data", "qconv_dw_bwd_data_rows_kernel"),
     ((151, 352, 56, 352, 3, 1), BF16, T2, 352, "bwd_data", "qconv_dw_bwd_data_col_kernel"),
     ((151, 352, 56, 352, 3, 1), BF16, T2, 352, "fwd", "qconv_dw_fwd_col_kernel"),
+    # 2^31 bytes of X: groups of images in the narrow kernels
+    ((32, 16, 1024, 16, 3, 1), F32, Q, 1, "fwd", "qconv_fwd_narrow_kernel"),
+    ((32, 16, 1024, 16, 3, 1), F32, Q, 1, "bwd_data", "qconv_bwd_data_narrow_kernel"),
+    ((32, 16, 1024, 16, 3, 1), F32, Q, 1, "bwd_weight", "qconv_bwd_weight_narrow_kernel"),
 ], ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else None)
 def test_kernel_of_a_pass(shape, dtype, neuron, groups, which, kernel):
     names = launches(shape, dtype, neuron, groups, (which,))[which]
