@@ -29,6 +29,12 @@ constexpr int kNumCUs = 256;         // MI355X compute units
 constexpr size_t kAlign = 256;
 constexpr long long kMaxElems = (1LL << 31) - 1;  // 32-bit element offsets in the kernels
 constexpr size_t kMaxSplitBytes = 128ull << 20;  // cap on split-K partial sums (written + read once)
+// Cap on a pass's padded copies (Geom::pad_fwd and its neighbours): beyond it the
+// register-staged kernels take the tensors as they are, so that a layer of a
+// few channels off the vector does not need most of its tensors' memory again.
+// No line of speed: the copies pay at any size (60 -> 100 channels, 3 x 3, bf16, 5 to 9
+// times).  256 x 112 x 112 maps of 60 channels in bf16, three maps a call, stay below.
+constexpr size_t kMaxPadBytes = 2048ull << 20;
 // Split-K cost model, in units of one K step of one workgroup alone on a CU:
 // a CU holding two co-resident workgroups finishes both in kSharedRound steps
 // per step each (the second one hides the first one's latency), and one unit
@@ -112,11 +118,14 @@ struct Geom {
     bool pad_o_fits() const {
         return O % vec() != 0 && (long long)N * HO * WO * opad() <= kMaxElems && 3LL * C * KH * KW * opad() <= kMaxElems;
     }
+    // Bytes of the copies: of X, and of the neuron's output-side maps (G, T_a, T_b).
+    size_t pad_x_bytes() const { return (size_t)N * H * W * cpad() * esize(); }
+    size_t pad_maps_bytes() const { return om_gmaps(om()) * ((size_t)N * HO * WO * opad() * esize()); }
     // Where the filter reads less than a tenth of the pixels that the copy of X
     // moves: not if the copy is large and the layer's work is not (1 x 1 / 4,
     // 227 x 60 x 60 maps, 204 -> 116, bf16: forward 112 us as it is, 171 padded).
     bool pad_x_skips() const {
-        const double bytes = (double)N * H * W * cpad() * esize();
+        const double bytes = (double)pad_x_bytes();
         return 10.0 * KH * KW * HO * WO < (double)H * W && bytes > 3e7 && flops() < 64 * bytes;
     }
     // The passes' lines, from 5000 layers of random sizes timed both ways (for each
@@ -128,7 +137,7 @@ struct Geom {
     // (0.76 up to 48, 1.0 to 1.15 up to 256, 0.96 above; 1.35 from 1 GFLOP).
     bool pad_fwd() const {
         if (!pad_c_fits() || few_c()) return pad_c_fits();
-        if (!pad_pays() || pad_x_skips()) return false;
+        if (!pad_pays() || pad_x_skips() || pad_x_bytes() > kMaxPadBytes) return false;
         const int K = KH * KW * C;
         if (dt == QL_BF16 || ne == NEURON_QUADRA) return K > 64 / (int)esize() || O > 16;
         return flops() >= 1e9 || (K > 48 && K <= 256);
@@ -143,7 +152,8 @@ struct Geom {
         const bool s1 = SH == 1 && SW == 1;
         const int K = KH * KW * O;
         const long long px = (long long)N * H * W;
-        const double bytes = (double)om_gmaps(om()) * N * HO * WO * opad() * esize();
+        const double bytes = (double)pad_maps_bytes();
+        if (pad_maps_bytes() > kMaxPadBytes) return false;
         if (dt == QL_BF16)
             return ne == NEURON_QUADRA || K > 40 || flops() >= 5e7 || (C <= 64 && (!s1 || px >= 4096));
         if (ne == NEURON_QUADRA) return C <= 32 || (!(K <= 48 && bytes > 3.3e5 && s1) && !(K <= 16 && bytes > 3e6));
@@ -160,6 +170,7 @@ struct Geom {
         if (!offc && !offo) return false;
         if (offo || !few_c()) {
             if (!pad_pays() || (offc && pad_x_skips())) return false;
+            if ((offc ? pad_x_bytes() : 0) + (offo ? pad_maps_bytes() : 0) > kMaxPadBytes) return false;
         }
         if (dt == QL_BF16 || (narrow && offc && few_c() && !offo)) return true;
         return flops() >= (narrow ? 3.2e7 : 3e8) || (long long)N * HO * WO >= 20000;
