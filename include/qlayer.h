@@ -216,13 +216,18 @@ ql_status qlayer_conv2d_bwd_weight(const ql_conv_desc *desc, const void *x, cons
  * that cannot allocate device memory: code under HIP graph capture, tight
  * serving or training loops, harnesses that forbid hipMalloc.  The same
  * operation, arguments and errors as qlayer_conv2d_bwd_weight minus the
- * workspace: the split-K partial sums (and the zero-padded copy of X of
- * few-channel layers) go to a scratch array the library owns, of
- * QLAYER_NOALLOC_SCRATCH_BYTES bytes on each GPU it runs on, held until the
- * process ends.  Where the regular call's workspace query fits that size the
- * plan, and so every result bit, is the regular call's; otherwise the split
- * count is lowered to fit (results equal up to summation order); a layer
- * that does not fit even then returns QL_EWORKSPACE.  No device memory is
+ * workspace: the split-K partial sums, and the zero-padded copies that layers
+ * whose channel counts are not multiples of 16 bytes take (of X where C is
+ * not; of gy, ta and tb where O is not), go to a scratch array the library
+ * owns, of QLAYER_NOALLOC_SCRATCH_BYTES bytes on each GPU it runs on, held
+ * until the process ends.  Where the regular call's workspace query fits that
+ * size the plan, and so every result bit, is the regular call's.  Otherwise
+ * the split count is lowered to fit, and where the copies alone do not fit,
+ * the kernel that takes the tensors uncopied runs (results equal up to
+ * summation order in both cases).  QL_EWORKSPACE where neither is possible:
+ * a single split's sums above that size, and the layers of few input channels
+ * (C < 16 in bf16 with whole vectors of O; C < 8 in fp32 on the layers of the
+ * narrow kernel) whose copy of X is.  No device memory is
  * allocated by this call; the first call on a device resolves the array's
  * address there.  Every call on one GPU shares its array, which keeps the
  * last call's contents (nothing in it needs to start at zero): calls that

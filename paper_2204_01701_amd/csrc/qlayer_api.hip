@@ -226,8 +226,8 @@ ql_status bwd_weight_common(const Geom &g, const void *x, const void *gy, const 
             const size_t room = kScratchBytes - std::min(kScratchBytes, pads + 2 * kAlign);
             p = plan_bwd_weight(g, room / (kpo + 1) * kpo);
             // Padded copies that do not fit: the register-staged kernel, which needs none.
-            // (Not on the few-channel layers, C below two vectors and O whole vectors:
-            // they are refused here, as the header says.)
+            // (Not on the few-channel layers, C below two vectors and O whole vectors, of
+            // bf16 and of the narrow kernel: callers know them as refused, see qlayer.h.)
             if (p.ws_bytes > kScratchBytes && (p.padc || p.pado) && !p.few)
                 p = plan_bwd_weight(g, (kScratchBytes - 2 * kAlign) / (kpo + 1) * kpo, false);
         }
