@@ -233,19 +233,62 @@ def _workspace(workspace, need, device, stream=None):
     return ws.data_ptr(), need
 
 
-# --- host-side checks of tensor arguments -------------------------------------
+# --- tensor operands: checks and pointers --------------------------------------
 # The C ABI sees bare pointers, so a tensor of the wrong size, dtype or device
 # would make the kernels read or write out of bounds.  Every tensor argument is
-# checked against the descriptor before the call: a CUDA tensor on the
-# device of the others, with the element count and dtype its role requires.
+# checked against the descriptor before the call: a contiguous CUDA tensor on
+# the device of the others, with the element count and dtype that its role in
+# _OPERANDS requires.
+#
+# A small layer's pass is a few microseconds of GPU work, so the host's share
+# of a call counts: _pointers checks in one loop with a few attribute reads
+# per tensor.  On anything it does not accept (a wrong tensor, raw pointers, an
+# unknown dtype) the call goes on in _checked_pointers, which holds the same
+# operands against the same requirements and raises what is to be raised.
 
-def _act_dtype(code):
-    import torch
-    if code == QL_BF16:
-        return torch.bfloat16
-    if code == QL_F32:
-        return torch.float32
-    return None  # (the library rejects unknown dtypes itself)
+# The tensor operands of an entry point in the order of its arguments, as
+# name:role; the roles are those of _conv_needs.
+_OPERANDS = {name: tuple(tuple(o.split(":")) for o in ops.split()) for name, ops in {
+    "qlayer_conv2d_fwd": "x:x wa:w wb:w wc:w ba:b bb:b bc:b y:y ta:y tb:y",
+    "qlayer_conv2d_fwd_ex": "x:x wa:w wb:w wc:w ba:b bb:b bc:b y:y ta:y tb:y",
+    "qlayer_conv2d_bwd_data": "gy:y ta:t tb:y wa:w wb:w wc:w dx:x",
+    "qlayer_conv2d_bwd_data_ex": "gy:y ta:t tb:y x:x wa:w wb:w wc:w dx:x",
+    "qlayer_conv2d_bwd_weight": "x:x gy:y ta:y tb:y dwa:g dwb:g dwc:g dba:b dbb:b dbc:b",
+    "qlayer_conv2d_bwd_weight_noalloc": "x:x gy:y ta:y tb:y dwa:g dwb:g dwc:g dba:b dbb:b dbc:b",
+    "qlayer_conv2d_bwd_relu": "x:x gy:y y_out:y ta:y tb:y wa:w wb:w wc:w dx:x dwa:g dwb:g dwc:g dba:b dbb:b dbc:b",
+    "qlayer_linear_fwd": "x:x wa:w wb:w wc:w ba:b bb:b bc:b y:y ta:y tb:y",
+    "qlayer_linear_fwd_ex": "x:x wa:w wb:w wc:w ba:b bb:b bc:b y:y ta:y tb:y",
+    "qlayer_linear_bwd": "x:x gy:y ta:y tb:y wa:w wb:w wc:w dx:x dwa:g dwb:g dwc:g dba:b dbb:b dbc:b",
+    "qlayer_linear_bwd_relu": "x:x gy:y y_out:y ta:y tb:y wa:w wb:w wc:w dx:x dwa:g dwb:g dwc:g dba:b dbb:b dbc:b",
+}.items()}
+
+_CONV_FIELDS = struct.Struct("14i")  # ConvDesc
+_LINEAR_FIELDS = struct.Struct("5i")  # LinearDesc
+_dtypes = {}  # (filled on the first call: importing this module does not import torch)
+
+
+def _needs(nx, nw, ny, no, code, t2=False):
+    """Element count and dtype per role: "x" shaped like X, "w" a weight, "y" an
+    output-side map, "t" the map T_a (X for the T2 neuron), "b" float32 of O, "g" a
+    float32 weight gradient.  dtype None: a code the library rejects itself."""
+    if not _dtypes:
+        import torch
+        _dtypes.update({QL_F32: torch.float32, QL_BF16: torch.bfloat16})
+    dt, f32 = _dtypes.get(code), _dtypes[QL_F32]
+    x, y = (nx, dt), (ny, dt)
+    return {"x": x, "w": (nw, dt), "y": y, "t": x if t2 else y, "b": (no, f32), "g": (nw, f32)}
+
+
+def _conv_needs(d):
+    n, c, h, w, o, kh, kw, sh, sw, ph, pw, code, neuron, groups = _CONV_FIELDS.unpack_from(d)
+    ny = n * ((h + 2 * ph - kh) // sh + 1) * ((w + 2 * pw - kw) // sw + 1) * o
+    nw = o * kh * kw * (1 if groups == c and c > 1 else c)
+    return _needs(n * h * w * c, nw, ny, o, code, neuron == QL_NEURON_T2)
+
+
+def _linear_needs(d):
+    b, i, o, code, _ = _LINEAR_FIELDS.unpack_from(d)
+    return _needs(b * i, o * i, b * o, o, code)
 
 
 def _expect(name, t, numel, dtype, device):
@@ -261,107 +304,25 @@ def _expect(name, t, numel, dtype, device):
         raise ValueError(f"{name}: dtype {t.dtype}, expected {dtype}")
 
 
-def _conv_sizes(d):
-    """Element counts of X, each W_t, the output-side maps, the biases."""
-    dw = d.groups == d.c and d.c > 1
-    nw = d.o * d.kh * d.kw * (1 if dw else d.c)
-    return d.n * d.h * d.w * d.c, nw, d.n * d.ho * d.wo * d.o, d.o
+def _checked_pointers(needs, operands, tensors):
+    """The pointers of `tensors` (raw pointers pass through) and their torch device."""
+    dev = _device(*tensors)
+    for (name, role), t in zip(operands, tensors):
+        _expect(name, t, *needs[role], dev)
+    return [_ptr(t) for t in tensors], dev
 
 
-def _linear_sizes(d):
-    return d.batch * d.in_, d.out * d.in_, d.batch * d.out, d.out
-
-
-def _check_args(sizes, dtype_code, device, act=(), weights=(), maps=(), vec32=(), w32=()):
-    """act: (name, tensor) pairs shaped like X; weights like W_t; maps like Y;
-    vec32: float32 vectors of O; w32: float32 tensors shaped like W_t."""
-    nx, nw, ny, no = sizes
-    import torch
-    dt = _act_dtype(dtype_code)
-    for n, t in act:
-        _expect(n, t, nx, dt, device)
-    for n, t in weights:
-        _expect(n, t, nw, dt, device)
-    for n, t in maps:
-        _expect(n, t, ny, dt, device)
-    for n, t in vec32:
-        _expect(n, t, no, torch.float32, device)
-    for n, t in w32:
-        _expect(n, t, nw, torch.float32, device)
-
-
-def _check(func, status):
-    if status != 0:
-        raise QLError(func, status)
-
-
-# --- the short way through a call -----------------------------------------------
-# A small layer's pass is a few microseconds of GPU work, so the host's share
-# of a call counts: the checks above, one Python call and several attribute
-# lookups per tensor, took more than the launches did.  _pointers makes the same
-# checks in one loop and returns the pointers; on anything unusual (a wrong
-# tensor, raw pointers, an unknown dtype) it returns None and the caller goes
-# through the checks above, which raise what is to be raised.
-
-_CONV_FIELDS = struct.Struct("14i")  # ConvDesc
-_LINEAR_FIELDS = struct.Struct("5i")  # LinearDesc
-_dtypes = {}  # (filled on the first call: importing this module does not import torch)
-
-
-def _conv_plan(d):
-    """_conv_sizes and the dtype code, from one read of the descriptor."""
-    n, c, h, w, o, kh, kw, sh, sw, ph, pw, dt, _, groups = _CONV_FIELDS.unpack_from(d)
-    if sh < 1 or sw < 1:
-        return None
-    ny = n * ((h + 2 * ph - kh) // sh + 1) * ((w + 2 * pw - kw) // sw + 1) * o
-    return n * h * w * c, o * kh * kw * (1 if groups == c and c > 1 else c), ny, o, dt
-
-
-def _linear_plan(d):
-    b, i, o, dt, _ = _LINEAR_FIELDS.unpack_from(d)
-    return b * i, o * i, b * o, o, dt
-
-
-def _current_stream(dev):
-    """Handle of the current stream of device `dev` (without building a torch.cuda.Stream)."""
-    import torch
-    return torch._C._cuda_getCurrentRawStream(dev)
-
-
-def _pointers(plan, roles, tensors):
-    """The data pointers of `tensors` (None: NULL) and their device index, or None.
-
-    roles: per tensor "x" (shaped like X), "w" (a weight), "y" (an output-side
-    map), "b" (float32 of O) or "g" (a float32 weight gradient)."""
-    if plan is None:
-        return None
-    nx, nw, ny, no, code = plan
-    dt = _dtypes.get(code)
-    if dt is None:
-        if _dtypes:
-            return None
-        import torch
-        _dtypes.update({QL_F32: torch.float32, QL_BF16: torch.bfloat16})
-        dt = _dtypes.get(code)
-    f32 = _dtypes[QL_F32]
+def _pointers(needs, operands, tensors):
+    """The data pointers of `tensors` (None: NULL) and their device index, or None."""
     out, dev = [], -1
-    for role, t in zip(roles, tensors):
+    for (_, role), t in zip(operands, tensors):
         if t is None:
             out.append(None)
             continue
-        if t.__class__ is int:
+        if isinstance(t, int):
             return None
-        if role == "y":
-            n, d = ny, dt
-        elif role == "w":
-            n, d = nw, dt
-        elif role == "x":
-            n, d = nx, dt
-        elif role == "b":
-            n, d = no, f32
-        else:
-            n, d = nw, f32
-        if t.numel() != n or t.dtype is not d or not t.is_cuda or not t.is_contiguous() or dt is None:
+        n, d = needs[role]
+        if t.numel() != n or t.dtype is not d or not t.is_cuda or not t.is_contiguous():
             return None
         i = t.get_device()
         if i != dev:
@@ -372,34 +333,62 @@ def _pointers(plan, roles, tensors):
     return (out, dev) if dev >= 0 else None
 
 
-def _call(name, query, desc, plan, roles, tensors, workspace, stream, epi=None, query_epi=False, extra=()):
-    """Run the entry point `name` on checked tensors; False if they need the long way.
-
-    extra: the epilogue's tensors (float32 of O; checked, their pointers are in epi)."""
-    got = _pointers(plan, roles + "b" * len(extra), (*tensors, *extra))
-    if got is None:
-        return False
-    ptrs, dev = got
-    del ptrs[len(tensors):]
-    if stream is None:
-        st = _current_stream(dev)
-    else:
-        st = stream if isinstance(stream, int) else stream.cuda_stream
-    ref = ctypes.byref(desc)
-    L = lib()
-    if workspace is None:
-        need = getattr(L, query)(ref, epi) if query_epi else getattr(L, query)(ref)
-        import torch
-        wp, wn = _workspace(None, need, torch.device("cuda", dev), stream)
-    elif isinstance(workspace, tuple):
-        wp, wn = workspace
-    else:
-        wp, wn = workspace.data_ptr(), workspace.numel() * workspace.element_size()
-    f = getattr(L, name)
-    status = f(ref, *ptrs, epi, wp, wn, st) if query_epi else f(ref, *ptrs, wp, wn, st)
+def _check(func, status):
     if status != 0:
-        raise QLError(name, status)
-    return True
+        raise QLError(func, status)
+
+
+def _current_stream(dev):
+    """Handle of the current stream of device `dev`."""
+    import torch
+    # the handle itself, without building a torch.cuda.Stream, where torch has it
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    return raw(dev) if raw is not None else torch.cuda.current_stream(dev).cuda_stream
+
+
+def _run(name, desc, needs, tensors, workspace, stream, epi=None):
+    """The entry point `name` on its operands: checks, workspace, stream, call.
+
+    epi: the epilogue of an _ex forward (a one-element tuple, its value None or an
+    Epilogue, whose tensors are checked with the others)."""
+    operands = _OPERANDS[name]
+    n = len(tensors)
+    if epi is not None and epi[0] is not None:
+        extra = getattr(epi[0], "tensors", ())
+        operands += tuple((en, "b") for en, _ in extra)
+        tensors += tuple(t for _, t in extra)
+    got = _pointers(needs, operands, tensors)
+    L = lib()
+    ref = ctypes.byref(desc)
+    args = () if epi is None else (_epi_ref(epi[0]),)
+    if got is not None:
+        ptrs, dev = got
+        if stream is None:
+            st = _current_stream(dev)
+        else:
+            st = stream if isinstance(stream, int) else stream.cuda_stream
+    else:
+        ptrs, dev = _checked_pointers(needs, operands, tensors)
+        st = _stream(stream, dev)
+    del ptrs[n:]
+    if workspace is _NO_WORKSPACE:
+        _check(name, getattr(L, name)(ref, *ptrs, st))
+        return
+    if workspace is None:
+        # (both input gradients share one query; the epilogue's sums need room too)
+        query = _QUERIES.get(name, name + "_workspace_size")
+        need = getattr(L, query)(ref, *args)
+        if got is not None and need:
+            import torch
+            dev = torch.device("cuda", dev)
+        wp, wn = _workspace(None, need, dev, stream)
+    else:
+        wp, wn = _workspace(workspace, 0, dev)
+    _check(name, getattr(L, name)(ref, *ptrs, *args, wp, wn, st))
+
+
+_NO_WORKSPACE = object()
+_QUERIES = {"qlayer_conv2d_bwd_data_ex": "qlayer_conv2d_bwd_data_workspace_size"}
 
 
 # --- the C ABI, one Python function per entry point -------------------------
@@ -410,16 +399,8 @@ def qlayer_conv2d_fwd_workspace_size(desc: ConvDesc) -> int:
 
 def qlayer_conv2d_fwd(desc, x, wa, wb, wc, ba=None, bb=None, bc=None, y=None, ta=None, tb=None,
                       workspace=None, stream=None):
-    if _call("qlayer_conv2d_fwd", "qlayer_conv2d_fwd_workspace_size", desc, _conv_plan(desc), "xwwwbbbyyy",
-             (x, wa, wb, wc, ba, bb, bc, y, ta, tb), workspace, stream):
-        return
-    dev = _device(x, wa)
-    _check_args(_conv_sizes(desc), desc.dtype, dev, act=[("x", x)], weights=[("wa", wa), ("wb", wb), ("wc", wc)],
-                maps=[("y", y), ("ta", ta), ("tb", tb)], vec32=[("ba", ba), ("bb", bb), ("bc", bc)])
-    wp, wn = _workspace(workspace, qlayer_conv2d_fwd_workspace_size(desc), dev, stream)
-    _check("qlayer_conv2d_fwd", lib().qlayer_conv2d_fwd(
-        ctypes.byref(desc), _ptr(x), _ptr(wa), _ptr(wb), _ptr(wc), _ptr(ba), _ptr(bb), _ptr(bc),
-        _ptr(y), _ptr(ta), _ptr(tb), wp, wn, _stream(stream, dev)))
+    _run("qlayer_conv2d_fwd", desc, _conv_needs(desc),
+         (x, wa, wb, wc, ba, bb, bc, y, ta, tb), workspace, stream)
 
 
 def qlayer_conv2d_bwd_data_workspace_size(desc: ConvDesc) -> int:
@@ -427,34 +408,14 @@ def qlayer_conv2d_bwd_data_workspace_size(desc: ConvDesc) -> int:
 
 
 def qlayer_conv2d_bwd_data(desc, gy, ta, tb, wa, wb, wc, dx, workspace=None, stream=None):
-    t2 = desc.neuron == QL_NEURON_T2  # (its `ta` carries X)
-    if _call("qlayer_conv2d_bwd_data", "qlayer_conv2d_bwd_data_workspace_size", desc, _conv_plan(desc),
-             "yxywwwx" if t2 else "yyywwwx", (gy, ta, tb, wa, wb, wc, dx), workspace, stream):
-        return
-    dev = _device(gy, wa)
-    _check_args(_conv_sizes(desc), desc.dtype, dev, act=[("dx", dx)] + ([("ta (X)", ta)] if t2 else []),
-                weights=[("wa", wa), ("wb", wb), ("wc", wc)],
-                maps=[("gy", gy), ("tb", tb)] + ([] if t2 else [("ta", ta)]))
-    wp, wn = _workspace(workspace, qlayer_conv2d_bwd_data_workspace_size(desc), dev, stream)
-    _check("qlayer_conv2d_bwd_data", lib().qlayer_conv2d_bwd_data(
-        ctypes.byref(desc), _ptr(gy), _ptr(ta), _ptr(tb), _ptr(wa), _ptr(wb), _ptr(wc), _ptr(dx),
-        wp, wn, _stream(stream, dev)))
+    _run("qlayer_conv2d_bwd_data", desc, _conv_needs(desc),
+         (gy, ta, tb, wa, wb, wc, dx), workspace, stream)
 
 
 def qlayer_conv2d_bwd_data_ex(desc, gy, ta, tb, x, wa, wb, wc, dx, workspace=None, stream=None):
     """qlayer_conv2d_bwd_data with the layer input X (T2&4 needs it; T2 may take it in place of `ta`)."""
-    t2 = desc.neuron == QL_NEURON_T2
-    if _call("qlayer_conv2d_bwd_data_ex", "qlayer_conv2d_bwd_data_workspace_size", desc, _conv_plan(desc),
-             "yxyxwwwx" if t2 else "yyyxwwwx", (gy, ta, tb, x, wa, wb, wc, dx), workspace, stream):
-        return
-    dev = _device(gy, wa)
-    _check_args(_conv_sizes(desc), desc.dtype, dev, act=[("dx", dx), ("x", x)] + ([("ta (X)", ta)] if t2 else []),
-                weights=[("wa", wa), ("wb", wb), ("wc", wc)],
-                maps=[("gy", gy), ("tb", tb)] + ([] if t2 else [("ta", ta)]))
-    wp, wn = _workspace(workspace, qlayer_conv2d_bwd_data_workspace_size(desc), dev, stream)
-    _check("qlayer_conv2d_bwd_data_ex", lib().qlayer_conv2d_bwd_data_ex(
-        ctypes.byref(desc), _ptr(gy), _ptr(ta), _ptr(tb), _ptr(x), _ptr(wa), _ptr(wb), _ptr(wc), _ptr(dx),
-        wp, wn, _stream(stream, dev)))
+    _run("qlayer_conv2d_bwd_data_ex", desc, _conv_needs(desc),
+         (gy, ta, tb, x, wa, wb, wc, dx), workspace, stream)
 
 
 def qlayer_conv2d_bwd_weight_workspace_size(desc: ConvDesc) -> int:
@@ -463,16 +424,8 @@ def qlayer_conv2d_bwd_weight_workspace_size(desc: ConvDesc) -> int:
 
 def qlayer_conv2d_bwd_weight(desc, x, gy, ta, tb, dwa, dwb, dwc, dba=None, dbb=None, dbc=None,
                              workspace=None, stream=None):
-    if _call("qlayer_conv2d_bwd_weight", "qlayer_conv2d_bwd_weight_workspace_size", desc, _conv_plan(desc),
-             "xyyygggbbb", (x, gy, ta, tb, dwa, dwb, dwc, dba, dbb, dbc), workspace, stream):
-        return
-    dev = _device(x, gy)
-    _check_args(_conv_sizes(desc), desc.dtype, dev, act=[("x", x)], maps=[("gy", gy), ("ta", ta), ("tb", tb)],
-                w32=[("dwa", dwa), ("dwb", dwb), ("dwc", dwc)], vec32=[("dba", dba), ("dbb", dbb), ("dbc", dbc)])
-    wp, wn = _workspace(workspace, qlayer_conv2d_bwd_weight_workspace_size(desc), dev, stream)
-    _check("qlayer_conv2d_bwd_weight", lib().qlayer_conv2d_bwd_weight(
-        ctypes.byref(desc), _ptr(x), _ptr(gy), _ptr(ta), _ptr(tb), _ptr(dwa), _ptr(dwb), _ptr(dwc),
-        _ptr(dba), _ptr(dbb), _ptr(dbc), wp, wn, _stream(stream, dev)))
+    _run("qlayer_conv2d_bwd_weight", desc, _conv_needs(desc),
+         (x, gy, ta, tb, dwa, dwb, dwc, dba, dbb, dbc), workspace, stream)
 
 
 NOALLOC_SCRATCH_BYTES = 32 << 20  # QLAYER_NOALLOC_SCRATCH_BYTES of qlayer.h
@@ -482,12 +435,8 @@ def qlayer_conv2d_bwd_weight_noalloc(desc, x, gy, ta, tb, dwa, dwb, dwc, dba=Non
                                      stream=None):
     """qlayer_conv2d_bwd_weight with the library's own scratch array in place of a
     workspace: allocates nothing (for graph capture and other callers that cannot)."""
-    dev = _device(x, gy)
-    _check_args(_conv_sizes(desc), desc.dtype, dev, act=[("x", x)], maps=[("gy", gy), ("ta", ta), ("tb", tb)],
-                w32=[("dwa", dwa), ("dwb", dwb), ("dwc", dwc)], vec32=[("dba", dba), ("dbb", dbb), ("dbc", dbc)])
-    _check("qlayer_conv2d_bwd_weight_noalloc", lib().qlayer_conv2d_bwd_weight_noalloc(
-        ctypes.byref(desc), _ptr(x), _ptr(gy), _ptr(ta), _ptr(tb), _ptr(dwa), _ptr(dwb), _ptr(dwc),
-        _ptr(dba), _ptr(dbb), _ptr(dbc), _stream(stream, dev)))
+    _run("qlayer_conv2d_bwd_weight_noalloc", desc, _conv_needs(desc),
+         (x, gy, ta, tb, dwa, dwb, dwc, dba, dbb, dbc), _NO_WORKSPACE, stream)
 
 
 def qlayer_linear_fwd_workspace_size(desc: LinearDesc) -> int:
@@ -496,16 +445,8 @@ def qlayer_linear_fwd_workspace_size(desc: LinearDesc) -> int:
 
 def qlayer_linear_fwd(desc, x, wa, wb, wc, ba=None, bb=None, bc=None, y=None, ta=None, tb=None,
                       workspace=None, stream=None):
-    if _call("qlayer_linear_fwd", "qlayer_linear_fwd_workspace_size", desc, _linear_plan(desc), "xwwwbbbyyy",
-             (x, wa, wb, wc, ba, bb, bc, y, ta, tb), workspace, stream):
-        return
-    dev = _device(x, wa)
-    _check_args(_linear_sizes(desc), desc.dtype, dev, act=[("x", x)], weights=[("wa", wa), ("wb", wb), ("wc", wc)],
-                maps=[("y", y), ("ta", ta), ("tb", tb)], vec32=[("ba", ba), ("bb", bb), ("bc", bc)])
-    wp, wn = _workspace(workspace, qlayer_linear_fwd_workspace_size(desc), dev, stream)
-    _check("qlayer_linear_fwd", lib().qlayer_linear_fwd(
-        ctypes.byref(desc), _ptr(x), _ptr(wa), _ptr(wb), _ptr(wc), _ptr(ba), _ptr(bb), _ptr(bc),
-        _ptr(y), _ptr(ta), _ptr(tb), wp, wn, _stream(stream, dev)))
+    _run("qlayer_linear_fwd", desc, _linear_needs(desc),
+         (x, wa, wb, wc, ba, bb, bc, y, ta, tb), workspace, stream)
 
 
 def _epi_ref(epi):
@@ -519,18 +460,8 @@ def qlayer_conv2d_fwd_ex_workspace_size(desc: ConvDesc, epi=None) -> int:
 def qlayer_conv2d_fwd_ex(desc, x, wa, wb, wc, ba=None, bb=None, bc=None, y=None, ta=None, tb=None, epi=None,
                          workspace=None, stream=None):
     """qlayer_conv2d_fwd with a fused epilogue (an Epilogue, see epilogue())."""
-    extra = [t for _, t in getattr(epi, "tensors", ())]
-    if _call("qlayer_conv2d_fwd_ex", "qlayer_conv2d_fwd_ex_workspace_size", desc, _conv_plan(desc),
-             "xwwwbbbyyy", (x, wa, wb, wc, ba, bb, bc, y, ta, tb), workspace, stream, _epi_ref(epi), True, extra):
-        return
-    dev = _device(x, wa)
-    _check_args(_conv_sizes(desc), desc.dtype, dev, act=[("x", x)], weights=[("wa", wa), ("wb", wb), ("wc", wc)],
-                maps=[("y", y), ("ta", ta), ("tb", tb)],
-                vec32=[("ba", ba), ("bb", bb), ("bc", bc)] + list(getattr(epi, "tensors", [])))
-    wp, wn = _workspace(workspace, qlayer_conv2d_fwd_ex_workspace_size(desc, epi), dev, stream)
-    _check("qlayer_conv2d_fwd_ex", lib().qlayer_conv2d_fwd_ex(
-        ctypes.byref(desc), _ptr(x), _ptr(wa), _ptr(wb), _ptr(wc), _ptr(ba), _ptr(bb), _ptr(bc),
-        _ptr(y), _ptr(ta), _ptr(tb), _epi_ref(epi), wp, wn, _stream(stream, dev)))
+    _run("qlayer_conv2d_fwd_ex", desc, _conv_needs(desc),
+         (x, wa, wb, wc, ba, bb, bc, y, ta, tb), workspace, stream, (epi,))
 
 
 def qlayer_linear_fwd_ex_workspace_size(desc: LinearDesc, epi=None) -> int:
@@ -540,18 +471,8 @@ def qlayer_linear_fwd_ex_workspace_size(desc: LinearDesc, epi=None) -> int:
 def qlayer_linear_fwd_ex(desc, x, wa, wb, wc, ba=None, bb=None, bc=None, y=None, ta=None, tb=None, epi=None,
                          workspace=None, stream=None):
     """qlayer_linear_fwd with a fused epilogue (an Epilogue, see epilogue())."""
-    extra = [t for _, t in getattr(epi, "tensors", ())]
-    if _call("qlayer_linear_fwd_ex", "qlayer_linear_fwd_ex_workspace_size", desc, _linear_plan(desc),
-             "xwwwbbbyyy", (x, wa, wb, wc, ba, bb, bc, y, ta, tb), workspace, stream, _epi_ref(epi), True, extra):
-        return
-    dev = _device(x, wa)
-    _check_args(_linear_sizes(desc), desc.dtype, dev, act=[("x", x)], weights=[("wa", wa), ("wb", wb), ("wc", wc)],
-                maps=[("y", y), ("ta", ta), ("tb", tb)],
-                vec32=[("ba", ba), ("bb", bb), ("bc", bc)] + list(getattr(epi, "tensors", [])))
-    wp, wn = _workspace(workspace, qlayer_linear_fwd_ex_workspace_size(desc, epi), dev, stream)
-    _check("qlayer_linear_fwd_ex", lib().qlayer_linear_fwd_ex(
-        ctypes.byref(desc), _ptr(x), _ptr(wa), _ptr(wb), _ptr(wc), _ptr(ba), _ptr(bb), _ptr(bc),
-        _ptr(y), _ptr(ta), _ptr(tb), _epi_ref(epi), wp, wn, _stream(stream, dev)))
+    _run("qlayer_linear_fwd_ex", desc, _linear_needs(desc),
+         (x, wa, wb, wc, ba, bb, bc, y, ta, tb), workspace, stream, (epi,))
 
 
 def qlayer_linear_bwd_workspace_size(desc: LinearDesc) -> int:
@@ -560,34 +481,8 @@ def qlayer_linear_bwd_workspace_size(desc: LinearDesc) -> int:
 
 def qlayer_linear_bwd(desc, x, gy, ta, tb, wa, wb, wc, dx=None, dwa=None, dwb=None, dwc=None,
                       dba=None, dbb=None, dbc=None, workspace=None, stream=None):
-    if _call("qlayer_linear_bwd", "qlayer_linear_bwd_workspace_size", desc, _linear_plan(desc), "xyyywwwxgggbbb",
-             (x, gy, ta, tb, wa, wb, wc, dx, dwa, dwb, dwc, dba, dbb, dbc), workspace, stream):
-        return
-    dev = _device(x, gy)
-    _check_args(_linear_sizes(desc), desc.dtype, dev, act=[("x", x), ("dx", dx)],
-                weights=[("wa", wa), ("wb", wb), ("wc", wc)], maps=[("gy", gy), ("ta", ta), ("tb", tb)],
-                w32=[("dwa", dwa), ("dwb", dwb), ("dwc", dwc)], vec32=[("dba", dba), ("dbb", dbb), ("dbc", dbc)])
-    wp, wn = _workspace(workspace, qlayer_linear_bwd_workspace_size(desc), dev, stream)
-    _check("qlayer_linear_bwd", lib().qlayer_linear_bwd(
-        ctypes.byref(desc), _ptr(x), _ptr(gy), _ptr(ta), _ptr(tb), _ptr(wa), _ptr(wb), _ptr(wc),
-        _ptr(dx), _ptr(dwa), _ptr(dwb), _ptr(dwc), _ptr(dba), _ptr(dbb), _ptr(dbc),
-        wp, wn, _stream(stream, dev)))
-
-
-def _bwd_relu(name, sizes, wsize, desc, x, gy, y_out, ta, tb, wa, wb, wc, dx, dwa, dwb, dwc, dba, dbb, dbc,
-              workspace, stream):
-    plan = _conv_plan(desc) if isinstance(desc, ConvDesc) else _linear_plan(desc)
-    if _call(name, name + "_workspace_size", desc, plan, "xyyyywwwxgggbbb",
-             (x, gy, y_out, ta, tb, wa, wb, wc, dx, dwa, dwb, dwc, dba, dbb, dbc), workspace, stream):
-        return
-    dev = _device(x, gy)
-    _check_args(sizes, desc.dtype, dev, act=[("x", x), ("dx", dx)], weights=[("wa", wa), ("wb", wb), ("wc", wc)],
-                maps=[("gy", gy), ("y_out", y_out), ("ta", ta), ("tb", tb)],
-                w32=[("dwa", dwa), ("dwb", dwb), ("dwc", dwc)], vec32=[("dba", dba), ("dbb", dbb), ("dbc", dbc)])
-    wp, wn = _workspace(workspace, wsize(desc), dev, stream)
-    _check(name, getattr(lib(), name)(
-        ctypes.byref(desc), _ptr(x), _ptr(gy), _ptr(y_out), _ptr(ta), _ptr(tb), _ptr(wa), _ptr(wb), _ptr(wc),
-        _ptr(dx), _ptr(dwa), _ptr(dwb), _ptr(dwc), _ptr(dba), _ptr(dbb), _ptr(dbc), wp, wn, _stream(stream, dev)))
+    _run("qlayer_linear_bwd", desc, _linear_needs(desc),
+         (x, gy, ta, tb, wa, wb, wc, dx, dwa, dwb, dwc, dba, dbb, dbc), workspace, stream)
 
 
 def qlayer_conv2d_bwd_relu_workspace_size(desc: ConvDesc) -> int:
@@ -597,8 +492,8 @@ def qlayer_conv2d_bwd_relu_workspace_size(desc: ConvDesc) -> int:
 def qlayer_conv2d_bwd_relu(desc, x, gy, y_out, ta, tb, wa, wb, wc, dx=None, dwa=None, dwb=None, dwc=None,
                            dba=None, dbb=None, dbc=None, workspace=None, stream=None):
     """The layer's backward behind the fused ReLU: G = gy o [y_out > 0], then dX and/or dW_t, db_t from G."""
-    _bwd_relu("qlayer_conv2d_bwd_relu", _conv_sizes(desc), qlayer_conv2d_bwd_relu_workspace_size, desc, x, gy, y_out,
-              ta, tb, wa, wb, wc, dx, dwa, dwb, dwc, dba, dbb, dbc, workspace, stream)
+    _run("qlayer_conv2d_bwd_relu", desc, _conv_needs(desc),
+         (x, gy, y_out, ta, tb, wa, wb, wc, dx, dwa, dwb, dwc, dba, dbb, dbc), workspace, stream)
 
 
 def qlayer_linear_bwd_relu_workspace_size(desc: LinearDesc) -> int:
@@ -608,8 +503,8 @@ def qlayer_linear_bwd_relu_workspace_size(desc: LinearDesc) -> int:
 def qlayer_linear_bwd_relu(desc, x, gy, y_out, ta, tb, wa, wb, wc, dx=None, dwa=None, dwb=None, dwc=None,
                            dba=None, dbb=None, dbc=None, workspace=None, stream=None):
     """The dense layer's backward behind the fused ReLU (as qlayer_conv2d_bwd_relu)."""
-    _bwd_relu("qlayer_linear_bwd_relu", _linear_sizes(desc), qlayer_linear_bwd_relu_workspace_size, desc, x, gy,
-              y_out, ta, tb, wa, wb, wc, dx, dwa, dwb, dwc, dba, dbb, dbc, workspace, stream)
+    _run("qlayer_linear_bwd_relu", desc, _linear_needs(desc),
+         (x, gy, y_out, ta, tb, wa, wb, wc, dx, dwa, dwb, dwc, dba, dbb, dbc), workspace, stream)
 
 
 # --- the network glue (include/qnet.h) ----------------------------------------
