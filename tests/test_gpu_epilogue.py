@@ -38,6 +38,8 @@ CONV_CASES = [
     ("narrow-stem", 3, 3, 10, 10, 16, 3, 1, 1, 1, {}),       # ... on the zero-padded 3-channel stem
     ("depthwise", 2, 32, 9, 7, 32, 3, 1, 1, 32, {}),
     ("depthwise-5x5", 2, 24, 8, 8, 24, 5, 1, 2, 24, {}),
+    ("padded", 8, 60, 13, 9, 100, 3, 1, 1, 1, {}),           # channels off the vector: on a padded copy of X
+    ("padded-odd", 6, 131, 9, 7, 73, 3, 2, 1, 1, {}),
 ]
 MODES = [  # scale, shift, relu, stats
     ("stats", False, False, False, True),

@@ -3,8 +3,8 @@ meets only the taps of its stride offset): maps that the strides do not
 divide, strides that differ, phases without taps (a filter smaller than the
 stride) or without pixels (a map smaller than it), split-K, the narrow kernel
 (C <= 16), padded channels, strides with more phases than the narrow kernel's
-arguments list, and one with too many, against the fp64 oracle element by
-element."""
+arguments list, and one with too many, the tiles with channel-aligned steps,
+against the fp64 oracle element by element."""
 import numpy as np
 import pytest
 import torch
@@ -70,10 +70,28 @@ def test_strided_input_gradient_matches_oracle(shape, bf16):
     qlh.check_elementwise("dx", "dx", qlh.nhwc_to_np(dx), ref, mag, bf16, 3 * O * K * K)
 
 
+# (C a multiple of 8, O of 32: K steps within one tap, scalar weight addresses)
+ALIGNED = [
+    (3, 136, 11, 8, 96, 3, (2, 2), 1),    # ragged maps and rows
+    (2, 72, 9, 10, 64, 1, (2, 2), 0),     # three of four phases without taps
+    (4, 256, 5, 5, 256, 3, (2, 2), 1),    # split-K
+    (1, 104, 6, 13, 32, 3, (3, 2), 1),    # one step per tap; strides that differ
+]
+
+
+@pytest.mark.parametrize("cfg", [3, 2], ids=["tile128x128", "tile128x64"])
+@pytest.mark.parametrize("shape", ALIGNED, ids=lambda s: "x".join(map(str, s)).replace(" ", ""))
+def test_strided_channel_aligned_tiles_match_oracle(shape, cfg, monkeypatch):
+    monkeypatch.setenv("QLAYER_BWD_DATA_CFG", str(cfg))
+    monkeypatch.setenv("QLAYER_BWD_DATA_CA", "1")
+    test_strided_input_gradient_matches_oracle(shape, True)
+
+
 @pytest.mark.parametrize("bf16", [False, True], ids=["fp32", "bf16"])
+@pytest.mark.parametrize("C", [40, 136], ids=["64rows", "128rows"])  # (bf16: 128-row tiles with channel-aligned steps)
 @pytest.mark.parametrize("neuron", [T4, T3, T2, T24], ids=lambda n: NAMES[n])
-def test_strided_neuron_types_match_oracle(neuron, bf16):
-    N, C, H, W, O, K, s, p = 2, 40, 7, 9, 64, 3, 2, 1
+def test_strided_neuron_types_match_oracle(neuron, C, bf16):
+    N, H, W, O, K, s, p = 2, 7, 9, 64, 3, 2, 1
     print(f"strided neuron {NAMES[neuron]} bf16={bf16}", flush=True)
     inp = synth.random_conv_case([982, neuron], N, C, H, W, O, K, K, s, p, bf16=bf16)
     nt = TERMS[neuron]
