@@ -358,7 +358,7 @@ _KERNEL_FAMILY = [
     (r"qconv_bwd_weight_reduce_kernel<", "bwd_weight", False),
     (r"qconv_bwd_weight_reduce2d_kernel<", "bwd_weight", False),
     (r"qconv_bwd_weight_reduce2dv_kernel[<(]", "bwd_weight", False),
-    (r"qconv_pad_rows_kernel<", "bwd_weight", False),  # (of these layers only the stem's weight gradient pads)
+    (r"qconv_pad_(short_)?rows_kernel<", "bwd_weight", False),  # (of these layers only the stem's weight gradient pads)
 ]
 
 
