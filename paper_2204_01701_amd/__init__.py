@@ -91,7 +91,7 @@ class Epilogue(ctypes.Structure):
 def epilogue(scale=None, shift=None, relu=False, stat_sum=None, stat_sumsq=None) -> Epilogue:
     """An Epilogue over float32 device tensors of O values (or None); the tensors must outlive the call."""
     e = Epilogue(_ptr(scale), _ptr(shift), int(bool(relu)), _ptr(stat_sum), _ptr(stat_sumsq))
-    e.tensors = [("epi.scale", scale), ("epi.shift", shift), ("epi.sum", stat_sum), ("epi.sumsq", stat_sumsq)]
+    e.tensors = (scale, shift, stat_sum, stat_sumsq)  # (_EPILOGUE: checked with the operands of a call)
     return e
 
 
@@ -262,6 +262,8 @@ _OPERANDS = {name: tuple(tuple(o.split(":")) for o in ops.split()) for name, ops
     "qlayer_linear_bwd_relu": "x:x gy:y y_out:y ta:y tb:y wa:w wb:w wc:w dx:x dwa:g dwb:g dwc:g dba:b dbb:b dbc:b",
 }.items()}
 
+_EPILOGUE = (("epi.scale", "b"), ("epi.shift", "b"), ("epi.sum", "b"), ("epi.sumsq", "b"))
+
 _CONV_FIELDS = struct.Struct("14i")  # ConvDesc
 _LINEAR_FIELDS = struct.Struct("5i")  # LinearDesc
 _dtypes = {}  # (filled on the first call: importing this module does not import torch)
@@ -354,9 +356,10 @@ def _run(name, desc, needs, tensors, workspace, stream, epi=None):
     operands = _OPERANDS[name]
     n = len(tensors)
     if epi is not None and epi[0] is not None:
-        extra = getattr(epi[0], "tensors", ())
-        operands += tuple((en, "b") for en, _ in extra)
-        tensors += tuple(t for _, t in extra)
+        extra = getattr(epi[0], "tensors", None)
+        if extra is not None:
+            operands += _EPILOGUE
+            tensors += extra
     got = _pointers(needs, operands, tensors)
     L = lib()
     ref = ctypes.byref(desc)
