@@ -247,8 +247,8 @@ def _workspace(workspace, need, device, stream=None):
 # operands against the same requirements and raises what is to be raised.
 
 # The tensor operands of an entry point in the order of its arguments, as
-# name:role; the roles are those of _conv_needs.
-_OPERANDS = {name: tuple(tuple(o.split(":")) for o in ops.split()) for name, ops in {
+# name:role, kept as a tuple of names and one of roles; the roles are those of _needs.
+_OPERANDS = {name: tuple(zip(*(o.split(":") for o in ops.split()))) for name, ops in {
     "qlayer_conv2d_fwd": "x:x wa:w wb:w wc:w ba:b bb:b bc:b y:y ta:y tb:y",
     "qlayer_conv2d_fwd_ex": "x:x wa:w wb:w wc:w ba:b bb:b bc:b y:y ta:y tb:y",
     "qlayer_conv2d_bwd_data": "gy:y ta:t tb:y wa:w wb:w wc:w dx:x",
@@ -262,7 +262,7 @@ _OPERANDS = {name: tuple(tuple(o.split(":")) for o in ops.split()) for name, ops
     "qlayer_linear_bwd_relu": "x:x gy:y y_out:y ta:y tb:y wa:w wb:w wc:w dx:x dwa:g dwb:g dwc:g dba:b dbb:b dbc:b",
 }.items()}
 
-_EPILOGUE = (("epi.scale", "b"), ("epi.shift", "b"), ("epi.sum", "b"), ("epi.sumsq", "b"))
+_EPILOGUE = ("epi.scale", "epi.shift", "epi.sum", "epi.sumsq"), ("b", "b", "b", "b")
 
 _CONV_FIELDS = struct.Struct("14i")  # ConvDesc
 _LINEAR_FIELDS = struct.Struct("5i")  # LinearDesc
@@ -306,32 +306,33 @@ def _expect(name, t, numel, dtype, device):
         raise ValueError(f"{name}: dtype {t.dtype}, expected {dtype}")
 
 
-def _checked_pointers(needs, operands, tensors):
+def _checked_pointers(needs, names, roles, tensors):
     """The pointers of `tensors` (raw pointers pass through) and their torch device."""
     dev = _device(*tensors)
-    for (name, role), t in zip(operands, tensors):
+    for name, role, t in zip(names, roles, tensors):
         _expect(name, t, *needs[role], dev)
     return [_ptr(t) for t in tensors], dev
 
 
-def _pointers(needs, operands, tensors):
+def _pointers(needs, roles, tensors):
     """The data pointers of `tensors` (None: NULL) and their device index, or None."""
     out, dev = [], -1
-    for (_, role), t in zip(operands, tensors):
-        if t is None:
-            out.append(None)
-            continue
-        if isinstance(t, int):
-            return None
-        n, d = needs[role]
-        if t.numel() != n or t.dtype is not d or not t.is_cuda or not t.is_contiguous():
-            return None
-        i = t.get_device()
-        if i != dev:
-            if dev >= 0:
+    try:
+        for role, t in zip(roles, tensors):
+            if t is None:
+                out.append(None)
+                continue
+            n, d = needs[role]
+            if t.numel() != n or t.dtype is not d or not t.is_cuda or not t.is_contiguous():
                 return None
-            dev = i
-        out.append(t.data_ptr())
+            i = t.get_device()
+            if i != dev:
+                if dev >= 0:
+                    return None
+                dev = i
+            out.append(t.data_ptr())
+    except AttributeError:  # a raw pointer (asking each operand for its type costs as much as a check)
+        return None
     return (out, dev) if dev >= 0 else None
 
 
@@ -353,14 +354,14 @@ def _run(name, desc, needs, tensors, workspace, stream, epi=None):
 
     epi: the epilogue of an _ex forward (a one-element tuple, its value None or an
     Epilogue, whose tensors are checked with the others)."""
-    operands = _OPERANDS[name]
+    names, roles = _OPERANDS[name]
     n = len(tensors)
     if epi is not None and epi[0] is not None:
         extra = getattr(epi[0], "tensors", None)
         if extra is not None:
-            operands += _EPILOGUE
+            names, roles = names + _EPILOGUE[0], roles + _EPILOGUE[1]
             tensors += extra
-    got = _pointers(needs, operands, tensors)
+    got = _pointers(needs, roles, tensors)
     L = lib()
     ref = ctypes.byref(desc)
     args = () if epi is None else (_epi_ref(epi[0]),)
@@ -371,7 +372,7 @@ def _run(name, desc, needs, tensors, workspace, stream, epi=None):
         else:
             st = stream if isinstance(stream, int) else stream.cuda_stream
     else:
-        ptrs, dev = _checked_pointers(needs, operands, tensors)
+        ptrs, dev = _checked_pointers(needs, names, roles, tensors)
         st = _stream(stream, dev)
     del ptrs[n:]
     if workspace is _NO_WORKSPACE:

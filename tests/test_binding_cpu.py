@@ -105,7 +105,7 @@ def test_sizes(d):
 def test_right_operands_reach_the_call_in_order(name, d, calls):
     tensors = good(name, d)
     assert ql._pointers((ql._linear_needs if isinstance(d, ql.LinearDesc) else ql._conv_needs)(d),
-                        ql._OPERANDS["qlayer_" + name], tuple(tensors.values())) is not None  # (in one pass)
+                        ql._OPERANDS["qlayer_" + name][1], tuple(tensors.values())) is not None  # (in one pass)
     ptrs = [t.ptr for t in tensors.values()]
     run(name, d, tensors)
     # raw pointers, all or in part, pass unchecked
@@ -148,6 +148,6 @@ def test_epilogue_operands_are_checked(name, d, calls):
 def test_unknown_type_codes_are_left_to_the_library():
     d = ql.linear_desc(4, 8, 8, ql.QL_F32)
     d.dtype = 7
-    assert ql._pointers(ql._linear_needs(d), ql._OPERANDS["qlayer_linear_fwd"], (Stub(64, 32, torch.float32),)) is None
+    assert ql._pointers(ql._linear_needs(d), ql._OPERANDS["qlayer_linear_fwd"][1], (Stub(64, 32, torch.float32),)) is None
     with pytest.raises(ql.QLError):
         ql.qlayer_linear_fwd(d, 4096, 4096, 4096, 4096, y=4096, ta=4096, tb=4096)
