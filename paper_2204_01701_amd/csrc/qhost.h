@@ -29,12 +29,13 @@ constexpr int kNumCUs = 256;         // MI355X compute units
 constexpr size_t kAlign = 256;
 constexpr long long kMaxElems = (1LL << 31) - 1;  // 32-bit element offsets in the kernels
 constexpr size_t kMaxSplitBytes = 128ull << 20;  // cap on split-K partial sums (written + read once)
-// Cap on a pass's padded copies (Geom::pad_fwd and its neighbours): beyond it the
-// register-staged kernels take the tensors as they are, so that a layer of a
-// few channels off the vector does not need most of its tensors' memory again.
-// No line of speed: the copies pay at any size (60 -> 100 channels, 3 x 3, bf16, 5 to 9
-// times).  256 x 112 x 112 maps of 60 channels in bf16, three maps a call, stay below.
-constexpr size_t kMaxPadBytes = 2048ull << 20;
+// Cap on a pass's padded copies (Geom::pad_bwd_data, pad_bwd_weight): what X alone
+// can take within 32-bit element offsets in fp32, so the forward's copy is always
+// below.  Beyond it the register-staged kernels take the tensors as they are.  A
+// bound on memory and not a line of speed: 24 x 512 x 512 maps, 20 -> 60 channels, 3 x 3,
+// bf16, input and weight gradient 18.8 and 9.5 ms as they are, 3.3 and 1.8 padded (2.4 GB
+// of copies); a cap of 2 GiB cost such layers four fifths of their speed.
+constexpr size_t kMaxPadBytes = 8192ull << 20;
 // Split-K cost model, in units of one K step of one workgroup alone on a CU:
 // a CU holding two co-resident workgroups finishes both in kSharedRound steps
 // per step each (the second one hides the first one's latency), and one unit
@@ -137,7 +138,7 @@ struct Geom {
     // (0.76 up to 48, 1.0 to 1.15 up to 256, 0.96 above; 1.35 from 1 GFLOP).
     bool pad_fwd() const {
         if (!pad_c_fits() || few_c()) return pad_c_fits();
-        if (!pad_pays() || pad_x_skips() || pad_x_bytes() > kMaxPadBytes) return false;
+        if (!pad_pays() || pad_x_skips()) return false;
         const int K = KH * KW * C;
         if (dt == QL_BF16 || ne == NEURON_QUADRA) return K > 64 / (int)esize() || O > 16;
         return flops() >= 1e9 || (K > 48 && K <= 256);
